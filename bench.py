@@ -577,7 +577,7 @@ def main():
     else:
         alg = algorithmic_bytes(batch)
         dom_s, launches = k_step_s, float(np.mean(passes))
-        dom_kernel = {"gacco": "gacco_kernel", "gputx": "gputx_exec_kernel"}.get(args.scheme, "txn_kernel")
+        dom_kernel = {"gacco": "chain_scan_kernel", "gputx": "gputx_rank_kernel"}.get(args.scheme, "txn_kernel")
     achieved = alg / dom_s / 1e9
     traffic = None
     if os.path.exists(args.traffic_json):
@@ -610,17 +610,13 @@ def main():
               + acc["stream_bytes"] / (probes["stream_GBps"] * 1e9))
     x_roof = batch.n_txns / t_roof
     if args.scheme == "gacco":
-        # every access of the hottest row (reads too) is one turn of its word;
-        # the bound takes the plain store-to-load hand-off per turn
-        _, h = workload.hottest_row_accesses(batch)
-        t_h, h_key = probes["handoff_ns"], "hot_row_accesses_H"
+        # the scan hands no row from transaction to transaction
+        h, t_h, h_key = 0, 0.0, "hot_row_accesses_H"
     elif args.scheme == "gputx":
         # the rank pass hands the hottest row along its accesses, one turn
-        # each; then the K-sets run one after another, each released by the
-        # done counter: at least one store-to-load hand-off per turn and per K-set
+        # each: at least one store-to-load hand-off per turn
         _, h = workload.hottest_row_accesses(batch)
-        h += int(st["ksets"])
-        t_h, h_key = probes["handoff_ns"], "hot_row_accesses_plus_ksets_H"
+        t_h, h_key = probes["handoff_ns"], "hot_row_accesses_H"
     else:
         _, h = workload.hottest_row_writes(batch)
         t_h, h_key = probes["commit_handoff_ns"], "hot_row_writes_H"
@@ -648,7 +644,7 @@ def main():
                         "engine_ms": round(float(np.mean(engine_ns)) / 1e6, 3)}
     eff = min(x_roof, x_cont)
     measured = {"random_access_roof_txn_per_s": round(x_roof, 1), h_key: h,
-                "t_h_ns": t_h, "contention_bound_txn_per_s": round(x_cont, 1),
+                "t_h_ns": t_h, "contention_bound_txn_per_s": round(x_cont, 1) if h else None,
                 "effective_roof_txn_per_s": round(eff, 1), "active_bound": "contention" if x_cont < x_roof else "random-access",
                 "frac_of_effective": round(value / eff, 4), "hot_row_engine": engine_bound, "probes": probes,
                 "per_batch_accesses": acc}

@@ -62,9 +62,11 @@ enum cc_scheme {
   CC_MVCC = 3,   /* multi-version timestamp ordering (TO word + version pointer) */
   CC_TICTOC = 4, /* TicToc: lock bit + 15-bit delta + 48-bit WTS */
   CC_GACCO = 5,  /* GaccO, conflict-graph ordering (Section 2 and Section 3, "Conflict Graph
-                    Ordering"): preprocessing sorts every row's accesses by transaction id into
-                    a lock table; each row is then handed to its accessors in that order, reads
-                    and writes alike.  Deterministic, no aborts.  Needs each transaction's ops
+                    Ordering"): preprocessing sorts the accesses so that each cell's come in
+                    transaction-id order, and every operation gets its value from the ones before
+                    it in its cell's list (a scan).  With wait_limit_us the preprocessing builds
+                    the paper's lock table instead, and each row is handed to its accessors in
+                    that order, reads and writes alike.  Deterministic, no aborts.  Needs each transaction's ops
                     after the previous transaction's (first_op nondecreasing) and
                     CC_MODE_PLAIN; accepts only CC_RUN_STRICT_FENCES, CC_RUN_INDEX_TREE and
                     CC_RUN_SHARED_READS. */
@@ -74,8 +76,8 @@ enum cc_scheme {
                     other conflict aborts it.  Age = index in the batch.  Lock word as 2PL. */
   CC_GPUTX = 7   /* GPUTx, conflict-graph ordering by K-sets (Section 2 and Section 3, "Conflict
                     Graph Ordering"): a transaction's rank is its level in the DAG of
-                    conflicts ordered by transaction id; the transactions of one rank run
-                    together without concurrency control, rank after rank.  Deterministic, no
+                    conflicts ordered by transaction id; the transactions of one rank do not
+                    conflict, and rank after rank is the serial order.  Deterministic, no
                     aborts.  Same batch and run rules as CC_GACCO. */
 };
 #define CC_N_SCHEMES 8
@@ -208,7 +210,8 @@ enum cc_mode { CC_MODE_PLAIN = 0, CC_MODE_EPOCH = 1, CC_MODE_SERVE = 2 };
                                      undefined (reload them before the next run) */
 #define CC_RUN_SHARED_READS 0x80u /* CC_GACCO: reads of a row between two of its writes run together (a
                                      write still waits for every earlier access, a read for every
-                                     earlier write); the paper's GaccO queues reads like writes */
+                                     earlier write); the paper's GaccO queues reads like writes.  Matters
+                                     with wait_limit_us only: the scan runs every access together */
 #define CC_RUN_INDEX_TREE 0x20u   /* keyed batches: look keys up by descending the index's 16-way tree
                                      (one 128-byte node per level) instead of by binary search of the
                                      sorted keys */
@@ -282,7 +285,8 @@ typedef struct {
   uint64_t hbm_cap_bytes; /* CC_MODE_SERVE: admission budget for uncommitted work and, under CC_MVCC, the
                              version arena's size; 0 = no cap (one version slot per op of the stream) */
   uint64_t wait_limit_us; /* CC_GACCO, CC_GPUTX: a team that sees no progress on its waits for this long
-                             stops every team and the run fails with CC_E_LIVELOCK; 0 = 4 s.  It cannot
+                             stops every team and the run fails with CC_E_LIVELOCK; 0 = 4 s, and under
+                             CC_GACCO the scan, which waits for no row.  It cannot
                              trigger while the lock table is consistent (the smallest unfinished
                              transaction can always proceed); a tiny value exercises the stop path.
                              Nonzero for another scheme: CC_E_INVAL */
@@ -304,7 +308,8 @@ enum cc_stat {
   CC_STAT_PASSES = 11,     /* kernel passes run (CC_MODE_PLAIN) */
   CC_STAT_DEFERRED = 12,   /* transactions deferred to a later pass */
   CC_STAT_GRID = 13,       /* workgroups of the first pass */
-  CC_STAT_T_USEFUL_NS = 14,/* summed over transactions: time in attempts that committed */
+  CC_STAT_T_USEFUL_NS = 14,/* summed over transactions: time in attempts that committed (CC_GACCO's and
+                              CC_GPUTX's scan runs the batch as one: its kernel time) */
   CC_STAT_T_ABORT_NS = 15, /* summed over transactions: time in attempts that aborted */
   CC_STAT_T_WAIT_NS = 16,  /* summed over transactions: back-off time between attempts */
   CC_STAT_GAVE_UP = 17,    /* transactions left pending (attempt limit or timestamp overflow) */

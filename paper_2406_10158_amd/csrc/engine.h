@@ -28,6 +28,9 @@ constexpr uint32_t ROW_MASK = (1u << ROW_BITS) - 1u;
 constexpr uint32_t KIND_SHIFT = 28;
 constexpr uint32_t FOLLOWER_BIT = 1u << 30;
 constexpr uint32_t WRITTEN_BIT = 1u << 31;
+// rowk of an operation no transaction names: a follower that writes in a row
+// group that is not written, which no real operation is
+constexpr uint32_t GAP_OP = FOLLOWER_BIT | ((uint32_t)CC_ADD << KIND_SHIFT);
 
 struct DevTxn {
   uint32_t first;  // first op
@@ -231,7 +234,34 @@ hipError_t gacco_prepare(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32
 hipError_t launch_gacco(hipStream_t s, int lanes, int max_ops, int waves_per_wg, int grid, bool strict,
                         const GaccoArgs &a, int n_cu, int *grid_used);
 
-// Kernel arguments for the GPUTx passes (gputx.hip).
+// Ordered execution by cell chains (chain.hip): arguments of its kernels.
+struct ChainArgs {
+  const DevOp *ops;
+  uint64_t n;               // operations
+  const uint32_t *keys;     // sorted by cell ...
+  const uint32_t *vals;     // ... the operations, in serial order within a cell
+  int64_t *data;
+  int64_t *reads;
+  uint64_t *meta, *sum, *total;  // per tile: look-back state (meta is cleared by chain_prepare)
+  uint32_t *base;           // batches with breaks: per operation, 1 + the break its value is relative to (else nullptr)
+  uint64_t *result;         //   per break: the value it leaves
+  uint32_t *ready;          //   per break: its result is there (cleared by chain_prepare)
+  uint32_t *txn_first;      // batches with slot writes: the first operation of an operation's transaction
+  Ctl *ctl;                 // queue and pending_n are counted up from 0
+  uint64_t wait_limit_ticks;
+};
+uint64_t chain_tiles(uint64_t n);
+// Builds and sorts the list of accesses by cell (ids below n_cells): keys and vals hold n words
+// each, sort_scratch radix_sort_scratch_words(n); *keys_out and *vals_out are
+// the sorted list for chain_execute.
+hipError_t chain_prepare(hipStream_t s, const ChainArgs &a, uint64_t n_cells, const DevTxn *txns, uint64_t n_txns,
+                         uint32_t *keys, uint32_t *vals, uint32_t *sort_scratch, uint32_t **keys_out, uint32_t **vals_out);
+// Runs the batch and writes its outcome records: serial key (rank, id), rank 0
+// where rank is nullptr.  Does nothing but mark them pending if ctl->stop is set.
+hipError_t chain_execute(hipStream_t s, bool strict, const ChainArgs &a, DevOutcome *out, uint64_t n_txns,
+                         const uint32_t *rank, uint32_t ns_per_tick_q16, int n_cu, int *grid_used);
+
+// Kernel arguments for GPUTx's rank pass (gputx.hip).
 struct GputxArgs {
   const DevOp *ops;
   const DevTxn *txns;
@@ -239,25 +269,17 @@ struct GputxArgs {
   const uint32_t *rank;       // per row-group leader: its place in its row's list (the turn it waits for)
   uint64_t *words;            // per row: the turn
   uint64_t *kstate;           // per row: (largest rank + 1 of its accessors so far) << 32 | (last writer's rank + 1)
-  uint32_t *txn_rank;         // rank pass output: per transaction
-  const uint32_t *order;      // execution: transaction at each sorted position
-  const uint32_t *order_rank; // execution: its rank
-  const uint32_t *kstart;     // execution: first sorted position of each rank
-  int64_t *data;
-  DevOutcome *out;
-  int64_t *reads;
+  uint32_t *txn_rank;         // output: per transaction
   Ctl *ctl;
   uint64_t wait_limit_ticks;
   uint32_t poll_ticks;
-  uint32_t ns_per_tick_q16;
-  uint32_t has_slot;
-  uint32_t packed;            // rank pass: turn and rank state share the row's word (see gputx.hip)
+  uint32_t packed;            // turn and rank state share the row's word (see gputx.hip)
 };
-hipError_t launch_gputx_pass(hipStream_t s, bool exec, int lanes, int max_ops, int waves_per_wg, int grid,
-                             bool strict, const GputxArgs &a, int n_cu, int *grid_used);
-hipError_t gputx_init_state(hipStream_t s, uint64_t *kstate, uint64_t n_rows, uint32_t *iota, uint64_t n_txns);
+hipError_t launch_gputx_rank(hipStream_t s, int lanes, int max_ops, int waves_per_wg, int grid, bool strict,
+                             const GputxArgs &a, int n_cu, int *grid_used);
+hipError_t gputx_init_state(hipStream_t s, uint64_t *kstate, uint64_t n_rows);
+// Claim counters back to 0, after the rank pass.
 hipError_t gputx_reset(hipStream_t s, Ctl *ctl);
-hipError_t gputx_kstart(hipStream_t s, const uint32_t *rank_sorted, uint64_t n, uint32_t *kstart);
 
 // Device-side ingest of a batch already in device memory (ingest.hip).
 struct IngestTable {
@@ -268,7 +290,8 @@ struct IngestTable {
   uint32_t indexed;    // keyed batches: the table has an index (its ops name rows by key)
 };
 // reduced results in IngestArgs::out
-enum IngestOut { INGEST_ERR = 0, INGEST_MAX_OPS = 1, INGEST_HAS_SLOT = 2, INGEST_UNORDERED = 3, INGEST_KEYED = 4,
+// INGEST_KINDS: bit 0 a WRITE_SLOT, bit 1 a COND_ADD
+enum IngestOut { INGEST_ERR = 0, INGEST_MAX_OPS = 1, INGEST_KINDS = 2, INGEST_UNORDERED = 3, INGEST_KEYED = 4,
                  INGEST_N = 5 };
 // what failed (bits 4-15 of the error word); the host turns it into a message
 enum IngestMsg {

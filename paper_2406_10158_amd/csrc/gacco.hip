@@ -25,7 +25,10 @@
 //    the position of the row's first access in the sorted table; the access
 //    at sorted position p runs when the word equals p and releases by storing
 //    p + 1.  Each row-group leader gets its position (rank) by a scatter.
-//  * Execution: persistent teams of L lanes take transactions in id order
+//  * Execution: by default the same sort, by cell, and the chain scan
+//    (chain.hip), which needs no lock table.  With a bound on the waits
+//    (wait_limit_us), the hand-off kernel (gacco_exec.hip) and the lock table:
+//    persistent teams of L lanes take transactions in id order
 //    from a device counter, so every transaction a team waits for has
 //    already been taken by a running wavefront and the oldest unfinished
 //    transaction can always proceed.  A team polls the words of its waiting

@@ -1,4 +1,5 @@
-// GaccO execution kernel: persistent teams hand every row to its accessors in
+// GaccO's hand-off kernel, for runs that bound its waits (wait_limit_us; the
+// default execution is the chain scan, chain.hip): persistent teams hand every row to its accessors in
 // transaction-id order, using the lock table built by the preprocessing
 // (gacco.hip).  No transaction aborts; each runs once.
 #include "opset.h"

@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(256) ingest_fill_kernel(IngestArgs a) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= a.n_ops) return;
   DevOp d;
-  d.rowk = FOLLOWER_BIT;
+  d.rowk = GAP_OP;
   d.elem = 0;
   d.arg = 0;
   a.dops[i] = d;
@@ -81,7 +81,7 @@ __global__ void __launch_bounds__(256) ingest_pack_kernel(IngestArgs a) {
   auto keyed = [&](const cc_op &o) { return a.op_keys != nullptr && o.table < a.n_tables && a.tab[o.table].indexed; };
   auto ident = [&](uint64_t op, const cc_op &o) -> int64_t { return keyed(o) ? a.op_keys[op] : (int64_t)o.row; };
   uint32_t group_start = 0;
-  bool group_written = false, slot = false, any_keyed = false;
+  bool group_written = false, slot = false, cond = false, any_keyed = false;
   cc_op prev{};
   int64_t prev_id = 0;
   for (uint32_t i = 0; i < x.n_ops; ++i) {
@@ -100,6 +100,7 @@ __global__ void __launch_bounds__(256) ingest_pack_kernel(IngestArgs a) {
       slot = true;
       if ((uint32_t)(o.arg & 0xFF) >= i) { report(a, t, INGEST_MSG_SLOT_SRC, (uint32_t)-CC_E_INVAL); return; }
     }
+    cond |= o.kind == CC_COND_ADD;
     const int64_t id = ident(op, o);
     const bool follower = i > 0 && prev.table == o.table && prev_id == id;
     if (!follower) {
@@ -151,7 +152,7 @@ __global__ void __launch_bounds__(256) ingest_pack_kernel(IngestArgs a) {
   dt.n = x.n_ops;
   a.dtx[t] = dt;
   atomicMax((unsigned long long *)&a.out[INGEST_MAX_OPS], (unsigned long long)x.n_ops);
-  if (slot) atomicOr((unsigned long long *)&a.out[INGEST_HAS_SLOT], 1ull);
+  if (slot || cond) atomicOr((unsigned long long *)&a.out[INGEST_KINDS], (slot ? 1ull : 0ull) | (cond ? 2ull : 0ull));
   if (any_keyed) atomicOr((unsigned long long *)&a.out[INGEST_KEYED], 1ull);
 }
 
