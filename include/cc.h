@@ -407,11 +407,11 @@ cc_status cc_read_table(cc_ctx *ctx, uint32_t table_id, int64_t *out, int out_on
  * in device memory for `scheme`: a batch whose read and write sets are fixed
  * before execution, over existing rows only (paper Section 4.1,
  * "Constraints"; the batch model of Section 3.3).  txns / ops are host
- * arrays (on_device = 0: validated on the host, packed and copied), or
- * device pointers on the context's device (on_device != 0, e.g. torch
- * tensors' data_ptr(): an ingest kernel validates them with the same rules
- * and the same status codes and packs them into the engine's layout, on the
- * context's stream).  Either way the arrays are read during the call only;
+ * arrays (on_device = 0: copied to the device), or device pointers on the
+ * context's device (on_device != 0, e.g. torch tensors' data_ptr()); ingest
+ * kernels validate them with cc_check_batch's rules and status codes, pack
+ * them into the engine's layout and count the rows' writes, on the context's
+ * stream.  Either way the arrays are read during the call only;
  * the caller keeps ownership and may reuse them once it returns.  Errors:
  * CC_E_INVAL (bad scheme/kind, op ranges outside the ops array, two
  * transactions sharing an op, WRITE_SLOT source not earlier, too many ops in
@@ -469,7 +469,8 @@ cc_status cc_fetch_rows(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows);
  * write one of them; *by_default 1 if no row left out of the engine is
  * written more than a quarter as often as the most written one -- one of the
  * conditions under which cc_run uses the engine without CC_RUN_HOT_ENGINE
- * (see there).  Host-side; no device work.
+ * (see there).  The transactions
+ * are counted at the first call that needs them (a kernel over the batch).
  */
 #define CC_ENGINE_MAX_ROWS 32
 cc_status cc_engine_plan(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows, uint32_t *n_rows, uint64_t *n_txns,

@@ -32,6 +32,8 @@ struct Batch {
   DevOutcome *d_out = nullptr;
   int64_t *d_reads = nullptr;
   uint32_t *d_list = nullptr;  // pending transactions between passes
+  void *arena = nullptr;       // one allocation for the buffers whose sizes the counts give
+  size_t arena_bytes = 0;
   uint64_t *d_nodes = nullptr; // MVCC version arena: a 32-byte header (the ring counter), then node_slots x 4 words
   uint64_t node_slots = 0;
   bool keyed = false;            // some ops name their row by key (cc_submit_batch_keyed)
@@ -50,24 +52,22 @@ struct Batch {
   int epoch_grid = 0;
   bool ran = false;
   uint64_t stats[CC_N_STATS] = {};
-  // counted at submission (find_hot_rows): writes to the most written row,
+  // counted at submission (plan_hot_rows): writes to the most written row,
   // and the most written rows (most first); hot_known is false for a batch
   // nobody counted (cc_run_static), which then runs with the contended defaults
   bool hot_known = false;
   uint64_t hot_writes = 0;
   uint32_t n_hot = 0;
   uint32_t hot_rows[HOT_MAX] = {};
-  // OCC hot-row engine, planned at submission (plan_engine): its rows, and
-  // d_part = the transactions that write one of them (n_eng_txns), then the
-  // others; eng_gain: every row left out is written at most a quarter as often
+  // OCC hot-row engine, planned at submission (plan_engine): its rows, and,
+  // once something needs them (split_batch), d_part = the transactions that
+  // write one of them (n_eng_txns), then the others; eng_gain: every row left out is written at most a quarter as often
   // as the most written row
   EngineArgs eng{};
   uint64_t n_eng_txns = 0;
   bool eng_gain = false;
   uint32_t *d_part = nullptr;
   EngineDesc *d_eng_desc = nullptr;  // the engine's transactions with their first op and op count
-  std::vector<uint32_t> eng_part;  // host copies until the upload
-  std::vector<EngineDesc> eng_desc;
 };
 
 }  // namespace
@@ -78,6 +78,10 @@ struct DevIndex {
   int64_t *tree = nullptr;
   IndexDesc desc{};
 };
+
+// Pinned host memory of a context: a batch's host arrays up to this size go to
+// the device in one copy from here (a pageable copy costs about 10 us more).
+constexpr size_t PIN_BYTES = 1u << 20;
 
 struct cc_ctx {
   int device = 0;
@@ -96,7 +100,12 @@ struct cc_ctx {
   IndexDesc *d_idx = nullptr;         // device copy of every table's IndexDesc
   uint32_t *d_latch = nullptr;        // CC_RUN_LATCH: one latch per global row
   uint64_t *d_kstate = nullptr;       // GPUTx: per-row rank state
-  uint64_t *d_ingest = nullptr;       // device-side batch ingest: reduced results
+  uint64_t *d_ingest = nullptr;       // batch submission: reduced results, then histograms
+  uint32_t *d_cnt = nullptr;          //   a count per global row, 0 between submissions
+  unsigned char *d_sub = nullptr;     //   scratch, grown to the largest batch's need
+  size_t sub_bytes = 0;
+  unsigned char *h_pin = nullptr;     // PIN_BYTES of pinned host memory: small arrays on their way to or from the device
+  std::vector<std::pair<void *, size_t>> pool;  // released batches' arenas (see release_arena)
   unsigned char *d_static = nullptr;  // cc_run_static: this device's static scratch (never freed)
   std::map<uint64_t, Batch> batches;
   uint64_t next_batch = 1;
@@ -180,43 +189,27 @@ cc_status resolve_keys(cc_ctx *c, Batch &b, const cc_run_params &p, float *ms) {
   return CC_OK;
 }
 
-void free_batch(Batch &b) {
-  if (b.d_ops) (void)hipFree(b.d_ops);
-  if (b.d_txns) (void)hipFree(b.d_txns);
-  if (b.d_out) (void)hipFree(b.d_out);
-  if (b.d_reads) (void)hipFree(b.d_reads);
-  if (b.d_list) (void)hipFree(b.d_list);
+// Arenas of released batches are kept for the next ones of about their size,
+// so that a stream of batches does not allocate (a 0.3 GB arena cost 0.4 ms a
+// batch): at most POOL_ARENAS of at most POOL_BYTES in all, given back with the
+// context or when an allocation fails.  The caller has waited for the context's
+// stream.
+constexpr size_t POOL_ARENAS = 4, POOL_BYTES = 512u << 20;
+
+void free_batch(cc_ctx *c, Batch &b) {
+  if (b.arena) {
+    size_t kept = b.arena_bytes;
+    for (auto &a : c->pool) kept += a.second;
+    if (kept <= POOL_BYTES && c->pool.size() < POOL_ARENAS) c->pool.emplace_back(b.arena, b.arena_bytes);
+    else (void)hipFree(b.arena);
+  }
   if (b.d_part) (void)hipFree(b.d_part);
-  b.d_part = nullptr;
   if (b.d_eng_desc) (void)hipFree(b.d_eng_desc);
-  b.d_eng_desc = nullptr;
   if (b.d_nodes) (void)hipFree(b.d_nodes);
-  if (b.d_opkeys) (void)hipFree(b.d_opkeys);
-  if (b.d_meta) (void)hipFree(b.d_meta);
-  if (b.d_rows) (void)hipFree(b.d_rows);
-  b.d_opkeys = nullptr;
-  b.d_meta = nullptr;
-  b.d_rows = nullptr;
-  if (b.d_rank) (void)hipFree(b.d_rank);
-  if (b.d_gscratch) (void)hipFree(b.d_gscratch);
-  if (b.d_tscratch) (void)hipFree(b.d_tscratch);
-  b.d_tscratch = nullptr;
-  if (b.d_chain) (void)hipFree(b.d_chain);
   if (b.d_breaks) (void)hipFree(b.d_breaks);
-  b.d_chain = b.d_breaks = nullptr;
-  b.d_rank = nullptr;
-  b.d_gscratch = nullptr;
   if (b.epoch_graph) (void)hipGraphExecDestroy(b.epoch_graph);
   if (b.d_arrival) (void)hipFree(b.d_arrival);
-  b.d_arrival = nullptr;
-  b.epoch_graph = nullptr;
-  b.d_list = nullptr;
-  b.d_nodes = nullptr;
-  b.node_slots = 0;
-  b.d_ops = nullptr;
-  b.d_txns = nullptr;
-  b.d_out = nullptr;
-  b.d_reads = nullptr;
+  b = Batch{};
 }
 
 // Percentile of committed commit times (host side, after a run).
@@ -312,9 +305,11 @@ cc_status cc_init(cc_ctx **out, const cc_config *cfg) {
     return CC_E_HIP;
   }
   c->wallclock_khz = (uint32_t)khz;
-  if (hipMalloc(&c->d_ctl, sizeof(Ctl)) != hipSuccess) {
+  if (hipMalloc(&c->d_ctl, sizeof(Ctl)) != hipSuccess ||
+      hipHostMalloc((void **)&c->h_pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+    if (c->d_ctl) (void)hipFree(c->d_ctl);
     delete c;
-    g_init_err = "hipMalloc of the control block failed";
+    g_init_err = "allocation of the control block failed";
     return CC_E_NOMEM;
   }
   for (auto &e : c->ev) {
@@ -341,7 +336,8 @@ cc_status cc_destroy(cc_ctx *c) {
   if (!c) return CC_OK;
   activate(c);
   (void)hipStreamSynchronize(c->stream);
-  for (auto &kv : c->batches) free_batch(kv.second);
+  for (auto &kv : c->batches) free_batch(c, kv.second);
+  for (auto &a : c->pool) (void)hipFree(a.first);
   for (auto &ix : c->indexes) {
     if (ix.keys) (void)hipFree(ix.keys);
     if (ix.rows) (void)hipFree(ix.rows);
@@ -351,6 +347,9 @@ cc_status cc_destroy(cc_ctx *c) {
   if (c->d_latch) (void)hipFree(c->d_latch);
   if (c->d_kstate) (void)hipFree(c->d_kstate);
   if (c->d_ingest) (void)hipFree(c->d_ingest);
+  if (c->d_cnt) (void)hipFree(c->d_cnt);
+  if (c->d_sub) (void)hipFree(c->d_sub);
+  if (c->h_pin) (void)hipHostFree(c->h_pin);
   if (c->d_data) (void)hipFree(c->d_data);
   if (c->d_words) (void)hipFree(c->d_words);
   if (c->d_aux) (void)hipFree(c->d_aux);
@@ -758,41 +757,26 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   return CC_OK;
 }
 
-// The hot-row engine's plan from the per-row write counts (see find_hot_rows).
-static void plan_engine(const DevOp *dops, const DevTxn *dtx, uint64_t n_txns, const std::vector<Table> &tables,
-                        const std::vector<uint32_t> &cnt, Batch &b) {
+// The hot-row engine's plan (hot_engine.h) from the most written rows, most
+// first: at most ENG_MAX of them, each written at least max(2, n_txns / 4096)
+// times, of at most ENG_FIELDS fields and ENG_VALS cells in all.  eng_gain
+// holds when every row left out is written at most a quarter as often as the
+// most written row: otherwise the rest of the batch is about as contended as
+// the engine's share, and the engine's serial pass gains nothing.
+static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &tables, Batch &b) {
   b.eng = EngineArgs{};
-  b.n_eng_txns = 0;
   b.eng_gain = false;
-  b.eng_part.clear();
-  b.eng_desc.clear();
-  const uint32_t thr = (uint32_t)std::max<uint64_t>(2, n_txns / 4096);
-  // candidates: the most written rows (more than fit, to know the best row left out)
-  constexpr int NC = ENG_MAX + 16;
-  uint32_t cc[NC] = {}, cr[NC] = {};
-  int nc = 0;
-  for (uint64_t r = 0; r < cnt.size(); ++r) {
-    const uint32_t c = cnt[r];
-    if (c == 0 || (nc == NC && c <= cc[NC - 1])) continue;
-    int i = nc < NC ? nc++ : NC - 1;
-    while (i > 0 && cc[i - 1] < c) {
-      cc[i] = cc[i - 1];
-      cr[i] = cr[i - 1];
-      --i;
-    }
-    cc[i] = c;
-    cr[i] = (uint32_t)r;
-  }
-  if (nc == 0 || cc[0] < thr) return;
+  const uint32_t thr = (uint32_t)std::max<uint64_t>(2, b.n_txns / 4096);
+  if (nc == 0 || (uint32_t)(cand[0] >> 32) < thr) return;
   uint32_t left_out = 0;  // writes of the most written row not taken
   bool full = false;
   for (int i = 0; i < nc; ++i) {
-    const uint32_t r = cr[i];
+    const uint32_t r = ~(uint32_t)cand[i], writes = (uint32_t)(cand[i] >> 32);
     const Table *tb = nullptr;
     for (const Table &t : tables)
       if (r >= t.row_base && r < t.row_base + t.n_rows) tb = &t;
-    bool take = !full && cc[i] >= thr && tb && tb->n_fields <= (uint32_t)ENG_FIELDS &&
-                b.eng.n_vals + tb->n_fields <= (uint32_t)ENG_VALS;
+    const bool take = !full && writes >= thr && tb && tb->n_fields <= (uint32_t)ENG_FIELDS &&
+                      b.eng.n_vals + tb->n_fields <= (uint32_t)ENG_VALS;
     if (take) {
       const uint32_t k = b.eng.n_rows++;
       b.eng.row[k] = r;
@@ -801,106 +785,79 @@ static void plan_engine(const DevOp *dops, const DevTxn *dtx, uint64_t n_txns, c
       b.eng.n_vals += tb->n_fields;
       full = b.eng.n_rows == (uint32_t)ENG_MAX;
     } else if (!left_out) {
-      left_out = cc[i];
+      left_out = writes;
     }
   }
   if (b.eng.n_rows == 0) return;
   b.eng.off[b.eng.n_rows] = b.eng.n_vals;
   // a row below the candidates is written at most as often as the last candidate
-  if (!left_out && nc == NC) left_out = cc[NC - 1];
-  b.eng_gain = (uint64_t)left_out * 4 <= (uint64_t)cc[0];
-  std::vector<uint8_t> eng_of(cnt.size(), 0);  // engine index + 1 of a row (0: not an engine row)
-  for (uint32_t k = 0; k < b.eng.n_rows; ++k) eng_of[b.eng.row[k]] = (uint8_t)(k + 1);
-  std::vector<uint8_t> in_eng(n_txns, 0);
-  for (uint64_t t = 0; t < n_txns; ++t)
-    for (uint32_t i = 0; i < dtx[t].n && !in_eng[t]; ++i) {
-      const uint32_t rk = dops[dtx[t].first + i].rowk;
-      in_eng[t] = (rk & WRITTEN_BIT) && eng_of[rk & ROW_MASK];
-    }
-  b.eng_part.reserve(n_txns);
-  for (uint64_t t = 0; t < n_txns; ++t)
-    if (in_eng[t]) {
-      uint32_t emask = 0;  // the engine rows the transaction touches, read or written
-      for (uint32_t i = 0; i < dtx[t].n; ++i) {
-        const uint32_t k = eng_of[dops[dtx[t].first + i].rowk & ROW_MASK];
-        if (k) emask |= 1u << (k - 1);
-      }
-      b.eng_part.push_back((uint32_t)t);
-      b.eng_desc.push_back(EngineDesc{(uint32_t)t, dtx[t].first, dtx[t].n, emask});
-    }
-  b.n_eng_txns = b.eng_part.size();
-  for (uint64_t t = 0; t < n_txns; ++t)
-    if (!in_eng[t]) b.eng_part.push_back((uint32_t)t);
-  if (b.n_eng_txns == 0) {
-    b.eng = EngineArgs{};
-    b.eng_part.clear();
-    b.eng_desc.clear();
-  }
+  if (!left_out && nc == PLAN_CAND) left_out = (uint32_t)(cand[nc - 1] >> 32);
+  b.eng_gain = (uint64_t)left_out * 4 <= cand[0] >> 32;
 }
 
-// Uploads the engine's transaction order planned at submission (nothing
-// without engine rows).
-static hipError_t upload_engine_plan(cc_ctx *c, Batch &b) {
-  if (b.n_eng_txns == 0) return hipSuccess;
-  hipError_t e = hipMalloc(&b.d_part, b.eng_part.size() * sizeof(uint32_t));
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b.d_part, b.eng_part.data(), b.eng_part.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
-                       c->stream);
-  if (e == hipSuccess) e = hipMalloc(&b.d_eng_desc, b.eng_desc.size() * sizeof(EngineDesc));
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(b.d_eng_desc, b.eng_desc.data(), b.eng_desc.size() * sizeof(EngineDesc),
-                       hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  b.eng_part = std::vector<uint32_t>();
-  b.eng_desc = std::vector<EngineDesc>();
-  return e;
-}
-
-// The batch's most written rows, counted at submission from its packed
-// descriptors: write accesses (row groups that write) per global row; the
-// most written row, and every row written at least a quarter as often, at
-// most HOT_MAX of them, most written first (ties: lower row first).
-//
-// With them, the OCC hot-row engine's plan (hot_engine.h): its rows are the
-// most written rows, at most ENG_MAX, each written at least
-// max(2, n_txns / 4096) times, of at most ENG_FIELDS fields and ENG_VALS
-// cells in all, most written first; its transactions are those that write
-// one of them, listed first in eng_part (in batch order), the others after
-// them.  eng_gain holds when every row left out is written at most a quarter
-// as often as the most written row: otherwise the rest of the batch is about
-// as contended as the engine's share, and the engine's serial pass gains
-// nothing.
-void find_hot_rows(const DevOp *dops, uint64_t n_ops, const DevTxn *dtx, uint64_t n_txns,
-                   const std::vector<Table> &tables, uint64_t total_rows, Batch &b) {
-  std::vector<uint32_t> cnt(std::max<uint64_t>(total_rows, 1), 0u);
-  for (uint64_t i = 0; i < n_ops; ++i) {
-    const uint32_t rk = dops[i].rowk;
-    if (!(rk & FOLLOWER_BIT) && (rk & WRITTEN_BIT)) ++cnt[rk & ROW_MASK];
-  }
-  if (b.scheme == CC_OCC) plan_engine(dops, dtx, n_txns, tables, cnt, b);
-  uint32_t top = 0;
-  for (uint32_t c : cnt) top = std::max(top, c);
+// The batch's most written rows, counted at submission (write accesses per
+// global row; ingest.hip): the most written row, and every row written at least
+// a quarter as often, at most HOT_MAX of them, most written first (ties: lower
+// row first).  With them, OCC's engine plan.
+static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables, Batch &b) {
+  const uint64_t *cand = res + INGEST_CAND;
+  int nc = 0;
+  while (nc < PLAN_CAND && cand[nc]) ++nc;
+  if (b.scheme == CC_OCC) plan_engine(cand, nc, tables, b);
+  const uint32_t top = (uint32_t)res[INGEST_TOP];
   b.hot_known = true;
   b.hot_writes = top;
   b.n_hot = 0;
-  if (top == 0) return;
   const uint32_t thr = std::max<uint32_t>(1u, (top + 3) / 4);
-  uint32_t best_c[HOT_MAX] = {}, best_r[HOT_MAX] = {};
-  uint32_t n = 0;
-  for (uint64_t r = 0; r < total_rows; ++r) {
-    const uint32_t c = cnt[r];
-    if (c < thr || (n == (uint32_t)HOT_MAX && c <= best_c[HOT_MAX - 1])) continue;
-    uint32_t i = n < (uint32_t)HOT_MAX ? n++ : (uint32_t)HOT_MAX - 1;
-    while (i > 0 && best_c[i - 1] < c) {
-      best_c[i] = best_c[i - 1];
-      best_r[i] = best_r[i - 1];
-      --i;
-    }
-    best_c[i] = c;
-    best_r[i] = (uint32_t)r;
+  for (int i = 0; i < nc && i < HOT_MAX && (uint32_t)(cand[i] >> 32) >= thr; ++i) b.hot_rows[b.n_hot++] = ~(uint32_t)cand[i];
+}
+
+// At least `bytes` of submission scratch.  It grows to the largest batch's
+// need; a very large one is given back when the submission is over (trim_sub).
+static hipError_t need_sub(cc_ctx *c, size_t bytes) {
+  if (bytes <= c->sub_bytes) return hipSuccess;
+  if (c->d_sub) (void)hipFree(c->d_sub);
+  c->d_sub = nullptr;
+  c->sub_bytes = 0;
+  const hipError_t e = hipMalloc(&c->d_sub, bytes);
+  if (e == hipSuccess) c->sub_bytes = bytes;
+  return e;
+}
+static void trim_sub(cc_ctx *c) {
+  constexpr size_t KEEP = 256u << 20;
+  if (c->sub_bytes <= KEEP) return;
+  (void)hipFree(c->d_sub);
+  c->d_sub = nullptr;
+  c->sub_bytes = 0;
+}
+
+// Splits the batch into the engine's transactions and the others, on the
+// device (once; nothing without engine rows).
+static hipError_t split_batch(cc_ctx *c, Batch &b) {
+  if (b.eng.n_rows == 0 || b.d_part || b.n_txns == 0) return hipSuccess;
+  uint32_t *part = nullptr, n_eng = 0;
+  EngineDesc *desc = nullptr;
+  hipError_t e = need_sub(c, split_scratch_words(b.n_txns) * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMalloc(&part, b.n_txns * sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMalloc(&desc, b.n_txns * sizeof(EngineDesc));
+  if (e == hipSuccess) e = launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, (uint32_t *)c->d_sub, part, desc);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(&n_eng, (uint32_t *)c->d_sub + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e != hipSuccess) {
+    if (part) (void)hipFree(part);
+    if (desc) (void)hipFree(desc);
+    return e;
   }
-  for (uint32_t i = 0; i < n; ++i) b.hot_rows[i] = best_r[i];
-  b.n_hot = n;
+  b.d_part = part;
+  b.d_eng_desc = desc;
+  b.n_eng_txns = n_eng;
+  return hipSuccess;
+}
+
+// Where the engine runs unless the caller says otherwise (see run_batch).
+static bool engine_by_default(const Batch &b) {
+  return b.eng.n_rows && b.eng_gain && b.max_ops <= 32 && (double)b.hot_writes / (double)b.n_txns >= 0.1;
 }
 
 // Run parameters against the scheme, before anything touches the device
@@ -987,29 +944,55 @@ cc_status cc_check_batch(uint32_t n_tables, const uint64_t *n_rows, const uint32
 }
 
 // Device buffers of a batch: descriptors, outcomes, read values, pending
-// list, and the scheme's extras.  All or nothing.
-static hipError_t alloc_batch(Batch &b, int scheme, bool keyed) {
-  const bool ordered_scheme = scheme == CC_GACCO || scheme == CC_GPUTX;
+// list, and the scheme's extras, in one allocation.  All or nothing.
+static hipError_t alloc_batch(cc_ctx *c, Batch &b, bool keyed) {
+  const bool ordered_scheme = b.scheme == CC_GACCO || b.scheme == CC_GPUTX;
   const uint64_t n_ops = b.n_ops, n_txns = b.n_txns;
-  auto alloc = [&](void **p, size_t bytes) -> hipError_t { return hipMalloc(p, bytes ? bytes : 16); };
-  hipError_t e;
-  if ((e = alloc((void **)&b.d_ops, n_ops * sizeof(DevOp))) != hipSuccess ||
-      (e = alloc((void **)&b.d_txns, n_txns * sizeof(DevTxn))) != hipSuccess ||
-      (e = alloc((void **)&b.d_out, n_txns * sizeof(DevOutcome))) != hipSuccess ||
-      (e = alloc((void **)&b.d_reads, n_ops * sizeof(int64_t))) != hipSuccess ||
-      (e = alloc((void **)&b.d_list, n_txns * sizeof(uint32_t))) != hipSuccess ||
-      (ordered_scheme && (e = alloc((void **)&b.d_rank, n_ops * sizeof(uint32_t))) != hipSuccess) ||
-      (ordered_scheme &&
-       (e = alloc((void **)&b.d_gscratch, gacco_scratch_words(n_ops) * sizeof(uint32_t))) != hipSuccess) ||
-      (ordered_scheme &&
-       (e = alloc((void **)&b.d_chain, 3 * chain_tiles(n_ops) * sizeof(uint64_t))) != hipSuccess) ||
-      (scheme == CC_GPUTX && (e = alloc((void **)&b.d_tscratch, n_txns * sizeof(uint32_t))) != hipSuccess) ||
-      (keyed && (e = alloc((void **)&b.d_opkeys, n_ops * sizeof(int64_t))) != hipSuccess) ||
-      (keyed && (e = alloc((void **)&b.d_meta, n_ops * sizeof(uint32_t))) != hipSuccess) ||
-      (keyed && (e = alloc((void **)&b.d_rows, n_ops * sizeof(uint32_t))) != hipSuccess)) {
-    free_batch(b);
-    return e;
+  size_t bytes = 0;
+  auto carve = [&](unsigned char *base) {
+    bytes = 0;
+    auto take = [&](auto **p, bool want, uint64_t n) {
+      if (!want) return;
+      if (base) *p = reinterpret_cast<std::remove_reference_t<decltype(*p)>>(base + bytes);
+      bytes += (std::max<uint64_t>(n, 1) * sizeof(**p) + 255) / 256 * 256;
+    };
+    take(&b.d_ops, true, n_ops);
+    take(&b.d_txns, true, n_txns);
+    take(&b.d_out, true, n_txns);
+    take(&b.d_reads, true, n_ops);
+    take(&b.d_list, true, n_txns);
+    take(&b.d_rank, ordered_scheme, n_ops);
+    take(&b.d_gscratch, ordered_scheme, gacco_scratch_words(n_ops));
+    take(&b.d_chain, ordered_scheme, 3 * chain_tiles(n_ops));
+    take(&b.d_tscratch, b.scheme == CC_GPUTX, n_txns);
+    take(&b.d_opkeys, keyed, n_ops);
+    take(&b.d_meta, keyed, n_ops);
+    take(&b.d_rows, keyed, n_ops);
+  };
+  carve(nullptr);
+  auto best = c->pool.end();
+  for (auto it = c->pool.begin(); it != c->pool.end(); ++it)
+    if (it->second >= bytes && it->second / 4 <= bytes && (best == c->pool.end() || it->second < best->second)) best = it;
+  if (best != c->pool.end()) {
+    b.arena = best->first;
+    b.arena_bytes = best->second;
+    c->pool.erase(best);
+  } else {
+    hipError_t e = hipMalloc(&b.arena, bytes);
+    if (e == hipErrorOutOfMemory && !c->pool.empty()) {
+      // the kept arenas first
+      (void)hipGetLastError();
+      for (auto &a : c->pool) (void)hipFree(a.first);
+      c->pool.clear();
+      e = hipMalloc(&b.arena, bytes);
+    }
+    if (e != hipSuccess) {
+      b.arena = nullptr;
+      return e;
+    }
+    b.arena_bytes = bytes;
   }
+  carve((unsigned char *)b.arena);
   return hipSuccess;
 }
 
@@ -1057,6 +1040,25 @@ static const char *ingest_message(uint32_t m) {
   }
 }
 
+// The ingest kernels' view of the tables and of a batch's arrays on the device.
+static IngestArgs ingest_args(const cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc_op *ops, uint64_t n_ops) {
+  IngestArgs ia{};
+  ia.txns = txns;
+  ia.ops = ops;
+  ia.n_txns = n_txns;
+  ia.n_ops = n_ops;
+  ia.n_tables = (uint32_t)c->tables.size();
+  for (uint32_t t = 0; t < ia.n_tables; ++t) {
+    const Table &tb = c->tables[t];
+    const bool indexed = t < c->indexes.size() && c->indexes[t].keys != nullptr;
+    ia.tab[t] = IngestTable{tb.n_rows, tb.row_base, tb.elem_base, tb.n_fields, indexed ? 1u : 0u};
+  }
+  return ia;
+}
+
+// Device arrays are taken where they are; host arrays are copied into the
+// submission scratch first.  Either way the ingest kernels validate, pack and
+// count, and one copy brings back what the host needs.
 static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc_op *ops, uint64_t n_ops,
                              const int64_t *op_keys, int scheme, int on_device, uint64_t *batch_id) {
   if (!c || !batch_id) return CC_E_INVAL;
@@ -1064,167 +1066,115 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   if (scheme < 0 || scheme >= CC_N_SCHEMES) return fail(c, CC_E_INVAL, "unknown scheme");
   if (!c->frozen) return fail(c, CC_E_STATE, "load the tables before submitting a batch");
   if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
-  std::vector<bool> indexed(c->tables.size(), false);
-  for (size_t t = 0; t < c->indexes.size() && t < indexed.size(); ++t) indexed[t] = c->indexes[t].keys != nullptr;
+  if ((n_txns && !txns) || (n_ops && !ops)) return fail(c, CC_E_INVAL, "null array");
+  if (n_txns > 0xFFFFFFFFull || n_ops > 0xFFFFFFFFull) return fail(c, CC_E_RANGE, "batch too large");
+  if (on_device &&
+      (!device_range(c, txns, n_txns * sizeof(cc_txn)) || !device_range(c, ops, n_ops * sizeof(cc_op)) ||
+       (op_keys && !device_range(c, op_keys, n_ops * sizeof(int64_t)))))
+    return fail(c, CC_E_INVAL, "on_device arrays must lie in device memory of the context's device");
+  bool any_index = false;
+  for (const DevIndex &x : c->indexes) any_index |= x.keys != nullptr;
+  const bool maybe_keyed = op_keys && any_index;
   const bool ordered_scheme = scheme == CC_GACCO || scheme == CC_GPUTX;
   Batch b;
   b.scheme = scheme;
   b.n_txns = n_txns;
   b.n_ops = n_ops;
-
-  if (on_device) {
-    // the caller's arrays are in device memory: validate and pack them there
-    if ((n_txns && !txns) || (n_ops && !ops)) return fail(c, CC_E_INVAL, "null array");
-    if (n_txns > 0xFFFFFFFFull || n_ops > 0xFFFFFFFFull) return fail(c, CC_E_RANGE, "batch too large");
-    if (!device_range(c, txns, n_txns * sizeof(cc_txn)) || !device_range(c, ops, n_ops * sizeof(cc_op)) ||
-        (op_keys && !device_range(c, op_keys, n_ops * sizeof(int64_t))))
-      return fail(c, CC_E_INVAL, "on_device arrays must lie in device memory of the context's device");
-    bool any_index = false;
-    for (bool x : indexed) any_index |= x;
-    const bool maybe_keyed = op_keys && any_index;
-    hipError_t e = alloc_batch(b, scheme, maybe_keyed);
-    if (e != hipSuccess) return hip_fail(c, e, "batch allocation");
-    if (!c->d_ingest && (e = hipMalloc(&c->d_ingest, INGEST_N * sizeof(uint64_t))) != hipSuccess) {
-      free_batch(b);
-      return hip_fail(c, e, "ingest buffer allocation");
-    }
-    IngestArgs ia{};
-    ia.txns = txns;
-    ia.ops = ops;
-    ia.op_keys = maybe_keyed ? op_keys : nullptr;
-    ia.n_txns = n_txns;
-    ia.n_ops = n_ops;
-    ia.n_tables = (uint32_t)c->tables.size();
-    for (uint32_t t = 0; t < ia.n_tables; ++t) {
-      const Table &tb = c->tables[t];
-      ia.tab[t] = IngestTable{tb.n_rows, tb.row_base, tb.elem_base, tb.n_fields, (uint32_t)(indexed[t] ? 1 : 0)};
-    }
-    ia.dops = b.d_ops;
-    ia.dtx = b.d_txns;
-    ia.owner = (uint32_t *)b.d_reads;  // n_ops x 8 bytes, cleared below before any run
-    ia.meta = maybe_keyed ? b.d_meta : nullptr;
-    ia.rows0 = maybe_keyed ? b.d_rows : nullptr;
-    ia.out = c->d_ingest;
-    uint64_t res[INGEST_N] = {};
-    e = launch_ingest(c->stream, ia);
-    if (e == hipSuccess && maybe_keyed && n_ops)
-      e = hipMemcpyAsync(b.d_opkeys, op_keys, n_ops * sizeof(int64_t), hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess && n_ops) e = hipMemsetAsync(b.d_reads, 0, n_ops * sizeof(int64_t), c->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(res, c->d_ingest, sizeof res, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) {
-      free_batch(b);
-      return hip_fail(c, e, "batch ingest");
-    }
-    if (res[INGEST_ERR] != ~0ull) {
-      free_batch(b);
-      const uint64_t w = res[INGEST_ERR];
-      const cc_status code = -(cc_status)(w & 15u);
-      return fail(c, code, std::string(ingest_message((uint32_t)((w >> 4) & 0xFFFu))) + " (transaction " +
-                               std::to_string(w >> 16) + ")");
-    }
-    if (ordered_scheme && res[INGEST_UNORDERED]) {
-      free_batch(b);
-      return fail(c, CC_E_INVAL,
-                  "CC_GACCO and CC_GPUTX need each transaction's ops after the previous transaction's (first_op "
-                  "nondecreasing)");
-    }
-    b.max_ops = (uint32_t)res[INGEST_MAX_OPS];
-    b.has_slot = (res[INGEST_KINDS] & 1) != 0;
-    b.has_cond = (res[INGEST_KINDS] & 2) != 0;
-    b.keyed = res[INGEST_KEYED] != 0;
-    if ((e = alloc_breaks(b)) != hipSuccess) {
-      free_batch(b);
-      return hip_fail(c, e, "batch allocation");
-    }
-    if (maybe_keyed && !b.keyed) {
-      (void)hipFree(b.d_opkeys);
-      (void)hipFree(b.d_meta);
-      (void)hipFree(b.d_rows);
-      b.d_opkeys = nullptr;
-      b.d_meta = nullptr;
-      b.d_rows = nullptr;
-    }
-    if (!b.keyed) {
-      // the packed descriptors come back once, to count the rows' writes
-      std::vector<DevOp> hd(n_ops);
-      std::vector<DevTxn> ht(n_txns);
-      if (n_ops && (e = hipMemcpy(hd.data(), b.d_ops, n_ops * sizeof(DevOp), hipMemcpyDeviceToHost)) != hipSuccess) {
-        free_batch(b);
-        return hip_fail(c, e, "batch descriptors");
-      }
-      if (n_txns && (e = hipMemcpy(ht.data(), b.d_txns, n_txns * sizeof(DevTxn), hipMemcpyDeviceToHost)) != hipSuccess) {
-        free_batch(b);
-        return hip_fail(c, e, "batch descriptors");
-      }
-      find_hot_rows(hd.data(), n_ops, ht.data(), n_txns, c->tables, c->total_rows, b);
-      if ((e = upload_engine_plan(c, b)) != hipSuccess) {
-        free_batch(b);
-        return hip_fail(c, e, "engine plan upload");
-      }
-    }
-    const uint64_t id = c->next_batch++;
-    c->batches[id] = b;
-    *batch_id = id;
-    return CC_OK;
+  if (!c->d_ingest)
+    HIP_OR(c, hipMalloc(&c->d_ingest, INGEST_N * sizeof(uint64_t) + (PLAN_COUNTS + PLAN_BINS) * sizeof(uint32_t)));
+  const uint64_t n_rows = std::max<uint64_t>(c->total_rows, 1);
+  if (!c->d_cnt) {
+    HIP_OR(c, hipMalloc(&c->d_cnt, n_rows * sizeof(uint32_t)));
+    HIP_OR(c, hipMemsetAsync(c->d_cnt, 0, n_rows * sizeof(uint32_t), c->stream));
   }
-
-  std::vector<DevOp> dops;
-  std::vector<DevTxn> dtx;
-  uint32_t max_ops = 0;
-  bool has_slot = false, has_cond = false, ordered = true;
-  cc_status st = validate_and_pack(c, c->tables, txns, n_txns, ops, n_ops, &dops, &dtx, &max_ops, &has_slot, &has_cond,
-                                   &ordered, op_keys, op_keys ? &indexed : nullptr);
-  if (st) return st;
-  if (ordered_scheme && !ordered)
-    return fail(c, CC_E_INVAL,
-                "CC_GACCO and CC_GPUTX need each transaction's ops after the previous transaction's (first_op nondecreasing)");
-  // keyed ops of the transactions (ops no transaction refers to are never looked up)
-  std::vector<uint32_t> meta;
-  std::vector<uint32_t> rows0;
-  bool keyed = false;
-  if (op_keys) {
-    meta.assign(n_ops, 0u);
-    rows0.assign(n_ops, 0u);
-    for (uint64_t i = 0; i < n_ops; ++i) rows0[i] = ops[i].row;
-    for (uint64_t t = 0; t < n_txns; ++t)
-      for (uint32_t i = 0; i < txns[t].n_ops; ++i) {
-        const uint64_t k = txns[t].first_op + i;
-        if (indexed[ops[k].table]) {
-          meta[k] = META_KEYED | ((uint32_t)ops[k].table << 16) | ops[k].field;
-          keyed = true;
-        }
-      }
-  }
-  b.max_ops = max_ops;
-  b.has_slot = has_slot;
-  b.has_cond = has_cond;
-  b.keyed = keyed;
-  // keyed ops learn their rows only when the index is searched, at the run
-  if (!keyed) find_hot_rows(dops.data(), n_ops, dtx.data(), n_txns, c->tables, c->total_rows, b);
-  hipError_t e = alloc_batch(b, scheme, keyed);
-  if (e == hipSuccess && (e = alloc_breaks(b)) != hipSuccess) free_batch(b);
+  // scratch: [the host's arrays], keys, candidates, marked rows, owners
+  const uint64_t staged = on_device ? 0 : n_ops * sizeof(cc_op) + n_txns * sizeof(cc_txn);
+  hipError_t e = need_sub(c, staged + n_ops * 16 + plan_cand_max(n_ops) * 8 + 256);
+  if (e == hipSuccess) e = alloc_batch(c, b, maybe_keyed);
   if (e != hipSuccess) return hip_fail(c, e, "batch allocation");
-  auto copy_in = [&]() -> hipError_t {
-    hipError_t r = hipSuccess;
-    if (n_ops) r = hipMemcpyAsync(b.d_ops, dops.data(), n_ops * sizeof(DevOp), hipMemcpyHostToDevice, c->stream);
-    if (r == hipSuccess && n_txns)
-      r = hipMemcpyAsync(b.d_txns, dtx.data(), n_txns * sizeof(DevTxn), hipMemcpyHostToDevice, c->stream);
-    if (r == hipSuccess && n_ops) r = hipMemsetAsync(b.d_reads, 0, n_ops * sizeof(int64_t), c->stream);
-    if (r == hipSuccess && keyed)
-      r = hipMemcpyAsync(b.d_opkeys, op_keys, n_ops * sizeof(int64_t), hipMemcpyHostToDevice, c->stream);
-    if (r == hipSuccess && keyed)
-      r = hipMemcpyAsync(b.d_meta, meta.data(), n_ops * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream);
-    if (r == hipSuccess && keyed)
-      r = hipMemcpyAsync(b.d_rows, rows0.data(), n_ops * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream);
-    if (r == hipSuccess) r = hipStreamSynchronize(c->stream);
-    return r;
-  };
-  if ((e = copy_in()) != hipSuccess || (e = upload_engine_plan(c, b)) != hipSuccess) {
-    free_batch(b);
-    return hip_fail(c, e, "batch upload");
+  if (!on_device) {
+    cc_op *s_ops = (cc_op *)c->d_sub;
+    cc_txn *s_txns = (cc_txn *)(s_ops + n_ops);
+    if (staged && staged <= PIN_BYTES) {
+      if (n_ops) std::memcpy(c->h_pin, ops, n_ops * sizeof(cc_op));
+      if (n_txns) std::memcpy(c->h_pin + n_ops * sizeof(cc_op), txns, n_txns * sizeof(cc_txn));
+      e = hipMemcpyAsync(c->d_sub, c->h_pin, staged, hipMemcpyHostToDevice, c->stream);
+    } else {
+      if (n_ops) e = hipMemcpyAsync(s_ops, ops, n_ops * sizeof(cc_op), hipMemcpyHostToDevice, c->stream);
+      if (e == hipSuccess && n_txns)
+        e = hipMemcpyAsync(s_txns, txns, n_txns * sizeof(cc_txn), hipMemcpyHostToDevice, c->stream);
+    }
+    ops = s_ops;
+    txns = s_txns;
   }
+  if (e == hipSuccess && maybe_keyed && n_ops)
+    e = hipMemcpyAsync(b.d_opkeys, op_keys, n_ops * sizeof(int64_t),
+                       on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream);
+  IngestArgs ia = ingest_args(c, txns, n_txns, ops, n_ops);
+  ia.op_keys = maybe_keyed ? b.d_opkeys : nullptr;
+  while (((n_rows - 1) >> ia.row_shift) >= (uint64_t)PLAN_BINS) ++ia.row_shift;
+  ia.dops = b.d_ops;
+  ia.dtx = b.d_txns;
+  ia.meta = maybe_keyed ? b.d_meta : nullptr;
+  ia.rows0 = maybe_keyed ? b.d_rows : nullptr;
+  ia.out = c->d_ingest;
+  ia.cnt = c->d_cnt;
+  ia.keys = (uint64_t *)(c->d_sub + staged);
+  ia.cand = ia.keys + n_ops;
+  ia.rows = (uint32_t *)(ia.cand + plan_cand_max(n_ops));
+  ia.owner = ia.rows + n_ops;
+  ia.hist = (uint32_t *)(c->d_ingest + INGEST_N);
+  uint64_t res[INGEST_N] = {};
+  if (e == hipSuccess) e = launch_ingest(c->stream, ia, c->n_cu);
+  if (e == hipSuccess && n_ops) e = hipMemsetAsync(b.d_reads, 0, n_ops * sizeof(int64_t), c->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(c->h_pin, c->d_ingest, sizeof res, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) std::memcpy(res, c->h_pin, sizeof res);
+  auto drop = [&]() {
+    free_batch(c, b);
+    trim_sub(c);
+  };
+  if (e != hipSuccess) {
+    (void)hipStreamSynchronize(c->stream);
+    drop();
+    // the counts may be anything now
+    (void)hipFree(c->d_cnt);
+    c->d_cnt = nullptr;
+    return hip_fail(c, e, "batch submission");
+  }
+  if (res[INGEST_ERR] != ~0ull) {
+    drop();
+    HIP_OR(c, hipMemsetAsync(c->d_cnt, 0, n_rows * sizeof(uint32_t), c->stream));
+    const uint64_t w = res[INGEST_ERR];
+    const cc_status code = -(cc_status)(w & 15u);
+    std::string msg = ingest_message((uint32_t)((w >> 4) & 0xFFFu));
+    if (on_device) msg += " (transaction " + std::to_string(w >> 16) + ")";
+    return fail(c, code, msg);
+  }
+  if (ordered_scheme && res[INGEST_UNORDERED]) {
+    drop();
+    return fail(c, CC_E_INVAL,
+                "CC_GACCO and CC_GPUTX need each transaction's ops after the previous transaction's (first_op "
+                "nondecreasing)");
+  }
+  b.max_ops = (uint32_t)res[INGEST_MAX_OPS];
+  b.has_slot = (res[INGEST_KINDS] & 1) != 0;
+  b.has_cond = (res[INGEST_KINDS] & 2) != 0;
+  b.keyed = res[INGEST_KEYED] != 0;
+  if (!b.keyed) {
+    b.d_opkeys = nullptr;
+    b.d_meta = nullptr;
+    b.d_rows = nullptr;
+    // (keyed ops learn their rows only when the index is searched, at the run)
+    plan_hot_rows(res, c->tables, b);
+  }
+  e = alloc_breaks(b);
+  if (e == hipSuccess && engine_by_default(b)) e = split_batch(c, b);
+  if (e != hipSuccess) {
+    drop();
+    return hip_fail(c, e, "batch allocation");
+  }
+  trim_sub(c);
   const uint64_t id = c->next_batch++;
   c->batches[id] = b;
   *batch_id = id;
@@ -1347,9 +1297,12 @@ cc_status cc_engine_plan(cc_ctx *c, uint64_t batch_id, uint32_t *rows, uint32_t 
   const Batch &b = it->second;
   static_assert(CC_ENGINE_MAX_ROWS == ENG_MAX, "engine rows");
   for (uint32_t i = 0; i < (uint32_t)ENG_MAX; ++i) rows[i] = i < b.eng.n_rows ? b.eng.row[i] : 0u;
-  *n_rows = b.n_eng_txns ? b.eng.n_rows : 0;
+  if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
+  const hipError_t e = split_batch(c, it->second);
+  if (e != hipSuccess) return hip_fail(c, e, "engine plan");
+  *n_rows = b.eng.n_rows;
   *n_txns = b.n_eng_txns;
-  *by_default = b.n_eng_txns && b.eng_gain ? 1 : 0;
+  *by_default = b.eng.n_rows && b.eng_gain ? 1 : 0;
   return CC_OK;
 }
 
@@ -1626,11 +1579,12 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     // and 0.99 gain 1.7-1.8x; Zipf 0.6 (0.5% of the transactions write the
     // hottest row) and order-entry (8 warehouses: 6%; 1 warehouse: transactions
     // of up to 66 ops) lose 7-56%.
-    const bool eng_default = hot_share >= 0.1 && b.max_ops <= 32 && b.eng_gain;
-    const bool use_eng = b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !latch && eng_fits && b.n_eng_txns &&
-                         b.d_part && b.d_eng_desc &&
-                         ((p.flags & CC_RUN_HOT_ENGINE) || (!(p.flags & CC_RUN_NO_HOT_ENGINE) && eng_default));
+    const bool use_eng =
+        b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !latch && eng_fits && b.eng.n_rows &&
+        ((p.flags & CC_RUN_HOT_ENGINE) || (!(p.flags & CC_RUN_NO_HOT_ENGINE) && engine_by_default(b)));
     if (use_eng) {
+      const hipError_t es = split_batch(c, b);
+      if (es != hipSuccess) return hip_fail(c, es, "engine plan");
       EngineArgs e = b.eng;
       e.desc = b.d_eng_desc;
       e.n_txns = b.n_eng_txns;
@@ -1763,25 +1717,13 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   b.d_list = (uint32_t *)(sc + STATIC_OFF_LIST);
   b.d_out = (DevOutcome *)per_txn;
   b.d_reads = per_op_read;
-  IngestArgs ia{};
-  ia.txns = txns;
-  ia.ops = ops;
-  ia.op_keys = nullptr;
-  ia.n_txns = n_txns;
-  ia.n_ops = n_ops;
-  ia.n_tables = (uint32_t)c->tables.size();
-  for (uint32_t t = 0; t < ia.n_tables; ++t) {
-    const Table &tb = c->tables[t];
-    ia.tab[t] = IngestTable{tb.n_rows, tb.row_base, tb.elem_base, tb.n_fields, 0u};
-  }
+  IngestArgs ia = ingest_args(c, txns, n_txns, ops, n_ops);
   ia.dops = b.d_ops;
   ia.dtx = b.d_txns;
   ia.owner = (uint32_t *)(sc + STATIC_OFF_OWNER);
-  ia.meta = nullptr;
-  ia.rows0 = nullptr;
   ia.out = (uint64_t *)(sc + STATIC_OFF_INGEST);
   uint64_t res[INGEST_N] = {};
-  hipError_t e = launch_ingest(c->stream, ia);
+  hipError_t e = launch_ingest(c->stream, ia, c->n_cu);
   if (e == hipSuccess) e = launch_fill_zero(c->stream, per_op_read, n_ops);
   if (e == hipSuccess) e = hipMemcpyAsync(res, ia.out, sizeof res, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -1847,7 +1789,7 @@ cc_status cc_release_batch(cc_ctx *c, uint64_t batch_id) {
   if (it == c->batches.end()) return fail(c, CC_E_NOBATCH, "unknown batch");
   activate(c);
   (void)hipStreamSynchronize(c->stream);
-  free_batch(it->second);
+  free_batch(c, it->second);
   c->batches.erase(it);
   return CC_OK;
 }

@@ -290,9 +290,38 @@ struct IngestTable {
   uint32_t indexed;    // keyed batches: the table has an index (its ops name rows by key)
 };
 // reduced results in IngestArgs::out
-// INGEST_KINDS: bit 0 a WRITE_SLOT, bit 1 a COND_ADD
-enum IngestOut { INGEST_ERR = 0, INGEST_MAX_OPS = 1, INGEST_KINDS = 2, INGEST_UNORDERED = 3, INGEST_KEYED = 4,
-                 INGEST_N = 5 };
+constexpr int PLAN_CAND = 48;         // candidates for hot rows and engine rows: more than both take
+constexpr int PLAN_COUNTS = 2048;     // bins of the histogram of row counts
+constexpr int PLAN_BINS = 4096;       // bins of the histogram of rows
+constexpr int PLAN_SORT = 2048;       // candidates sorted in LDS
+constexpr int INGEST_LOCAL = 2048;    // ops that one workgroup takes in
+// Rows gathered for the sort: those above the cut (fewer than PLAN_CAND), and
+// at the cut at most PLAN_SORT / 2 rows, or one bin of rows more than the
+// PLAN_CAND needed (2^16 rows), or all that are written PLAN_COUNTS - 1 times
+// and more.
+constexpr uint64_t plan_cand_max(uint64_t n_ops) {
+  const uint64_t m = 2 * PLAN_CAND + PLAN_SORT + (1u << 16) + n_ops / (PLAN_COUNTS - 1);
+  return m < n_ops ? m : n_ops;
+}
+enum IngestOut {
+  INGEST_ERR = 0,
+  INGEST_MAX_OPS,
+  INGEST_KINDS,      // bit 0 a WRITE_SLOT, bit 1 a COND_ADD
+  INGEST_UNORDERED,
+  INGEST_KEYED,
+  INGEST_LOOSE,      // the transactions' ops do not simply follow one another
+  INGEST_DONE1,      // workgroups done with a part
+  INGEST_DONE2,
+  INGEST_DONE3,
+  INGEST_CUT,        // lowest count of a candidate, and the rows above it
+  INGEST_ABOVE,
+  INGEST_TIES,
+  INGEST_ROW_CUT,
+  INGEST_N_CAND,
+  INGEST_TOP,        // writes to the most written row
+  INGEST_CAND,       // PLAN_CAND x (count << 32 | ~row), most written first, 0: none
+  INGEST_N = INGEST_CAND + PLAN_CAND
+};
 // what failed (bits 4-15 of the error word); the host turns it into a message
 enum IngestMsg {
   INGEST_MSG_RESERVED = 1,
@@ -314,16 +343,32 @@ struct IngestArgs {
   uint64_t n_txns, n_ops;
   IngestTable tab[CC_MAX_TABLES];
   uint32_t n_tables;
-  uint32_t pad;
+  uint32_t row_shift;     // rows per bin of the histogram of rows: 1 << row_shift, PLAN_BINS bins cover every row
   DevOp *dops;            // packed descriptors (the batch's own buffers)
   DevTxn *dtx;
   uint32_t *owner;        // n_ops scratch words: lowest transaction naming each op
   uint32_t *meta;         // keyed batches: per-op keyed flag, table, field (else nullptr)
   uint32_t *rows0;        // keyed batches: per-op row as submitted
   uint64_t *out;          // INGEST_N words
+  // rows the batch writes most (cnt nullptr: not looked for)
+  uint32_t *cnt;          // per global row; 0 before and, if the batch is well formed, after
+                          // (ops named by two transactions may leave counts behind)
+  uint32_t *rows;         // n_ops scratch words
+  uint64_t *keys;         // n_ops scratch words
+  uint64_t *cand;         // plan_cand_max(n_ops) scratch words
+  uint32_t *hist;         // PLAN_COUNTS + PLAN_BINS scratch words
 };
 // Resets out, then validates and packs; the host reads `out` afterwards.
-hipError_t launch_ingest(hipStream_t s, const IngestArgs &a);
+hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu);
+
+// The transactions that write one of the engine rows, in batch order: part
+// (n_txns entries) lists them and then the others, desc describes them; their
+// number is scratch[n_txns] afterwards.  scratch: split_scratch_words(n_txns).
+constexpr uint64_t split_scratch_words(uint64_t n_txns) { return 2 * n_txns + 1 + (n_txns + 1) / 4096 + 2; }
+hipError_t launch_split(hipStream_t s, const DevOp *ops, const DevTxn *txns, uint64_t n_txns, const EngineArgs &e,
+                        uint32_t *scratch, uint32_t *part, EngineDesc *desc);
+// Exclusive scan of m 32-bit values in place (partial: (m + 4095) / 4096 + 1 words).
+void exclusive_scan_u32(hipStream_t s, uint32_t *data, uint64_t m, uint32_t *partial);
 
 // Host-side launchers (kernels.hip).
 hipError_t launch_init(hipStream_t s, uint64_t *words, uint64_t n_words, uint64_t *aux, uint64_t n_aux,
@@ -366,9 +411,9 @@ constexpr uint64_t STATIC_OFF_TXNS = STATIC_OFF_OPS + (uint64_t)CC_STATIC_MAX_OP
 constexpr uint64_t STATIC_OFF_LIST = STATIC_OFF_TXNS + (uint64_t)CC_STATIC_MAX_TXNS * sizeof(DevTxn);
 constexpr uint64_t STATIC_OFF_OWNER = STATIC_OFF_LIST + (uint64_t)CC_STATIC_MAX_TXNS * sizeof(uint32_t);
 constexpr uint64_t STATIC_OFF_INGEST = STATIC_OFF_OWNER + (uint64_t)CC_STATIC_MAX_OPS * sizeof(uint32_t);
-constexpr uint64_t STATIC_SCRATCH_BYTES = STATIC_OFF_INGEST + 256;
+constexpr uint64_t STATIC_SCRATCH_BYTES = STATIC_OFF_INGEST + 512;
 static_assert(STATIC_OFF_TXNS % 256 == 0 && STATIC_OFF_LIST % 256 == 0 && STATIC_OFF_OWNER % 256 == 0 &&
-                  STATIC_OFF_INGEST % 256 == 0 && INGEST_N * sizeof(uint64_t) <= 256,
+                  STATIC_OFF_INGEST % 256 == 0 && INGEST_N * sizeof(uint64_t) <= 512,
               "static scratch regions are 256-byte aligned");
 // Device address of `device`'s array; `device` must be current.  Resolved
 // with hipGetSymbolAddress on a device's first call, then kept.

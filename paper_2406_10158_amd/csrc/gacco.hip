@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(256) gacco_shared_clear_kernel(const uint32_t 
 }
 
 // Exclusive scan of m 32-bit values in place (partial: (m + 4095) / 4096 + 1 words).
-static void exclusive_scan_u32(hipStream_t s, uint32_t *data, uint64_t m, uint32_t *partial) {
+void exclusive_scan_u32(hipStream_t s, uint32_t *data, uint64_t m, uint32_t *partial) {
   const uint64_t chunks = (m + SCAN_CHUNK - 1) / SCAN_CHUNK;
   hipLaunchKernelGGL(scan_sum_kernel, dim3((unsigned)chunks), dim3(RS_THREADS), 0, s, data, m, partial);
   hipLaunchKernelGGL(scan_partials_kernel, dim3(1), dim3(RS_THREADS), 0, s, partial, (uint32_t)chunks);
