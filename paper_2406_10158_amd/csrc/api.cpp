@@ -45,7 +45,7 @@ struct Batch {
   uint32_t *d_tscratch = nullptr;// GPUTx: per-transaction ranks
   uint64_t *d_chain = nullptr;   // GaccO, GPUTx: the chain scan's tile states, 3 words per tile
   uint64_t *d_breaks = nullptr;  //   with conditional adds or slot writes: results, ready words, transactions' first ops
-  int64_t *d_arrival = nullptr;           // serving: arrival ticks per transaction
+  int64_t *d_arrival = nullptr;           // serving: arrival ticks per transaction, then nanoseconds
   std::vector<int64_t> arrival_ns;        // host copy, for latency statistics
   hipGraphExec_t epoch_graph = nullptr;  // captured epochs for the last epoch-mode parameters
   uint64_t epoch_key[4] = {0, 0, 0, 0};
@@ -104,6 +104,7 @@ struct cc_ctx {
   uint32_t *d_cnt = nullptr;          //   a count per global row, 0 between submissions
   unsigned char *d_sub = nullptr;     //   scratch, grown to the largest batch's need
   size_t sub_bytes = 0;
+  LatState *d_lat = nullptr;          // latency percentiles: state, then histograms
   unsigned char *h_pin = nullptr;     // PIN_BYTES of pinned host memory: small arrays on their way to or from the device
   std::vector<std::pair<void *, size_t>> pool;  // released batches' arenas (see release_arena)
   unsigned char *d_static = nullptr;  // cc_run_static: this device's static scratch (never freed)
@@ -212,23 +213,55 @@ void free_batch(cc_ctx *c, Batch &b) {
   b = Batch{};
 }
 
-// Percentile of committed commit times (host side, after a run).
-void latency_percentiles(std::vector<cc_outcome> &o, uint64_t *p50, uint64_t *p99) {
+// Queues the copy of the control block and, if wanted, the latency percentiles
+// and their copy; both arrive in pinned memory (RunTail) with the next
+// synchronisation.
+struct RunTail {
+  Ctl ctl;
+  LatState lat;
+};
+static_assert(sizeof(RunTail) <= PIN_BYTES, "a run's tail fits the pinned memory");
+
+hipError_t queue_tail(cc_ctx *c, const Batch &b, const int64_t *arrival_ns, bool latency) {
+  RunTail *t = (RunTail *)c->h_pin;
+  hipError_t e = hipSuccess;
+  if (latency) {
+    LatArgs a{};
+    a.out = b.d_out;
+    a.n = b.n_txns;
+    a.arrival_ns = arrival_ns;
+    a.st = c->d_lat;
+    a.hist = (uint32_t *)(c->d_lat + 1);
+    a.ksets = b.scheme == CC_GPUTX ? 1u : 0u;
+    e = launch_latency(c->stream, a, c->n_cu);
+    if (e == hipSuccess) e = hipMemcpyAsync(&t->lat, c->d_lat, sizeof(LatState), hipMemcpyDeviceToHost, c->stream);
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(&t->ctl, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c->stream);
+  return e;
+}
+
+// The latency statistics that came with a tail.  Latencies further apart than
+// the levels resolve (68 s) are selected from the records here.
+cc_status take_latency(cc_ctx *c, Batch &b, bool serve) {
+  const LatState &l = ((RunTail *)c->h_pin)->lat;
+  b.stats[CC_STAT_LAT_P50_NS] = l.value[0];
+  b.stats[CC_STAT_LAT_P99_NS] = l.value[1];
+  if (b.scheme == CC_GPUTX) b.stats[CC_STAT_KSETS] = l.ksets;
+  if (l.shift == 0) return CC_OK;
+  std::vector<cc_outcome> o(b.n_txns);
+  HIP_OR(c, hipMemcpy(o.data(), b.d_out, b.n_txns * sizeof(cc_outcome), hipMemcpyDeviceToHost));
   std::vector<int64_t> lat;
   lat.reserve(o.size());
-  for (auto &x : o)
-    if (x.status == CC_COMMITTED) lat.push_back(x.commit_ns);
-  if (lat.empty()) {
-    *p50 = *p99 = 0;
-    return;
-  }
+  for (uint64_t t = 0; t < b.n_txns; ++t)
+    if (o[t].status == CC_COMMITTED) lat.push_back(o[t].commit_ns - (serve ? b.arrival_ns[t] : 0));
   auto pick = [&](double q) {
-    size_t i = (size_t)(q * (double)(lat.size() - 1) + 0.5);
+    const size_t i = (size_t)(q * (double)(lat.size() - 1) + 0.5);
     std::nth_element(lat.begin(), lat.begin() + i, lat.end());
     return (uint64_t)lat[i];
   };
-  *p50 = pick(0.50);
-  *p99 = pick(0.99);
+  b.stats[CC_STAT_LAT_P50_NS] = pick(0.50);
+  b.stats[CC_STAT_LAT_P99_NS] = pick(0.99);
+  return CC_OK;
 }
 
 }  // namespace
@@ -306,8 +339,10 @@ cc_status cc_init(cc_ctx **out, const cc_config *cfg) {
   }
   c->wallclock_khz = (uint32_t)khz;
   if (hipMalloc(&c->d_ctl, sizeof(Ctl)) != hipSuccess ||
+      hipMalloc(&c->d_lat, sizeof(LatState) + LAT_LEVELS * 2 * LAT_BINS * sizeof(uint32_t)) != hipSuccess ||
       hipHostMalloc((void **)&c->h_pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
     if (c->d_ctl) (void)hipFree(c->d_ctl);
+    if (c->d_lat) (void)hipFree(c->d_lat);
     delete c;
     g_init_err = "allocation of the control block failed";
     return CC_E_NOMEM;
@@ -349,6 +384,7 @@ cc_status cc_destroy(cc_ctx *c) {
   if (c->d_ingest) (void)hipFree(c->d_ingest);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
   if (c->d_sub) (void)hipFree(c->d_sub);
+  if (c->d_lat) (void)hipFree(c->d_lat);
   if (c->h_pin) (void)hipHostFree(c->h_pin);
   if (c->d_data) (void)hipFree(c->d_data);
   if (c->d_words) (void)hipFree(c->d_words);
@@ -582,8 +618,9 @@ ChainArgs chain_args(const cc_ctx *c, const Batch &b, const cc_run_params &p) {
 
 // What an ordered run reports, from the control block and the events of its parts.
 cc_status ordered_stats(cc_ctx *c, Batch &b, bool chain, int grid_used, float ms_index, Ctl *h) {
+  HIP_OR(c, queue_tail(c, b, nullptr, b.n_txns != 0));
   HIP_OR(c, hipStreamSynchronize(c->stream));
-  HIP_OR(c, hipMemcpy(h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+  *h = ((RunTail *)c->h_pin)->ctl;
   float ms_run = 0, ms_prep = 0, ms_kernel = 0;
   HIP_OR(c, hipEventElapsedTime(&ms_run, c->ev[0], c->ev[3]));
   HIP_OR(c, hipEventElapsedTime(&ms_prep, c->ev[4], c->ev[5]));
@@ -603,18 +640,7 @@ cc_status ordered_stats(cc_ctx *c, Batch &b, bool chain, int grid_used, float ms
       chain ? b.stats[CC_STAT_KERNEL_NS] : (uint64_t)((double)h->stats[DS_T_USEFUL] * ns_per_tick);
   b.stats[CC_STAT_T_WAIT_NS] = (uint64_t)((double)h->stats[DS_T_WAIT] * ns_per_tick);
   b.ran = true;
-  if (b.n_txns) {
-    std::vector<cc_outcome> o(b.n_txns);
-    HIP_OR(c, hipMemcpy(o.data(), b.d_out, b.n_txns * sizeof(cc_outcome), hipMemcpyDeviceToHost));
-    if (b.scheme == CC_GPUTX) {
-      uint64_t ksets = 0;
-      for (auto &x : o)
-        if (x.status == CC_COMMITTED) ksets = std::max<uint64_t>(ksets, x.serial_hi + 1);
-      b.stats[CC_STAT_KSETS] = ksets;
-    }
-    latency_percentiles(o, &b.stats[CC_STAT_LAT_P50_NS], &b.stats[CC_STAT_LAT_P99_NS]);
-  }
-  return CC_OK;
+  return b.n_txns ? take_latency(c, b, false) : CC_OK;
 }
 
 // GaccO run: CC initialisation, preprocessing, execution.  Every transaction
@@ -635,7 +661,7 @@ cc_status run_gacco(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   HIP_OR(c, hipEventRecord(c->ev[0], c->stream));
   // no word is cleared: the chain scan uses none, the lock table sets those of every accessed row
   HIP_OR(c, launch_init(c->stream, c->d_words, 0, nullptr, 0, b.d_out, chain && !b.keyed ? 0 : b.n_txns, c->d_ctl,
-                        p.ts_start));
+                        c->d_lat, p.ts_start));
   float ms_index = 0;
   if (b.keyed) {
     cc_status st = resolve_keys(c, b, p, &ms_index);
@@ -719,7 +745,7 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   const bool strict = (p.flags & CC_RUN_STRICT_FENCES) != 0;
 
   HIP_OR(c, hipEventRecord(c->ev[0], c->stream));
-  HIP_OR(c, launch_init(c->stream, c->d_words, 0, nullptr, 0, b.d_out, b.keyed ? n : 0, c->d_ctl, 0));
+  HIP_OR(c, launch_init(c->stream, c->d_words, 0, nullptr, 0, b.d_out, b.keyed ? n : 0, c->d_ctl, c->d_lat, 0));
   float ms_index = 0;
   if (b.keyed) {
     cc_status st = resolve_keys(c, b, p, &ms_index);
@@ -1438,13 +1464,19 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
 
   HIP_OR(c, hipEventRecord(c->ev[0], c->stream));
   HIP_OR(c, launch_init(c->stream, c->d_words, c->total_rows, c->d_aux, b.scheme == CC_MVCC ? c->total_rows : 0,
-                        b.d_out, b.n_txns, c->d_ctl, p.ts_start));
+                        b.d_out, b.n_txns, c->d_ctl, c->d_lat, p.ts_start));
   float ms_index = 0;
   if (b.keyed) {
     cc_status st = resolve_keys(c, b, p, &ms_index);
     if (st) return st;
   }
   Ctl h{};
+  const RunTail *tail = (const RunTail *)c->h_pin;
+  // the latencies of a small batch are looked at behind every pass, which costs
+  // less than a synchronisation of its own behind the last
+  const bool lat_early = host_stats && b.n_txns && b.n_txns <= (uint64_t)LAT_SMALL;
+  const int64_t *lat_arrival = p.mode == CC_MODE_SERVE && b.d_arrival ? b.d_arrival + b.n_txns : nullptr;
+  bool have_tail = false, have_latency = false;  // the last tail is the run's, and so are its latencies
   double kernel_ms = 0, engine_ms = 0;
   uint64_t engine_txns = 0;
   uint32_t passes = 0, epochs = 0;
@@ -1461,8 +1493,9 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     for (;;) {
       if (!all) {
         HIP_OR(c, launch_compact(c->stream, b.d_out, b.n_txns, a.max_attempts, b.d_list, c->d_ctl));
-        HIP_OR(c, hipMemcpyAsync(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost, c->stream));
+        HIP_OR(c, queue_tail(c, b, nullptr, false));
         HIP_OR(c, hipStreamSynchronize(c->stream));
+        h = tail->ctl;
         a.list = b.d_list;
         a.n_txns = h.pending_n;
         a.pass = 1;  // attempt counts continue from the outcome records
@@ -1478,6 +1511,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
                                 c->n_cu, &grid_used);
       if (e != hipSuccess) return launch_error(c, e);
       HIP_OR(c, hipEventRecord(c->ev[2], c->stream));
+      HIP_OR(c, queue_tail(c, b, lat_arrival, lat_early));
       HIP_OR(c, hipStreamSynchronize(c->stream));
       float ms = 0;
       HIP_OR(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]));
@@ -1485,7 +1519,9 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       if (first_grid == 0) first_grid = grid_used;
       ++passes;
       all = false;
-      HIP_OR(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+      h = tail->ctl;
+      have_tail = true;
+      have_latency = lat_early;
       // a stuck latch stopped the run (reported below)
       if (h.stats[DS_COMMITTED] + h.stats[DS_GAVE_UP] >= b.n_txns || last || h.stop) return CC_OK;
       grid = std::max(1, grid_used / 8);
@@ -1546,12 +1582,14 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       HIP_OR(c, hipEventRecord(c->ev[1], c->stream));
       HIP_OR(c, hipGraphLaunch(b.epoch_graph, c->stream));
       HIP_OR(c, hipEventRecord(c->ev[2], c->stream));
+      HIP_OR(c, queue_tail(c, b, nullptr, false));
       HIP_OR(c, hipStreamSynchronize(c->stream));
       float ms = 0;
       HIP_OR(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]));
       kernel_ms += ms;
       epochs += EPOCHS_PER_GRAPH;
-      HIP_OR(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+      h = tail->ctl;
+      have_tail = true;
       const uint64_t done = h.stats[DS_COMMITTED] + h.stats[DS_GAVE_UP];
       if (done >= b.n_txns || h.stop) break;
       if (epochs >= max_epochs) {
@@ -1611,11 +1649,16 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       if (st) return st;
     }
   }
-  HIP_OR(c, hipEventRecord(c->ev[3], c->stream));
-  HIP_OR(c, hipStreamSynchronize(c->stream));
-  HIP_OR(c, hipMemcpy(&h, c->d_ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
+  // the run ends with its last kernel (ev[2]); nothing to run ends with its initialisation
+  const bool want_latency = host_stats && b.n_txns && !have_latency;
+  if (!passes && !epochs) HIP_OR(c, hipEventRecord(c->ev[2], c->stream));
+  if (!have_tail || want_latency) {
+    HIP_OR(c, queue_tail(c, b, lat_arrival, want_latency));
+    HIP_OR(c, hipStreamSynchronize(c->stream));
+    h = tail->ctl;
+  }
   float ms_run = 0;
-  HIP_OR(c, hipEventElapsedTime(&ms_run, c->ev[0], c->ev[3]));
+  HIP_OR(c, hipEventElapsedTime(&ms_run, c->ev[0], c->ev[2]));
   std::memset(b.stats, 0, sizeof(b.stats));
   b.stats[CC_STAT_COMMITTED] = h.stats[DS_COMMITTED];
   b.stats[CC_STAT_ATTEMPTS] = h.stats[DS_ATTEMPTS];
@@ -1652,11 +1695,8 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   b.stats[CC_STAT_INDEX_NS] = (uint64_t)((double)ms_index * 1e6);
   b.ran = true;
   if (b.n_txns && host_stats) {
-    std::vector<cc_outcome> o(b.n_txns);
-    HIP_OR(c, hipMemcpy(o.data(), b.d_out, b.n_txns * sizeof(cc_outcome), hipMemcpyDeviceToHost));
-    if (p.mode == CC_MODE_SERVE)
-      for (uint64_t t = 0; t < b.n_txns; ++t) o[t].commit_ns -= b.arrival_ns[t];
-    latency_percentiles(o, &b.stats[CC_STAT_LAT_P50_NS], &b.stats[CC_STAT_LAT_P99_NS]);
+    const cc_status st = take_latency(c, b, p.mode == CC_MODE_SERVE);
+    if (st) return st;
   }
   if (h.stats[DS_LATCH_STUCK] || h.stop)
     return fail(c, CC_E_LIVELOCK, "a row latch was not obtained within the spin limit; table contents are undefined");
@@ -1761,15 +1801,16 @@ cc_status cc_set_arrivals(cc_ctx *c, uint64_t batch_id, const int64_t *arrival_n
   if (it == c->batches.end()) return fail(c, CC_E_NOBATCH, "unknown batch");
   Batch &b = it->second;
   if (n != b.n_txns) return fail(c, CC_E_INVAL, "one arrival time per transaction");
-  std::vector<int64_t> ticks(std::max<uint64_t>(n, 1), 0);
+  std::vector<int64_t> ticks(std::max<uint64_t>(2 * n, 1), 0);
   for (uint64_t t = 0; t < n; ++t) {
     if (arrival_ns[t] < 0 || (t && arrival_ns[t] < arrival_ns[t - 1]))
       return fail(c, CC_E_INVAL, "arrival times must be non-negative and non-decreasing");
     ticks[t] = (int64_t)((double)arrival_ns[t] * (double)c->wallclock_khz / 1e6);
+    ticks[n + t] = arrival_ns[t];
   }
   if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
   if (!b.d_arrival) HIP_OR(c, hipMalloc(&b.d_arrival, ticks.size() * sizeof(int64_t)));
-  HIP_OR(c, hipMemcpyAsync(b.d_arrival, ticks.data(), n * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
+  HIP_OR(c, hipMemcpyAsync(b.d_arrival, ticks.data(), 2 * n * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
   HIP_OR(c, hipStreamSynchronize(c->stream));
   b.arrival_ns.assign(arrival_ns, arrival_ns + n);
   return CC_OK;

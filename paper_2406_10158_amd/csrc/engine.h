@@ -370,9 +370,31 @@ hipError_t launch_split(hipStream_t s, const DevOp *ops, const DevTxn *txns, uin
 // Exclusive scan of m 32-bit values in place (partial: (m + 4095) / 4096 + 1 words).
 void exclusive_scan_u32(hipStream_t s, uint32_t *data, uint64_t m, uint32_t *partial);
 
-// Host-side launchers (kernels.hip).
+// Latency percentiles of a run (latency.hip).
+constexpr uint64_t LAT_BITS = 12;  // of the latencies' range, a level
+constexpr int LAT_BINS = 1 << LAT_BITS;
+constexpr int LAT_LEVELS = 3;      // up to 2^36 ns of range
+constexpr int LAT_SMALL = 8192;    // transactions that one workgroup looks at
+struct LatState {                  // zeroed by the init kernel
+  uint64_t n, not_min, max, ksets;
+  uint64_t done[1 + LAT_LEVELS];
+  uint64_t shift;                  // 0: value[] is exact; else they need more levels than LAT_LEVELS
+  uint64_t prefix[2], rank[2], value[2];
+};
+struct LatArgs {
+  const DevOutcome *out;
+  uint64_t n;
+  const int64_t *arrival_ns;       // served batches: latencies count from here (else nullptr)
+  LatState *st;
+  uint32_t *hist;                  // LAT_LEVELS x 2 x LAT_BINS words
+  uint32_t ksets;                  // also find the largest serial_hi + 1
+  uint32_t pad;
+};
+hipError_t launch_latency(hipStream_t s, const LatArgs &a, int n_cu);
+
+// Host-side launchers (kernels.hip).  lat: the latency state to zero.
 hipError_t launch_init(hipStream_t s, uint64_t *words, uint64_t n_words, uint64_t *aux, uint64_t n_aux,
-                       DevOutcome *out, uint64_t n_out, Ctl *ctl, uint64_t ticket_start);
+                       DevOutcome *out, uint64_t n_out, Ctl *ctl, LatState *lat, uint64_t ticket_start);
 
 // Between passes: list the transactions neither committed nor given up, and
 // reset the claim counter.  ctl->pending_n receives the count.

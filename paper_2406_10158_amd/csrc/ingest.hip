@@ -38,7 +38,7 @@
 // transactions (540k ops) from the host.  Now 0.55 ms for the whole submission
 // of 2^18 x 16 device-resident ops (pack 0.32, counts 0.14, pick 0.07) and
 // 0.45 ms for the uneven host batch; 30 us of kernel for 256 transactions x 4.
-#include "device.h"
+#include "select.h"
 
 namespace cce {
 
@@ -186,6 +186,12 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
       s.cnt[i] = 0;
     }
   __syncthreads();
+  // tables whose ops name their rows by key (bit t: table t)
+  uint32_t indexed = 0;
+  if (a.op_keys)
+    for (uint32_t t = 0; t < a.n_tables; ++t) indexed |= a.tab[t].indexed ? 1u << t : 0u;
+  static_assert(CC_MAX_TABLES <= 32, "a bit per table");
+  auto is_keyed = [&](const cc_op &o) { return o.table < 32u && ((indexed >> o.table) & 1u); };
   uint32_t max_ops = 0, kinds = 0;
   bool unordered = false, any_keyed = false;
   OpBits &bits = s.bits[team];
@@ -216,14 +222,16 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     }
     const uint32_t chunks = (longest + IG_L - 1) / IG_L;
     // an op and its row's identity: its key on an indexed table (keyed batch), else its row
+    // (a select between the two: a key loaded under the lane's own condition was
+    // miscompiled, the row's register reused for the condition)
     auto load = [&](uint32_t i, cc_op *o, int64_t *id) {
       *o = cc_op{0, 0, 0, 0, 0};
-      *id = 0;
+      int64_t key = 0;
       if (i < n) {
         *o = a.ops[f0 + i];
-        const bool kd = a.op_keys != nullptr && o->table < a.n_tables && s.tab[o->table].indexed;
-        *id = kd ? a.op_keys[f0 + i] : (int64_t)o->row;
+        if (indexed) key = a.op_keys[f0 + i];
       }
+      *id = is_keyed(*o) ? key : (int64_t)o->row;
     };
     if (tl < 4) bits.lead[tl] = bits.write[tl] = 0;
     wave_lds_order();
@@ -265,7 +273,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
           msg = INGEST_MSG_TABLE;
         } else {
           const IngestTable &tb_ = s.tab[o.table];
-          const bool kd = a.op_keys != nullptr && tb_.indexed;
+          const bool kd = is_keyed(o);
           any_keyed |= kd;
           if (kd && o.row != 0) msg = INGEST_MSG_KEYED_ROW;
           else if ((!kd && o.row >= tb_.n_rows) || o.field >= tb_.n_fields) msg = INGEST_MSG_ROW_FIELD;
@@ -334,7 +342,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
       uint32_t mark = RC_NONE;
       if (in) {
         const IngestTable &tb_ = s.tab[o.table];
-        const bool kd = a.op_keys != nullptr && tb_.indexed;
+        const bool kd = is_keyed(o);
         const bool lead = (bits.lead[i >> 6] >> (i & 63)) & 1u, wr = group_writes(bits, i);
         const uint32_t grow = kd ? 0u : (uint32_t)(tb_.row_base + o.row);
         DevOp d;
@@ -387,56 +395,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
 
 // ---- the most written rows ---------------------------------------------------
 
-__device__ __forceinline__ uint32_t ld_u32(const uint32_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint32_t count_bin(uint32_t c) { return c < (uint32_t)PLAN_COUNTS ? c : (uint32_t)PLAN_COUNTS - 1; }
-
-// True in the workgroup that is last to get here (of nb).  What the others left
-// for it they wrote with agent-scope atomics, so their completion is enough
-// (write-backs of the caches, 2,048 times, took 0.3 ms).
-__device__ __forceinline__ bool last_block(const IngestArgs &a, int word, uint32_t nb) {
-  __shared__ uint32_t mine;
-  if (nb == 1) {
-    __syncthreads();
-    return true;
-  }
-  order_point<false>();
-  __syncthreads();
-  if (threadIdx.x == 0) mine = (uint32_t)add_word(&a.out[word], 1);
-  __syncthreads();
-  return mine + 1 == nb;
-}
-
-// First bin (of `bins`, a multiple of 64 up to 64 x 64, in order or from the
-// last down) at which the running count reaches `want`, and the count before
-// it; the last one tried if it never does.  Wavefront 0 of a workgroup calls it.
-__device__ __forceinline__ void find_bin(const uint32_t *h, uint32_t bins, bool down, uint64_t want, uint32_t *bin,
-                                         uint64_t *before) {
-  const uint32_t lane = __lane_id(), per = bins / 64;
-  auto at = [&](uint32_t k) { return h + (down ? bins - 1 - k : k); };
-  auto scan = [&](uint64_t v) {  // inclusive, over the lanes
-#pragma unroll
-    for (uint32_t o = 1; o < 64; o <<= 1) {
-      const uint64_t y = (uint64_t)__shfl_up((long long)v, o, 64);
-      if (lane >= o) v += y;
-    }
-    return v;
-  };
-  uint64_t sum = 0;
-  for (uint32_t i = 0; i < per; ++i) sum += ld_u32(at(lane * per + i));
-  uint64_t inc = scan(sum);
-  uint64_t reach = ballot(inc >= want);
-  const int group = reach ? __ffsll((unsigned long long)reach) - 1 : 63;
-  const uint64_t base = (uint64_t)__shfl((long long)(inc - sum), group, 64);
-  sum = lane < per ? ld_u32(at((uint32_t)group * per + lane)) : 0;
-  inc = scan(sum);
-  reach = ballot(lane < per && base + inc >= want);
-  const int k = reach ? __ffsll((unsigned long long)reach) - 1 : (int)per - 1;
-  *before = base + (uint64_t)__shfl((long long)(inc - sum), k, 64);
-  const uint32_t found = (uint32_t)group * per + (uint32_t)k;
-  *bin = down ? bins - 1 - found : found;
-}
 
 // A marked row's candidate key, larger for more writes, then for the lower
 // row; 0: not marked.
@@ -481,7 +440,7 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
     if (lds[i]) atomicAdd(&a.hist[i], lds[i]);
   top = (uint32_t)wave_max(top);
   if (__lane_id() == 0 && top) atomicMax((unsigned long long *)&a.out[INGEST_TOP], (unsigned long long)top);
-  if (!last_block(a, INGEST_DONE1, nb)) return;
+  if (!last_block(&a.out[INGEST_DONE1], nb)) return;
   if (tid < 64) {
     uint32_t cut = 0;
     uint64_t above = 0;
@@ -512,7 +471,7 @@ __device__ __forceinline__ void part_ties(const IngestArgs &a, uint32_t *lds, ui
   uint32_t *h = a.hist + PLAN_COUNTS;
   for (uint32_t i = tid; i < (uint32_t)PLAN_BINS; i += NT)
     if (lds[i]) atomicAdd(&h[i], lds[i]);
-  if (!last_block(a, INGEST_DONE2, nb)) return;
+  if (!last_block(&a.out[INGEST_DONE2], nb)) return;
   if (tid < 64) {
     uint32_t bin = 0;
     uint64_t before = 0;
@@ -578,7 +537,7 @@ __device__ __forceinline__ void part_pick(const IngestArgs &a, uint64_t *lds, ui
       if (p && at < plan_cand_max(a.n_ops)) st_word(a.cand + at, key);
     }
   }
-  if (!last_block(a, INGEST_DONE3, nb)) return;
+  if (!last_block(&a.out[INGEST_DONE3], nb)) return;
   const uint64_t n = ld_word(&a.out[INGEST_N_CAND]);
   if (n <= (uint64_t)PLAN_SORT) {
     for (uint32_t i = tid; i < (uint32_t)n; i += NT) lds[i] = ld_word(a.cand + i);

@@ -71,7 +71,7 @@ hipError_t launch_compact(hipStream_t s, const DevOutcome *out, uint64_t n_txns,
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) init_kernel(uint64_t *words, uint64_t n_words, uint64_t *aux,
                                                    uint64_t n_aux, DevOutcome *out, uint64_t n_out, Ctl *ctl,
-                                                   uint64_t ticket_start) {
+                                                   LatState *lat, uint64_t ticket_start) {
   const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t i = tid; i < n_words; i += stride) words[i] = 0;
@@ -93,19 +93,20 @@ __global__ void __launch_bounds__(256) init_kernel(uint64_t *words, uint64_t n_w
     ctl->budget_released = 0;
     for (int i = 0; i < DS_N; ++i) ctl->stats[i] = 0;
     ctl->stop = 0;
+    *lat = LatState{};
     ctl->start_clock = wall_clock64();
   }
 }
 
 hipError_t launch_init(hipStream_t s, uint64_t *words, uint64_t n_words, uint64_t *aux, uint64_t n_aux,
-                       DevOutcome *out, uint64_t n_out, Ctl *ctl, uint64_t ticket_start) {
+                       DevOutcome *out, uint64_t n_out, Ctl *ctl, LatState *lat, uint64_t ticket_start) {
   uint64_t n = n_words > n_aux ? n_words : n_aux;
   n = n > n_out ? n : n_out;
   uint64_t blocks = (n + 255) / 256;
   if (blocks < 1) blocks = 1;
   if (blocks > 16384) blocks = 16384;
   hipLaunchKernelGGL(init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, words, n_words, aux, n_aux, out, n_out,
-                     ctl, ticket_start);
+                     ctl, lat, ticket_start);
   return hipGetLastError();
 }
 
