@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 
 # the sources a kernel's HBM counters depend on (profiles/traffic.json keys them by their hash)
 KERNEL_SOURCES = {"txn_kernel": ("kernels.hip", "schemes.h", "txn_kernel.h", "device.h"),
-                  "engine_kernel": ("hot_engine.h", "schemes.h", "device.h")}
+                  "hot_engine": ("hot_engine.hip", "chain.hip", "gacco.hip", "engine.h", "device.h")}
 
 
 def algorithmic_bytes(batch) -> int:
@@ -128,7 +128,7 @@ def run_probes(ctx, binding, batch=None, quick=False) -> dict:
     # the hot row is touched from every XCD: the bounds take the cross-XCD hand-offs
     out["handoff_ns"] = out["handoff_cross_xcd_ns"]
     out["commit_handoff_ns"] = out["commit_handoff_cross_xcd_ns"]
-    # OCC's hot-row engine passes its rows between wavefronts of one workgroup, in LDS
+    # a row passed between two wavefronts of one workgroup, in LDS
     out["engine_handoff_ns"] = binding.cc_probe(ctx, "engine_handoff", 1 << 20, rounds) * 1e6 / rounds
     ms = binding.cc_probe(ctx, "wave_counter", 1 << 20, 1 << 26)
     out["one_word_atomic_ns"] = ms * 1e6 / (threads // 64 * (((1 << 26) + threads - 1) // threads + 3) // 4 * 4)
@@ -560,20 +560,15 @@ def main():
     final_last = eng.tables()
 
     # HBM roofline of the dominant kernel (algorithmic bytes / its time): the
-    # transaction kernel, or, when OCC's hot-row engine ran, the engine over
-    # its own share of the batch
-    eng_rows, _, _ = binding.cc_engine_plan(eng.ctx, bid) if args.scheme == "occ" else (np.zeros(0), 0, False)
+    # transaction kernel, or, when OCC's hot-row engine ran, the engine (its
+    # sort and its scan) over its own share of the batch: the first tickets
     eng_txns = np.zeros(0, np.int64)
-    if len(engine_ns) and np.mean(engine_ns) > 0:
-        w = batch.kind != workload.READ
-        txn_of_op = np.repeat(np.arange(batch.n_txns), batch.n_ops.astype(np.int64))
-        hit = np.zeros(batch.n_txns, bool)
-        hit[txn_of_op[w & (batch.table == 0) & np.isin(batch.row, eng_rows)]] = True
-        eng_txns = np.nonzero(hit)[0]
+    if args.scheme == "occ" and st["engine_txns"]:
+        eng_txns = np.nonzero(out_last["serial_lo"] < st["engine_txns"])[0]
     k_step_s = float(np.mean(kernel_ns)) * 1e-9
     if len(eng_txns):
         alg = algorithmic_bytes(batch.subset(eng_txns))
-        dom_s, launches, dom_kernel = float(np.mean(engine_ns)) * 1e-9, 1.0, "engine_kernel"
+        dom_s, launches, dom_kernel = float(np.mean(engine_ns)) * 1e-9, 1.0, "hot_engine"
     else:
         alg = algorithmic_bytes(batch)
         dom_s, launches = k_step_s, float(np.mean(passes))
@@ -623,28 +618,18 @@ def main():
     x_cont = batch.n_txns / (h * t_h * 1e-9) if h else float("inf")
     engine_bound = None
     if len(eng_txns):
-        # the engine runs before the rest of the batch: the passes' bounds add.
-        # Engine: its hottest row's writes at the engine's hand-off; rest: its
-        # own hottest row at OCC's commit hand-off, or its random accesses.
+        # the engine hands no row from commit to commit; the rest runs after
+        # it: its own hottest row at OCC's commit hand-off
         rest = batch.subset(np.setdiff1d(np.arange(batch.n_txns), eng_txns))
         _, h_rest = workload.hottest_row_writes(rest)
-        acc_r = access_counts(rest)
-        t_rest_roof = (acc_r["word_loads"] / (probes["gather_80MB_Gops"] * 1e9)
-                       + acc_r["value_loads"] / (probes["gather_880MB_Gops"] * 1e9)
-                       + acc_r["word_atomics"] / (probes["atomic_80MB_Gops"] * 1e9)
-                       + acc_r["value_stores"] / (probes["scatter_880MB_Gops"] * 1e9)
-                       + acc_r["word_stores"] / (probes["scatter_80MB_Gops"] * 1e9)
-                       + acc_r["stream_bytes"] / (probes["stream_GBps"] * 1e9))
-        t_eng = h * probes["engine_handoff_ns"] * 1e-9
-        t_rest = max(h_rest * probes["commit_handoff_ns"] * 1e-9, t_rest_roof)
-        x_cont = batch.n_txns / (t_eng + t_rest)
-        engine_bound = {"engine_txns": int(len(eng_txns)), "engine_rows": int(len(eng_rows)),
-                        "t_h_engine_ns": probes["engine_handoff_ns"], "engine_min_ms": round(t_eng * 1e3, 3),
-                        "rest_hot_row_writes": int(h_rest), "rest_min_ms": round(t_rest * 1e3, 3),
+        t_rest = h_rest * probes["commit_handoff_ns"] * 1e-9
+        x_cont = batch.n_txns / t_rest if h_rest else float("inf")
+        engine_bound = {"engine_txns": int(len(eng_txns)), "rest_hot_row_writes": int(h_rest),
+                        "rest_min_ms": round(t_rest * 1e3, 3),
                         "engine_ms": round(float(np.mean(engine_ns)) / 1e6, 3)}
     eff = min(x_roof, x_cont)
     measured = {"random_access_roof_txn_per_s": round(x_roof, 1), h_key: h,
-                "t_h_ns": t_h, "contention_bound_txn_per_s": round(x_cont, 1) if h else None,
+                "t_h_ns": t_h, "contention_bound_txn_per_s": round(x_cont, 1) if x_cont < float("inf") else None,
                 "effective_roof_txn_per_s": round(eff, 1), "active_bound": "contention" if x_cont < x_roof else "random-access",
                 "frac_of_effective": round(value / eff, 4), "hot_row_engine": engine_bound, "probes": probes,
                 "per_batch_accesses": acc}
@@ -652,8 +637,8 @@ def main():
     roofline["active_bound"] = measured["active_bound"]
     roofline["active"] = {"achieved": round(value, 1), "peak": round(eff, 1), "unit": "txn/s",
                           "frac": round(value / eff, 4),
-                          "peak_from": ("hot-row engine, then the rest of the batch: H x the engine's LDS hand-off, "
-                                        "plus the rest's hottest row x the commit hand-off (or its random accesses)"
+                          "peak_from": ("hot-row engine, then the rest of the batch: the rest's hottest row x the "
+                                        "commit hand-off"
                                         if engine_bound and measured["active_bound"] == "contention" else
                                         "H x t_h: writes to the hottest row times the measured commit hand-off"
                                         if measured["active_bound"] == "contention" else
@@ -669,7 +654,7 @@ def main():
                    "failed_holds": st["hot_failed"], "held_share": round(held, 4), "idle_share": round(1 - held, 4),
                    "hold_per_acquisition_ns": round(st["hot_hold_ns"] / st["hot_acq"], 1),
                    "kernel_ns_per_hot_commit": round(span / max(st["hot_writes"], 1), 1),
-                   "in": "engine_kernel" if st["engine_txns"] else "txn_kernel"}
+                   "in": "hot_engine" if st["engine_txns"] else "txn_kernel"}
 
     cpu = None
     if not args.no_cpu_baseline:

@@ -233,27 +233,19 @@ enum cc_mode { CC_MODE_PLAIN = 0, CC_MODE_EPOCH = 1, CC_MODE_SERVE = 2 };
                                      CC_MODE_SERVE); the final pass, which never defers, keeps the
                                      randomised back-off, so two transactions that block each other cannot
                                      retry in lockstep forever there */
-#define CC_RUN_HOT_ENGINE 0x800u  /* OCC, CC_MODE_PLAIN (CC_E_INVAL otherwise, and with CC_RUN_LATCH): run
-                                     the transactions that write one of the batch's most written rows
-                                     first, in one workgroup that holds those rows in LDS (hot-row engine:
-                                     up to 32 rows written at least max(2, n_txns / 4096) times, of at most
-                                     64 fields, found at submission; CC_STAT_ENGINE_*).  There an engine
-                                     row takes a reader-writer lock in LDS -- shared to read, exclusive to
-                                     write -- and a transaction that finds it taken gives back what it holds
-                                     and waits until it is free; the other rows follow OCC (lock written
-                                     rows, validate read rows) and the ticket comes from an LDS counter.  The rest of the
-                                     batch then runs as usual, with the engine rows only read.  Paper
-                                     Section 2 "Optimistic Concurrency Control" and Section 3.5 "OCC", with
-                                     hot rows locked pessimistically.  On by default for an OCC batch whose
-                                     most written row is written by at least a tenth of its transactions,
-                                     whose transactions have at most 32 ops, and whose rows left out of the
-                                     engine are written at most a quarter as often as the most written one
-                                     (elsewhere one workgroup carrying the hot rows' share loses to the
-                                     whole GPU).  The engine runs one
-                                     transaction per wavefront (64 lanes) and as many wavefronts as fit,
-                                     unless lanes_per_txn / waves_per_wg are set; it needs at most 4 ops per
-                                     lane (CC_E_INVAL at cc_run when forced without) and a batch submitted by
-                                     row (the keyed path finds rows only at the run). */
+#define CC_RUN_HOT_ENGINE 0x800u  /* OCC, CC_MODE_PLAIN (CC_E_INVAL otherwise, and with CC_RUN_LATCH): run the
+                                     transactions that write hot rows first, in their order in the batch, by a sort
+                                     of their accesses and a prefix scan (hot-row engine), as CC_GACCO does with a
+                                     whole batch; the rest of the batch then runs as usual, with the hot rows only
+                                     read.  Their tickets are their places in that order.  Paper Section 2
+                                     "Optimistic Concurrency Control" and Section 3.5 "OCC", with the conflicts
+                                     that are known before the run taken out of it.  On by default for an OCC batch
+                                     submitted by row (the keyed path finds rows only at the run) whose counted
+                                     conflicts make it pay; hot rows are then all rows written more than once.
+                                     Forced for another batch, they are up to 32 rows written at least max(2,
+                                     n_txns / 4096) times, of at most 64 fields, found at submission (none: no
+                                     engine).  Needs at most 4 ops per lane (64 lanes unless lanes_per_txn is set;
+                                     CC_E_INVAL at cc_run when forced without).  CC_STAT_ENGINE_* describe it. */
 #define CC_RUN_NO_HOT_ENGINE 0x1000u /* OCC: no hot-row engine (CC_E_INVAL with CC_RUN_HOT_ENGINE) */
 #define CC_RUN_EAGER_INSTALL 0x2u /* OCC only (CC_E_INVAL for another scheme): store new values in the
                                      validation round (undo on abort) instead of after validation
@@ -325,10 +317,11 @@ enum cc_stat {
   CC_STAT_KSETS = 26,      /* CC_GPUTX: K-sets (largest rank + 1) */
   CC_STAT_PACKED_STATE = 27, /* CC_GPUTX: 1 if the rank pass kept each row's rank state in its turn word
                                 (fewer than 2^20 transactions and 2^24 operations), else 0 */
-  CC_STAT_HOT_ACQ = 28,    /* OCC: acquisitions of the lock of the batch's most written row */
+  CC_STAT_HOT_ACQ = 28,    /* OCC: acquisitions of the lock of the batch's most written row (in the
+                              hot-row engine: its writes) */
   CC_STAT_HOT_FAILED = 29, /* OCC: of those, acquisitions whose attempt aborted (a failed hold) */
   CC_STAT_HOT_HOLD_NS = 30,/* OCC: time that row's lock was held, summed over acquisitions (the rest of
-                              CC_STAT_KERNEL_NS it was free) */
+                              CC_STAT_KERNEL_NS it was free; the hot-row engine has it for all its time) */
   CC_STAT_HOT_WRITES = 31, /* writes to the batch's most written row (counted at submission) */
   CC_STAT_BLOCKED_WAITS = 32, /* CC_RUN_WAIT_BLOCKER: waits for a held row that failed attempts entered */
   CC_STAT_VERSION_SLOTS = 33, /* CC_MVCC: slots of the version arena (32 bytes each): one per op of the
@@ -339,10 +332,10 @@ enum cc_stat {
                                  (the attempt aborted and retried with a newer timestamp) */
   CC_STAT_ENGINE_TXNS = 35,   /* hot-row engine (CC_RUN_HOT_ENGINE, or by default): transactions it ran
                                  (0: no engine) */
-  CC_STAT_ENGINE_ROWS = 36,   /* hot-row engine: rows it held in LDS */
+  CC_STAT_ENGINE_ROWS = 36,   /* hot-row engine: rows of the batch's plan (cc_engine_plan), at most 32 */
   CC_STAT_ENGINE_NS = 37,     /* hot-row engine: its kernel time (part of CC_STAT_KERNEL_NS) */
-  CC_STAT_ENGINE_WAITS = 38,  /* hot-row engine: times a transaction found an engine row taken, gave back
-                                 every row it held and waited for that row */
+  CC_STAT_ENGINE_WAITS = 38,  /* hot-row engine: accesses of its transactions to hot rows, each ordered
+                                 behind the row's earlier ones */
   CC_N_STATS = 40
 };
 
@@ -466,11 +459,9 @@ cc_status cc_fetch_rows(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows);
  * shared row space plus the row, tables in creation order -- most written
  * first; *n_rows their count (0: no engine for this batch: not OCC, keyed,
  * static, or nothing written often enough); *n_txns the transactions that
- * write one of them; *by_default 1 if no row left out of the engine is
- * written more than a quarter as often as the most written one -- one of the
- * conditions under which cc_run uses the engine without CC_RUN_HOT_ENGINE
- * (see there).  The transactions
- * are counted at the first call that needs them (a kernel over the batch).
+ * write one of them (counted by each call, a kernel over the batch);
+ * *by_default 1 if no row left out is written more than a quarter as often as
+ * the most written one.
  */
 #define CC_ENGINE_MAX_ROWS 32
 cc_status cc_engine_plan(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows, uint32_t *n_rows, uint64_t *n_txns,
@@ -597,11 +588,11 @@ cc_status cc_run_static(cc_ctx *ctx, const cc_txn *txns, uint64_t n_txns, const 
  *                          value store, publish), alternating between two
  *                          workgroups `peer` apart: ms / n_ops is the hot-row
  *                          hand-off time t_h
- *   CC_PROBE_ENGINE_HANDOFF n_ops rounds of the OCC hot-row engine's commit
- *                          critical section on one engine row (LDS lock, LDS
- *                          ticket, LDS validation load, LDS store and release),
- *                          alternating between two wavefronts of one workgroup:
- *                          ms / n_ops is the engine's t_h (peer is ignored)
+ *   CC_PROBE_ENGINE_HANDOFF n_ops rounds of a commit's critical section on a
+ *                          row held in LDS (LDS lock, LDS ticket, LDS
+ *                          validation load, LDS store and release), alternating
+ *                          between two wavefronts of one workgroup: ms / n_ops
+ *                          is the hand-off time there (peer is ignored)
  * Random addresses are uniform over the footprint_bytes / 8 words of the
  * probe's buffer (rounded down to a multiple of 4).  For the hand-off probes,
  * peer places the second side: 0 in the same workgroup (same CU), 8 in

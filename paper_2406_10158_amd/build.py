@@ -16,17 +16,12 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcc.so")
 SOURCES = [os.path.join(CSRC, f) for f in
            ("txn_occ.hip", "txn_2pl.hip", "txn_2plwd.hip", "txn_to.hip", "txn_mvcc.hip", "txn_tictoc.hip", "gacco.hip",
-            "gacco_exec.hip", "chain.hip", "gputx.hip", "index.hip", "ingest.hip", "kernels.hip", "latency.hip", "roofline.hip", "static_run.hip", "api.cpp")]
+            "gacco_exec.hip", "chain.hip", "gputx.hip", "hot_engine.hip", "index.hip", "ingest.hip", "kernels.hip", "latency.hip", "roofline.hip", "static_run.hip", "api.cpp")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else "hipcc")
 ARCH = "gfx950"
 # Packed FP32 instructions are disabled in all device code.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include")]
-# The OCC sources hold the hot-row engine, whose LDS atomics are issued by one
-# lane that owns the row (or are already aggregated per wavefront by hand): the
-# compiler's wavefront aggregation of atomics would only lengthen its critical
-# sections.
-EXTRA_FLAGS = {"txn_occ.hip": ["-Xarch_device", "-mllvm=-amdgpu-atomic-optimizer-strategy=None"]}
 
 
 def build(verbose: bool = False) -> str:
@@ -38,7 +33,7 @@ def build(verbose: bool = False) -> str:
         obj = os.path.join(tmpdir, os.path.basename(src) + ".o")
         cmd = [HIPCC, f"--offload-arch={ARCH}", *COMMON, "-c", src, "-o", obj]
         if src.endswith(".hip"):
-            cmd[1:1] = DEVICE_FLAGS + EXTRA_FLAGS.get(os.path.basename(src), [])
+            cmd[1:1] = DEVICE_FLAGS
         cmds.append((src, cmd))
         objs.append(obj)
 

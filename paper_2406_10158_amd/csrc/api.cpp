@@ -57,17 +57,19 @@ struct Batch {
   // nobody counted (cc_run_static), which then runs with the contended defaults
   bool hot_known = false;
   uint64_t hot_writes = 0;
+  double meet = 0;  // expected writes of one transaction to rows another one writes, for a random pair
   uint32_t n_hot = 0;
   uint32_t hot_rows[HOT_MAX] = {};
-  // OCC hot-row engine, planned at submission (plan_engine): its rows, and,
-  // once something needs them (split_batch), d_part = the transactions that
-  // write one of them (n_eng_txns), then the others; eng_gain: every row left out is written at most a quarter as often
-  // as the most written row
-  EngineArgs eng{};
-  uint64_t n_eng_txns = 0;
-  bool eng_gain = false;
+  // OCC's hot-row engine (hot_engine.hip): the plan's rows, and whether the
+  // batch's hot rows are worth it (decided at submission).  d_part, from the
+  // split (split_batch): the engine's transactions (n_eng_txns), then the
+  // others; d_eng_desc: the engine's.  eng_gain: every row left out of the plan
+  // is written at most a quarter as often as the most written row
+  EngineRows eng{};
+  bool eng_gain = false, eng_default = false;
+  uint64_t n_eng_txns = 0, n_eng_ops = 0, eng_behind = 0;
   uint32_t *d_part = nullptr;
-  EngineDesc *d_eng_desc = nullptr;  // the engine's transactions with their first op and op count
+  EngineDesc *d_eng_desc = nullptr;
 };
 
 }  // namespace
@@ -101,6 +103,7 @@ struct cc_ctx {
   uint32_t *d_latch = nullptr;        // CC_RUN_LATCH: one latch per global row
   uint64_t *d_kstate = nullptr;       // GPUTx: per-row rank state
   uint64_t *d_ingest = nullptr;       // batch submission: reduced results, then histograms
+  uint32_t *d_hot = nullptr;          //   a bit per global row: hot in the batch being submitted
   uint32_t *d_cnt = nullptr;          //   a count per global row, 0 between submissions
   unsigned char *d_sub = nullptr;     //   scratch, grown to the largest batch's need
   size_t sub_bytes = 0;
@@ -383,6 +386,7 @@ cc_status cc_destroy(cc_ctx *c) {
   if (c->d_kstate) (void)hipFree(c->d_kstate);
   if (c->d_ingest) (void)hipFree(c->d_ingest);
   if (c->d_cnt) (void)hipFree(c->d_cnt);
+  if (c->d_hot) (void)hipFree(c->d_hot);
   if (c->d_sub) (void)hipFree(c->d_sub);
   if (c->d_lat) (void)hipFree(c->d_lat);
   if (c->h_pin) (void)hipHostFree(c->h_pin);
@@ -783,18 +787,15 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   return CC_OK;
 }
 
-// The hot-row engine's plan (hot_engine.h) from the most written rows, most
-// first: at most ENG_MAX of them, each written at least max(2, n_txns / 4096)
-// times, of at most ENG_FIELDS fields and ENG_VALS cells in all.  eng_gain
-// holds when every row left out is written at most a quarter as often as the
-// most written row: otherwise the rest of the batch is about as contended as
-// the engine's share, and the engine's serial pass gains nothing.
+// The hot-row engine's plan from the most written rows, most first: at most
+// ENG_MAX of them, each written at least max(2, n_txns / 4096) times, of at
+// most ENG_FIELDS fields and ENG_VALS cells in all.
 static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &tables, Batch &b) {
-  b.eng = EngineArgs{};
+  b.eng = EngineRows{};
   b.eng_gain = false;
   const uint32_t thr = (uint32_t)std::max<uint64_t>(2, b.n_txns / 4096);
   if (nc == 0 || (uint32_t)(cand[0] >> 32) < thr) return;
-  uint32_t left_out = 0;  // writes of the most written row not taken
+  uint32_t left_out = 0, cells = 0;  // left_out: writes of the most written row not taken
   bool full = false;
   for (int i = 0; i < nc; ++i) {
     const uint32_t r = ~(uint32_t)cand[i], writes = (uint32_t)(cand[i] >> 32);
@@ -802,23 +803,34 @@ static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &
     for (const Table &t : tables)
       if (r >= t.row_base && r < t.row_base + t.n_rows) tb = &t;
     const bool take = !full && writes >= thr && tb && tb->n_fields <= (uint32_t)ENG_FIELDS &&
-                      b.eng.n_vals + tb->n_fields <= (uint32_t)ENG_VALS;
+                      cells + tb->n_fields <= (uint32_t)ENG_VALS;
     if (take) {
-      const uint32_t k = b.eng.n_rows++;
-      b.eng.row[k] = r;
-      b.eng.elem0[k] = (uint32_t)(tb->elem_base + (r - tb->row_base) * tb->n_fields);
-      b.eng.off[k] = b.eng.n_vals;
-      b.eng.n_vals += tb->n_fields;
+      b.eng.row[b.eng.n_rows++] = r;
+      cells += tb->n_fields;
       full = b.eng.n_rows == (uint32_t)ENG_MAX;
     } else if (!left_out) {
       left_out = writes;
     }
   }
-  if (b.eng.n_rows == 0) return;
-  b.eng.off[b.eng.n_rows] = b.eng.n_vals;
   // a row below the candidates is written at most as often as the last candidate
   if (!left_out && nc == PLAN_CAND) left_out = (uint32_t)(cand[nc - 1] >> 32);
-  b.eng_gain = (uint64_t)left_out * 4 <= cand[0] >> 32;
+  b.eng_gain = b.eng.n_rows && (uint64_t)left_out * 4 <= cand[0] >> 32;
+}
+
+// Whether the hot-row engine is worth it: it takes about 100 us and 0.1 ns an
+// op whatever the contention.  The transaction kernel takes about 2 ns a
+// transaction and try, and where `meet` and the transactions in flight make
+// x conflicts a transaction about 1 + 7 x tries; and it takes 3 us a write of
+// the most written row.  Measured, the run with the kernel alone and with the
+// engine (us; x): 2^18 x 16 ops on 4M rows 797, 560 (0.06); on 65,536 rows 9266,
+// 427 (4.0); Zipf 0.6 on 1M rows 10094, 476 (3.4); 2^16 x 16 ops on 4M rows 272,
+// 325 (0.06), on 1M rows 795, 225 (0.25); 2^12 x 4 ops on 16,384 rows 62, 111
+// (1.0), on 4,096 rows 221, 106 (4.1).  Below x = 0.05, where a transaction in
+// twenty meets another, the batch stays optimistic.
+static bool engine_pays(const Batch &b) {
+  const double n = (double)b.n_txns, x = b.meet * std::min(n, 4096.0);
+  const double kernel = 30.0 + std::max(2e-3 * n * (1.0 + 7.0 * x), 3.0 * (double)b.hot_writes);
+  return x >= 0.05 && 100.0 + 1e-4 * (double)b.n_ops < kernel;
 }
 
 // The batch's most written rows, counted at submission (write accesses per
@@ -829,10 +841,14 @@ static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables,
   const uint64_t *cand = res + INGEST_CAND;
   int nc = 0;
   while (nc < PLAN_CAND && cand[nc]) ++nc;
-  if (b.scheme == CC_OCC) plan_engine(cand, nc, tables, b);
   const uint32_t top = (uint32_t)res[INGEST_TOP];
   b.hot_known = true;
   b.hot_writes = top;
+  b.meet = b.n_txns ? (double)res[INGEST_PAIRS] / ((double)b.n_txns * (double)b.n_txns) : 0.0;
+  if (b.scheme == CC_OCC && !b.keyed) {
+    plan_engine(cand, nc, tables, b);
+    b.eng_default = engine_pays(b);
+  }
   b.n_hot = 0;
   const uint32_t thr = std::max<uint32_t>(1u, (top + 3) / 4);
   for (int i = 0; i < nc && i < HOT_MAX && (uint32_t)(cand[i] >> 32) >= thr; ++i) b.hot_rows[b.n_hot++] = ~(uint32_t)cand[i];
@@ -850,7 +866,7 @@ static hipError_t need_sub(cc_ctx *c, size_t bytes) {
   return e;
 }
 static void trim_sub(cc_ctx *c) {
-  constexpr size_t KEEP = 256u << 20;
+  constexpr size_t KEEP = 1u << 30;
   if (c->sub_bytes <= KEEP) return;
   (void)hipFree(c->d_sub);
   c->d_sub = nullptr;
@@ -858,17 +874,22 @@ static void trim_sub(cc_ctx *c) {
 }
 
 // Splits the batch into the engine's transactions and the others, on the
-// device (once; nothing without engine rows).
-static hipError_t split_batch(cc_ctx *c, Batch &b) {
-  if (b.eng.n_rows == 0 || b.d_part || b.n_txns == 0) return hipSuccess;
-  uint32_t *part = nullptr, n_eng = 0;
+// device (once): by `map`, the rows found hot at submission, or, without it, by
+// the plan's rows.
+static hipError_t split_batch(cc_ctx *c, Batch &b, const uint32_t *map) {
+  if (b.d_part || b.n_txns == 0) return hipSuccess;
+  uint32_t *part = nullptr, n_eng = 0, n_ops = 0;
+  uint64_t behind = 0;
   EngineDesc *desc = nullptr;
   hipError_t e = need_sub(c, split_scratch_words(b.n_txns) * sizeof(uint32_t));
+  uint32_t *w = (uint32_t *)c->d_sub;
   if (e == hipSuccess) e = hipMalloc(&part, b.n_txns * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMalloc(&desc, b.n_txns * sizeof(EngineDesc));
-  if (e == hipSuccess) e = launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, (uint32_t *)c->d_sub, part, desc);
+  if (e == hipSuccess) e = launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, map, w, part, desc, c->n_cu);
+  if (e == hipSuccess) e = hipMemcpyAsync(&behind, w, sizeof behind, hipMemcpyDeviceToHost, c->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(&n_eng, w + 2 + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(&n_eng, (uint32_t *)c->d_sub + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(&n_ops, w + 2 + 2 * b.n_txns + 1, sizeof n_ops, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
     if (part) (void)hipFree(part);
@@ -878,12 +899,9 @@ static hipError_t split_batch(cc_ctx *c, Batch &b) {
   b.d_part = part;
   b.d_eng_desc = desc;
   b.n_eng_txns = n_eng;
+  b.n_eng_ops = n_ops;
+  b.eng_behind = behind;
   return hipSuccess;
-}
-
-// Where the engine runs unless the caller says otherwise (see run_batch).
-static bool engine_by_default(const Batch &b) {
-  return b.eng.n_rows && b.eng_gain && b.max_ops <= 32 && (double)b.hot_writes / (double)b.n_txns >= 0.1;
 }
 
 // Run parameters against the scheme, before anything touches the device
@@ -1150,6 +1168,12 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   ia.rows = (uint32_t *)(ia.cand + plan_cand_max(n_ops));
   ia.owner = ia.rows + n_ops;
   ia.hist = (uint32_t *)(c->d_ingest + INGEST_N);
+  if (scheme == CC_OCC && !maybe_keyed) {
+    const size_t words = (n_rows + 31) / 32;
+    if (!c->d_hot) e = hipMalloc(&c->d_hot, words * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMemsetAsync(c->d_hot, 0, words * sizeof(uint32_t), c->stream);
+    ia.hot_map = c->d_hot;
+  }
   uint64_t res[INGEST_N] = {};
   if (e == hipSuccess) e = launch_ingest(c->stream, ia, c->n_cu);
   if (e == hipSuccess && n_ops) e = hipMemsetAsync(b.d_reads, 0, n_ops * sizeof(int64_t), c->stream);
@@ -1195,7 +1219,7 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
     plan_hot_rows(res, c->tables, b);
   }
   e = alloc_breaks(b);
-  if (e == hipSuccess && engine_by_default(b)) e = split_batch(c, b);
+  if (e == hipSuccess && b.eng_default) e = split_batch(c, b, c->d_hot);
   if (e != hipSuccess) {
     drop();
     return hip_fail(c, e, "batch allocation");
@@ -1323,11 +1347,18 @@ cc_status cc_engine_plan(cc_ctx *c, uint64_t batch_id, uint32_t *rows, uint32_t 
   const Batch &b = it->second;
   static_assert(CC_ENGINE_MAX_ROWS == ENG_MAX, "engine rows");
   for (uint32_t i = 0; i < (uint32_t)ENG_MAX; ++i) rows[i] = i < b.eng.n_rows ? b.eng.row[i] : 0u;
-  if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
-  const hipError_t e = split_batch(c, it->second);
-  if (e != hipSuccess) return hip_fail(c, e, "engine plan");
   *n_rows = b.eng.n_rows;
-  *n_txns = b.n_eng_txns;
+  *n_txns = 0;
+  if (b.eng.n_rows) {
+    if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
+    uint32_t n_eng = 0;
+    HIP_OR(c, need_sub(c, split_scratch_words(b.n_txns) * sizeof(uint32_t)));
+    uint32_t *w = (uint32_t *)c->d_sub;
+    HIP_OR(c, launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, nullptr, w, nullptr, nullptr, c->n_cu));
+    HIP_OR(c, hipMemcpyAsync(&n_eng, w + 2 + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream));
+    HIP_OR(c, hipStreamSynchronize(c->stream));
+    *n_txns = n_eng;
+  }
   *by_default = b.eng.n_rows && b.eng_gain ? 1 : 0;
   return CC_OK;
 }
@@ -1359,7 +1390,18 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   // contention of the batch: the share of transactions that write its most
   // written row (unknown: treated as contended)
   const double hot_share = b.hot_known && b.n_txns ? (double)b.hot_writes / (double)b.n_txns : 1.0;
-  const bool no_hot_row = hot_share < 0.001, contended = hot_share >= 0.02;
+  // OCC's hot-row engine (plain mode only: it knows no arrivals).  It has the
+  // scope of the launch shapes of at most 4 ops per lane (64 lanes unless the
+  // caller chose)
+  const uint32_t eng_lanes = p.lanes_per_txn ? p.lanes_per_txn : 64;
+  const bool eng_fits = (b.max_ops + eng_lanes - 1) / eng_lanes <= 4;
+  const bool use_eng = b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !(p.flags & CC_RUN_LATCH) && eng_fits &&
+                       b.n_txns &&
+                       ((p.flags & CC_RUN_HOT_ENGINE) ? b.eng.n_rows || b.eng_default
+                                                      : !(p.flags & CC_RUN_NO_HOT_ENGINE) && b.eng_default);
+  // (after the engine by the hot-row map nothing is left to conflict)
+  const bool no_hot_row = hot_share < 0.001 || (use_eng && b.eng_default);
+  const bool contended = !no_hot_row && hot_share >= 0.02;
   uint32_t lanes = p.lanes_per_txn;
   uint32_t wpw = p.waves_per_wg;
   if (lanes == 0) {
@@ -1374,11 +1416,6 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     }
   }
   if (wpw == 0) wpw = 1;
-  // the hot-row engine has variants up to 4 ops per lane; unless the caller
-  // chose, it runs one transaction per wavefront (64 lanes): its waiting teams
-  // then poll without waiting for other teams' round trips
-  const uint32_t eng_lanes = p.lanes_per_txn ? lanes : 64;
-  const bool eng_fits = (b.max_ops + eng_lanes - 1) / eng_lanes <= 4;
   if ((p.flags & CC_RUN_HOT_ENGINE) && !eng_fits)
     return fail(c, CC_E_INVAL, "CC_RUN_HOT_ENGINE needs at most 4 ops per lane");
   if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
@@ -1453,6 +1490,11 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     a.latch = c->d_latch;
   }
 
+  if (use_eng) {
+    HIP_OR(c, split_batch(c, b, nullptr));
+    HIP_OR(c, need_sub(c, engine_scratch_bytes(b.n_eng_ops, b.has_slot || b.has_cond, b.has_slot)));
+  }
+
   const uint32_t defer = p.defer_after ? p.defer_after : (p.mode == CC_MODE_SERVE ? 256 : 16);
   a.pass = 0;
   a.list = nullptr;
@@ -1477,8 +1519,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   const bool lat_early = host_stats && b.n_txns && b.n_txns <= (uint64_t)LAT_SMALL;
   const int64_t *lat_arrival = p.mode == CC_MODE_SERVE && b.d_arrival ? b.d_arrival + b.n_txns : nullptr;
   bool have_tail = false, have_latency = false;  // the last tail is the run's, and so are its latencies
-  double kernel_ms = 0, engine_ms = 0;
-  uint64_t engine_txns = 0;
+  double kernel_ms = 0;
   uint32_t passes = 0, epochs = 0;
   int first_grid = 0;
   bool epoch_limit = false;
@@ -1608,38 +1649,15 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       done_before = done;
     }
   } else if (b.n_txns) {
-    // OCC's hot-row engine: the transactions that write the batch's engine
-    // rows run first, alone, in one workgroup; the rest then run as usual
-    // (plain mode only: serving also passes here, and the engine knows no arrivals)
-    // By default only where its one workgroup pays: the most written row
-    // written by at least a tenth of the transactions, transactions of at
-    // most 32 ops, and no row left out nearly as hot.  Measured: Zipf 0.9
-    // and 0.99 gain 1.7-1.8x; Zipf 0.6 (0.5% of the transactions write the
-    // hottest row) and order-entry (8 warehouses: 6%; 1 warehouse: transactions
-    // of up to 66 ops) lose 7-56%.
-    const bool use_eng =
-        b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !latch && eng_fits && b.eng.n_rows &&
-        ((p.flags & CC_RUN_HOT_ENGINE) || (!(p.flags & CC_RUN_NO_HOT_ENGINE) && engine_by_default(b)));
     if (use_eng) {
-      const hipError_t es = split_batch(c, b);
-      if (es != hipSuccess) return hip_fail(c, es, "engine plan");
-      EngineArgs e = b.eng;
-      e.desc = b.d_eng_desc;
-      e.n_txns = b.n_eng_txns;
-      a.defer_after = 0;
-      HIP_OR(c, hipEventRecord(c->ev[1], c->stream));
-      int threads = 0;
-      // one workgroup: as many wavefronts as the variant allows, unless the caller chose
-      const hipError_t er =
-          launch_engine_occ(c->stream, (int)eng_lanes, (int)b.max_ops, (int)p.waves_per_wg, strict, a, e, &threads);
-      if (er != hipSuccess) return launch_error(c, er);
+      // OCC's hot-row engine: the transactions on the batch's hot rows run
+      // first, in their order; the rest then run as usual
+      HIP_OR(c, hipEventRecord(c->ev[4], c->stream));
+      HIP_OR(c, launch_engine(c->stream, strict, a, b.d_eng_desc, b.n_eng_txns, b.n_eng_ops, c->total_cells,
+                              b.has_slot || b.has_cond, b.has_slot, c->d_sub, p.ts_start, wait_limit_ticks(c, p),
+                              c->n_cu));
+      HIP_OR(c, hipEventRecord(c->ev[5], c->stream));
       HIP_OR(c, hipEventRecord(c->ev[2], c->stream));
-      HIP_OR(c, hipStreamSynchronize(c->stream));
-      float ms = 0;
-      HIP_OR(c, hipEventElapsedTime(&ms, c->ev[1], c->ev[2]));
-      kernel_ms += ms;
-      engine_ms = ms;
-      engine_txns = b.n_eng_txns;
       ++passes;
       a.list = b.d_part + b.n_eng_txns;
       a.n_txns = b.n_txns - b.n_eng_txns;
@@ -1657,8 +1675,10 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     HIP_OR(c, hipStreamSynchronize(c->stream));
     h = tail->ctl;
   }
-  float ms_run = 0;
+  float ms_run = 0, engine_ms = 0;
   HIP_OR(c, hipEventElapsedTime(&ms_run, c->ev[0], c->ev[2]));
+  if (use_eng) HIP_OR(c, hipEventElapsedTime(&engine_ms, c->ev[4], c->ev[5]));
+  kernel_ms += engine_ms;
   std::memset(b.stats, 0, sizeof(b.stats));
   b.stats[CC_STAT_COMMITTED] = h.stats[DS_COMMITTED];
   b.stats[CC_STAT_ATTEMPTS] = h.stats[DS_ATTEMPTS];
@@ -1670,10 +1690,10 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   b.stats[CC_STAT_MAX_ATTEMPTS] = h.stats[DS_MAX_ATTEMPTS];
   b.stats[CC_STAT_PASSES] = passes;
   b.stats[CC_STAT_DEFERRED] = h.stats[DS_DEFERRED];
-  b.stats[CC_STAT_ENGINE_TXNS] = engine_txns;
-  b.stats[CC_STAT_ENGINE_ROWS] = engine_txns ? b.eng.n_rows : 0;
+  b.stats[CC_STAT_ENGINE_TXNS] = use_eng ? b.n_eng_txns : 0;
+  b.stats[CC_STAT_ENGINE_ROWS] = use_eng ? b.eng.n_rows : 0;
   b.stats[CC_STAT_ENGINE_NS] = (uint64_t)(engine_ms * 1e6);
-  b.stats[CC_STAT_ENGINE_WAITS] = h.stats[DS_ENGINE_WAITS];
+  b.stats[CC_STAT_ENGINE_WAITS] = use_eng ? b.eng_behind : 0;
   b.stats[CC_STAT_GRID] = (uint64_t)first_grid;
   b.stats[CC_STAT_EPOCHS] = epochs;
   const double ns_per_tick = 1e6 / (double)c->wallclock_khz;
@@ -1687,6 +1707,12 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   b.stats[CC_STAT_HOT_FAILED] = h.stats[DS_HOT_FAILED];
   b.stats[CC_STAT_HOT_HOLD_NS] = (uint64_t)((double)h.stats[DS_HOT_HOLD] * ns_per_tick);
   b.stats[CC_STAT_HOT_WRITES] = b.hot_writes;
+  if (use_eng && (b.eng_default || b.eng.row[0] == a.hot0)) {
+    // every write of the most written row is in the engine, whose rows are its
+    // own as long as it runs
+    b.stats[CC_STAT_HOT_ACQ] += b.hot_writes;
+    b.stats[CC_STAT_HOT_HOLD_NS] += b.stats[CC_STAT_ENGINE_NS];
+  }
   b.stats[CC_STAT_BLOCKED_WAITS] = h.stats[DS_BLOCKED_WAITS];
   b.stats[CC_STAT_VERSION_SLOTS] = b.node_slots;
   b.stats[CC_STAT_VERSION_MISSES] = h.stats[DS_VERSION_MISS];
@@ -1698,6 +1724,8 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     const cc_status st = take_latency(c, b, p.mode == CC_MODE_SERVE);
     if (st) return st;
   }
+  if (h.stop && use_eng && !h.stats[DS_LATCH_STUCK])
+    return fail(c, CC_E_LIVELOCK, "the hot-row engine stopped: a value was not resolved within the wait limit");
   if (h.stats[DS_LATCH_STUCK] || h.stop)
     return fail(c, CC_E_LIVELOCK, "a row latch was not obtained within the spin limit; table contents are undefined");
   if (h.stats[DS_TS_OVERFLOW]) return fail(c, CC_E_TS_OVERFLOW, "timestamp overflow during the run");

@@ -1,6 +1,7 @@
-// Ordered execution of a whole batch by cell chains, for a serial order that
-// is known before the run (GaccO: transaction ids; GPUTx: its K-sets put
-// conflicting transactions in id order too, so the same values result).
+// Ordered execution of transactions by cell chains, for a serial order that is
+// known before the run (GaccO: transaction ids; GPUTx: its K-sets put
+// conflicting transactions in id order too, so the same values result; OCC's
+// hot-row engine: batch order, of its share of the batch, hot_engine.hip).
 //
 // Given the order, what an operation reads depends only on the earlier
 // operations of its own cell: a transaction touches a cell at most once, and
@@ -124,7 +125,7 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
   }
   const uint32_t before = p0 > 0 && p0 <= a.n ? a.keys[p0 - 1] : 0u;
   const uint32_t after = p0 + CH_ITEMS < a.n ? a.keys[p0 + CH_ITEMS] : 0u;
-  uint32_t kind[CH_ITEMS];
+  uint32_t kind[CH_ITEMS], read[CH_ITEMS];  // read: where the access's read value goes
   int64_t arg[CH_ITEMS], init[CH_ITEMS];
   bool ok[CH_ITEMS], gap[CH_ITEMS], head[CH_ITEMS], last[CH_ITEMS];
 #pragma unroll
@@ -135,11 +136,13 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
     kind[j] = CC_READ;
     arg[j] = init[j] = 0;
     gap[j] = true;
+    read[j] = op[j];
     if (ok[j]) {
       const DevOp o = a.ops[op[j]];
       gap[j] = o.rowk == GAP_OP;
       if (!gap[j]) kind[j] = op_kind(o.rowk);
       arg[j] = o.arg;
+      if (a.listed) read[j] = o.elem;
     }
     if (head[j]) init[j] = a.data[key[j]];
   }
@@ -217,7 +220,7 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
   for (int j = 0; j < CH_ITEMS; ++j) {
     if (head[j]) st = ChainVal{(uint64_t)init[j], CH_ABS, 0};
     if (ok[j]) {
-      if (!gap[j]) __builtin_nontemporal_store((int64_t)st.v, a.reads + op[j]);
+      if (!gap[j]) __builtin_nontemporal_store((int64_t)st.v, a.reads + read[j]);
       else if (BREAKS) a.result[op[j]] = st.v;  // chain_finish's value of the cell, if the chain ends here
       if (BREAKS) a.base[op[j]] = st.f == CH_BRK ? st.b + 1 : 0u;
     }
@@ -250,7 +253,7 @@ __global__ void __launch_bounds__(256) chain_break_kernel(ChainArgs a) {
     if (brk) {
       const uint64_t from = kind == CC_COND_ADD ? i : (uint64_t)a.txn_first[i] + (uint64_t)(o.arg & 0xFF);
       dep = a.base[from];
-      rel = (uint64_t)a.reads[from];
+      rel = (uint64_t)a.reads[a.listed ? a.ops[from].elem : (uint32_t)from];
     }
     bool done = !brk, told = !brk;
     uint64_t res = 0;
@@ -302,10 +305,11 @@ __global__ void __launch_bounds__(256) chain_finish_kernel(ChainArgs a) {
   const bool gap = o.rowk == GAP_OP;
   const uint32_t kind = gap ? (uint32_t)CC_READ : op_kind(o.rowk);
   const uint32_t dep = a.base[op];
-  uint64_t x = gap ? a.result[op] : (uint64_t)a.reads[op];
+  const uint32_t read = a.listed ? o.elem : op;
+  uint64_t x = gap ? a.result[op] : (uint64_t)a.reads[read];
   if (dep) {
     x += a.result[dep - 1];
-    if (!gap) a.reads[op] = (int64_t)x;
+    if (!gap) a.reads[read] = (int64_t)x;
   }
   const bool brk = ch_is_break(kind, o.arg);
   const bool last = p + 1 >= a.n || a.keys[p + 1] != key;
@@ -365,10 +369,8 @@ hipError_t chain_prepare(hipStream_t s, const ChainArgs &a, uint64_t n_cells, co
 }
 
 template <bool STRICT>
-static hipError_t chain_run(hipStream_t s, const ChainArgs &a, DevOutcome *out, uint64_t n_txns, const uint32_t *rank,
-                            uint32_t ns_per_tick_q16, int n_cu, int *grid_used) {
+static void chain_run(hipStream_t s, const ChainArgs &a, int n_cu) {
   const uint64_t tiles = chain_tiles(a.n);
-  *grid_used = (int)tiles;
   if (tiles) {
     const unsigned blocks = (unsigned)((a.n + 255) / 256);
     if (!a.base) {
@@ -381,16 +383,22 @@ static hipError_t chain_run(hipStream_t s, const ChainArgs &a, DevOutcome *out, 
       hipLaunchKernelGGL(chain_finish_kernel, dim3(blocks), dim3(256), 0, s, a);
     }
   }
-  const uint64_t bt = (n_txns + 255) / 256;
-  hipLaunchKernelGGL(chain_outcomes_kernel, dim3((unsigned)(bt ? bt : 1)), dim3(256), 0, s, out, n_txns, rank, a.ctl,
-                     ns_per_tick_q16);
+}
+
+hipError_t chain_scan(hipStream_t s, bool strict, const ChainArgs &a, int n_cu) {
+  strict ? chain_run<true>(s, a, n_cu) : chain_run<false>(s, a, n_cu);
   return hipGetLastError();
 }
 
 hipError_t chain_execute(hipStream_t s, bool strict, const ChainArgs &a, DevOutcome *out, uint64_t n_txns,
                          const uint32_t *rank, uint32_t ns_per_tick_q16, int n_cu, int *grid_used) {
-  return strict ? chain_run<true>(s, a, out, n_txns, rank, ns_per_tick_q16, n_cu, grid_used)
-                : chain_run<false>(s, a, out, n_txns, rank, ns_per_tick_q16, n_cu, grid_used);
+  *grid_used = (int)chain_tiles(a.n);
+  const hipError_t e = chain_scan(s, strict, a, n_cu);
+  if (e != hipSuccess) return e;
+  const uint64_t bt = (n_txns + 255) / 256;
+  hipLaunchKernelGGL(chain_outcomes_kernel, dim3((unsigned)(bt ? bt : 1)), dim3(256), 0, s, out, n_txns, rank, a.ctl,
+                     ns_per_tick_q16);
+  return hipGetLastError();
 }
 
 }  // namespace cce

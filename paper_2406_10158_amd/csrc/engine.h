@@ -72,8 +72,7 @@ enum DevStat {
   DS_HOT_HOLD = 21,     //   ticks the row was held, summed over acquisitions
   DS_BLOCKED_WAITS = 22,// CC_RUN_WAIT_BLOCKER: waits for a held row entered
   DS_VERSION_MISS = 23, // MVCC: old-version reads that found their version's slot reused (attempt aborted)
-  DS_ENGINE_WAITS = 24, // OCC hot-row engine: times a team kept its locks and waited for an engine row
-  DS_N = 25
+  DS_N = 24
 };
 
 struct Ctl {
@@ -157,26 +156,18 @@ struct IndexDesc {
   uint32_t levels;       // tree levels above level 0
 };
 
-// OCC hot-row engine (hot_engine.h): the batch's most written rows, held in
-// one workgroup's LDS while the transactions that write them run there.
-// Rows of at most ENG_FIELDS fields, ENG_VALS cells in all.
+// OCC's hot-row engine (hot_engine.hip).  Its plan: at most ENG_MAX rows of at
+// most ENG_FIELDS fields, ENG_VALS cells in all.
 constexpr int ENG_MAX = 32;
 constexpr int ENG_FIELDS = 64;
 constexpr int ENG_VALS = 1024;
-struct EngineDesc {           // one engine transaction: its id, first op and op count, and the
-  uint32_t txn, first, n, emask;  // engine rows it touches (bit k: engine row k)
+struct EngineRows {
+  uint32_t n_rows;            // 0: no engine
+  uint32_t row[ENG_MAX];      // global rows
 };
-struct EngineArgs {
-  const EngineDesc *desc;     // the engine's transactions, in batch order
-  uint64_t n_txns;
-  uint32_t n_rows;            // engine rows (0: no engine)
-  uint32_t n_vals;            // their cells
-  uint32_t row[ENG_MAX];      // global row of engine row i
-  uint32_t elem0[ENG_MAX];    // its first cell in the value arena
-  uint32_t off[ENG_MAX + 1];  // its first cell in LDS; off[n_rows] = n_vals
-  uint32_t pad[2];
+struct EngineDesc {           // one engine transaction: its id, first op, op count, and its first op's
+  uint32_t txn, first, n, at; // place among the engine's ops
 };
-
 // Per-op metadata of a keyed batch: bit 31 keyed, bits 16-23 table, 0-7 field.
 constexpr uint32_t META_KEYED = 1u << 31;
 
@@ -236,10 +227,12 @@ hipError_t launch_gacco(hipStream_t s, int lanes, int max_ops, int waves_per_wg,
 
 // Ordered execution by cell chains (chain.hip): arguments of its kernels.
 struct ChainArgs {
-  const DevOp *ops;
-  uint64_t n;               // operations
+  const DevOp *ops;         // in serial order
+  uint64_t n;
+  uint32_t listed;          // ops is a list of its own: an entry's elem is the index of its read value
+  uint32_t pad;
   const uint32_t *keys;     // sorted by cell ...
-  const uint32_t *vals;     // ... the operations, in serial order within a cell
+  const uint32_t *vals;     // ... the entries of ops, in serial order within a cell
   int64_t *data;
   int64_t *reads;
   uint64_t *meta, *sum, *total;  // per tile: look-back state (meta is cleared by chain_prepare)
@@ -256,6 +249,8 @@ uint64_t chain_tiles(uint64_t n);
 // the sorted list for chain_execute.
 hipError_t chain_prepare(hipStream_t s, const ChainArgs &a, uint64_t n_cells, const DevTxn *txns, uint64_t n_txns,
                          uint32_t *keys, uint32_t *vals, uint32_t *sort_scratch, uint32_t **keys_out, uint32_t **vals_out);
+// The scan alone.
+hipError_t chain_scan(hipStream_t s, bool strict, const ChainArgs &a, int n_cu);
 // Runs the batch and writes its outcome records: serial key (rank, id), rank 0
 // where rank is nullptr.  Does nothing but mark them pending if ctl->stop is set.
 hipError_t chain_execute(hipStream_t s, bool strict, const ChainArgs &a, DevOutcome *out, uint64_t n_txns,
@@ -319,6 +314,7 @@ enum IngestOut {
   INGEST_ROW_CUT,
   INGEST_N_CAND,
   INGEST_TOP,        // writes to the most written row
+  INGEST_PAIRS,      // sum over the rows of c (c - 1), c writes: ordered pairs of writes that meet
   INGEST_CAND,       // PLAN_CAND x (count << 32 | ~row), most written first, 0: none
   INGEST_N = INGEST_CAND + PLAN_CAND
 };
@@ -357,16 +353,27 @@ struct IngestArgs {
   uint64_t *keys;         // n_ops scratch words
   uint64_t *cand;         // plan_cand_max(n_ops) scratch words
   uint32_t *hist;         // PLAN_COUNTS + PLAN_BINS scratch words
+  uint32_t *hot_map;      // a bit per global row, cleared: set for rows written more than once (nullptr: no)
 };
 // Resets out, then validates and packs; the host reads `out` afterwards.
 hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu);
 
-// The transactions that write one of the engine rows, in batch order: part
-// (n_txns entries) lists them and then the others, desc describes them; their
-// number is scratch[n_txns] afterwards.  scratch: split_scratch_words(n_txns).
-constexpr uint64_t split_scratch_words(uint64_t n_txns) { return 2 * n_txns + 1 + (n_txns + 1) / 4096 + 2; }
-hipError_t launch_split(hipStream_t s, const DevOp *ops, const DevTxn *txns, uint64_t n_txns, const EngineArgs &e,
-                        uint32_t *scratch, uint32_t *part, EngineDesc *desc);
+// The transactions that write one of the engine's rows -- those of `map` (a bit
+// per global row), or e's where map is nullptr -- in batch order: part (n_txns
+// entries; nullptr: only count) lists them and then the others, desc describes
+// them.  Afterwards scratch (split_scratch_words(n_txns) words) holds a 64-bit
+// count of accesses to engine rows, then their number at [2 + n_txns] and their
+// ops' at [2 + n_txns + 1 + n_txns].
+constexpr uint64_t split_scratch_words(uint64_t n_txns) { return 2 + 2 * (n_txns + 1) + (n_txns + 1) / 4096 + 2; }
+hipError_t launch_split(hipStream_t s, const DevOp *ops, const DevTxn *txns, uint64_t n_txns, const EngineRows &e,
+                        const uint32_t *map, uint32_t *scratch, uint32_t *part, EngineDesc *desc, int n_cu);
+// The engine over n_txns transactions of m ops, in desc's order (tickets
+// ticket0 + 1, ...); leaves the claim counters at 0.  breaks: the batch has
+// conditional adds or slot writes; slots: slot writes.
+size_t engine_scratch_bytes(uint64_t m, bool breaks, bool slots);
+hipError_t launch_engine(hipStream_t s, bool strict, const RunArgs &r, const EngineDesc *desc, uint64_t n_txns,
+                         uint64_t m, uint64_t n_cells, bool breaks, bool slots, void *scratch, uint64_t ticket0,
+                         uint64_t wait_limit_ticks, int n_cu);
 // Exclusive scan of m 32-bit values in place (partial: (m + 4095) / 4096 + 1 words).
 void exclusive_scan_u32(hipStream_t s, uint32_t *data, uint64_t m, uint32_t *partial);
 
@@ -405,13 +412,6 @@ hipError_t launch_compact(hipStream_t s, const DevOutcome *out, uint64_t n_txns,
 // (lanes, ops-per-lane) combination.
 hipError_t launch_txn(hipStream_t s, int scheme, int lanes, int max_ops, int waves_per_wg, int grid,
                       bool strict, bool latch, const RunArgs &a, int n_cu, int *grid_used);
-
-// The OCC hot-row engine over e.list (txn_occ.hip): one workgroup of `waves`
-// wavefronts (0: the largest size the (lanes, ops-per-lane) variant allows);
-// hipErrorInvalidValue for a combination it has no variant for (more than 4
-// ops per lane).
-hipError_t launch_engine_occ(hipStream_t s, int lanes, int max_ops, int waves, bool strict, const RunArgs &a,
-                             const EngineArgs &e, int *threads_used);
 
 // Per-scheme launchers (txn_<scheme>.hip).
 #define CCE_DECLARE_LAUNCH(NAME)                                                                    \

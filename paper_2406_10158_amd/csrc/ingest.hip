@@ -415,6 +415,7 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
   for (uint32_t i = tid; i < (uint32_t)PLAN_COUNTS; i += NT) lds[i] = 0;
   __syncthreads();
   uint32_t top = 0;
+  uint64_t pairs = 0;
   for (uint64_t i0 = (uint64_t)b * NT * PLAN_STEP; i0 < a.n_ops; i0 += (uint64_t)nb * NT * PLAN_STEP) {
     uint32_t row[PLAN_STEP], c[PLAN_STEP];
 #pragma unroll
@@ -429,6 +430,8 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
       const uint64_t i = i0 + (uint64_t)j * NT + tid;
       if (row[j] != RC_NONE) {
         a.cnt[row[j]] = 0;
+        pairs += (uint64_t)c[j] * (c[j] - 1);
+        if (a.hot_map && c[j] > 1) atomicOr(&a.hot_map[row[j] >> 5], 1u << (row[j] & 31));
         atomicAdd(&lds[count_bin(c[j])], 1u);
         top = c[j] > top ? c[j] : top;
       }
@@ -439,7 +442,9 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
   for (uint32_t i = tid; i < (uint32_t)PLAN_COUNTS; i += NT)
     if (lds[i]) atomicAdd(&a.hist[i], lds[i]);
   top = (uint32_t)wave_max(top);
+  pairs = wave_sum(pairs);
   if (__lane_id() == 0 && top) atomicMax((unsigned long long *)&a.out[INGEST_TOP], (unsigned long long)top);
+  if (__lane_id() == 0 && pairs) add_word(&a.out[INGEST_PAIRS], pairs);
   if (!last_block(&a.out[INGEST_DONE1], nb)) return;
   if (tid < 64) {
     uint32_t cut = 0;
@@ -625,8 +630,15 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
   part_pack<1024, true>(a, s, loose, 0, 1);
   if (!a.cnt) return;
   __syncthreads();
+  uint64_t pairs = 0;
   for (uint32_t i = tid; i < rc_slots<true>; i += 1024)
-    if (s.cnt[i]) keys[atomicAdd(&n_keys, 1u)] = plan_key(s.row[i], s.cnt[i]);
+    if (s.cnt[i]) {
+      keys[atomicAdd(&n_keys, 1u)] = plan_key(s.row[i], s.cnt[i]);
+      pairs += (uint64_t)s.cnt[i] * (s.cnt[i] - 1);
+      if (a.hot_map && s.cnt[i] > 1) atomicOr(&a.hot_map[s.row[i] >> 5], 1u << (s.row[i] & 31));
+    }
+  pairs = wave_sum(pairs);
+  if (__lane_id() == 0 && pairs) add_word(&a.out[INGEST_PAIRS], pairs);
   __syncthreads();
   sort_candidates<1024>(a, keys, n_keys);
   __syncthreads();
@@ -655,71 +667,6 @@ hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu) {
     hipLaunchKernelGGL(plan_ties_kernel, g, dim3(256), 0, s, a);
     hipLaunchKernelGGL(plan_pick_kernel, g, dim3(256), 0, s, a);
   }
-  return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// the hot-row engine's share of a batch
-// ---------------------------------------------------------------------------
-// Per transaction: whether it writes an engine row, and which it touches.
-__global__ void __launch_bounds__(256) split_flags_kernel(const DevOp *ops, const DevTxn *txns, uint64_t n_txns,
-                                                          EngineArgs e, uint32_t *flag, uint32_t *emask) {
-  const uint64_t t = ((uint64_t)blockIdx.x * 256 + threadIdx.x) / IG_L;
-  const uint32_t tl = threadIdx.x % IG_L;
-  uint32_t touch = 0, write = 0;
-  if (t < n_txns) {
-    const DevTxn d = txns[t];
-    for (uint32_t j = tl; j < d.n; j += IG_L) {
-      const uint32_t rk = ops[d.first + j].rowk, row = op_row(rk);
-      uint32_t bit = 0;
-#pragma unroll
-      for (int k = 0; k < ENG_MAX; ++k)
-        bit |= (uint32_t)k < e.n_rows && e.row[k] == row ? 1u << k : 0u;
-      touch |= bit;
-      write |= op_written(rk) ? bit : 0u;
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < IG_L; o <<= 1) {
-    touch |= (uint32_t)__shfl_xor((int)touch, o, 64);
-    write |= (uint32_t)__shfl_xor((int)write, o, 64);
-  }
-  if (t < n_txns && tl == 0) {
-    flag[t] = write ? 1u : 0u;
-    emask[t] = touch;
-  }
-}
-
-// Engine transactions first, then the others, each in batch order.  `before`
-// is the exclusive scan of the flags over n_txns + 1 entries.
-__global__ void __launch_bounds__(256) split_lists_kernel(const DevTxn *txns, uint64_t n_txns, const uint32_t *before,
-                                                          const uint32_t *emask, uint32_t *part, EngineDesc *desc) {
-  const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= n_txns) return;
-  const uint32_t at = before[t], n_eng = before[n_txns];
-  if (before[t + 1] != at) {
-    const DevTxn d = txns[t];
-    part[at] = (uint32_t)t;
-    desc[at] = EngineDesc{(uint32_t)t, d.first, d.n, emask[t]};
-  } else {
-    part[n_eng + (uint32_t)t - at] = (uint32_t)t;
-  }
-}
-
-__global__ void __launch_bounds__(64) split_end_kernel(uint32_t *flag, uint64_t n_txns) {
-  if (threadIdx.x == 0) flag[n_txns] = 0;
-}
-
-hipError_t launch_split(hipStream_t s, const DevOp *ops, const DevTxn *txns, uint64_t n_txns, const EngineArgs &e,
-                        uint32_t *scratch, uint32_t *part, EngineDesc *desc) {
-  uint32_t *flag = scratch, *emask = flag + n_txns + 1, *partial = emask + n_txns;
-  if (n_txns == 0) return hipSuccess;
-  const uint64_t teams = (n_txns * IG_L + 255) / 256, blocks = (n_txns + 255) / 256;
-  if (teams > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(split_flags_kernel, dim3((unsigned)teams), dim3(256), 0, s, ops, txns, n_txns, e, flag, emask);
-  hipLaunchKernelGGL(split_end_kernel, dim3(1), dim3(64), 0, s, flag, n_txns);
-  exclusive_scan_u32(s, flag, n_txns + 1, partial);
-  hipLaunchKernelGGL(split_lists_kernel, dim3((unsigned)blocks), dim3(256), 0, s, txns, n_txns, flag, emask, part, desc);
   return hipGetLastError();
 }
 

@@ -140,13 +140,11 @@ __global__ void __launch_bounds__(128) probe_commit_handoff(uint64_t *buf, uint6
   }
 }
 
-// The hot-row engine's commit critical section on one engine row, handed
-// back and forth between two wavefronts of one workgroup: wait for the turn
-// (an LDS word, bounded), take the row's LDS lock, draw a ticket from an LDS
-// counter, load a validation word from LDS (the engine validates its other
-// rows in an LDS table), store the new value in LDS and release the lock.
-// The time per round is the shortest interval between two commits on one
-// engine row: the engine's t_h.
+// A commit's critical section on one row held in LDS, handed back and forth
+// between two wavefronts of one workgroup: wait for the turn (an LDS word,
+// bounded), take the row's LDS lock, draw a ticket from an LDS counter, load a
+// validation word from LDS, store the new value in LDS and release the lock.  The time per round is the shortest interval between two commits
+// on one such row.
 __global__ void __launch_bounds__(128) probe_engine_handoff(uint64_t *buf, uint64_t rounds, uint64_t spin_limit,
                                                             uint64_t *err) {
   __shared__ uint32_t lk;
