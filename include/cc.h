@@ -198,7 +198,8 @@ enum cc_mode { CC_MODE_PLAIN = 0, CC_MODE_EPOCH = 1, CC_MODE_SERVE = 2 };
                                      sign of contention) when the batch's most written row takes writes
                                      from at least 2% of its transactions, and never below that, where
                                      the extra round costs more than it saves.  CC_E_INVAL for another
-                                     scheme, or together with CC_RUN_NO_PRECHECK */
+                                     scheme, or together with CC_RUN_NO_PRECHECK.  TO and MVCC look at every word
+                                     before they take anything in any case: neither flag changes them */
 #define CC_RUN_NO_PRECHECK 0x10u  /* OCC, TicToc, TO and MVCC: never run the pre-check round (CC_E_INVAL for
                                      another scheme) */
 #define CC_RUN_LATCH 0x40u        /* latch variants of the non-deterministic schemes (paper Section 4.2,

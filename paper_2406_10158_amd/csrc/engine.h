@@ -116,8 +116,8 @@ struct RunArgs {
   uint64_t budget_cap;     // serving: admission cap on reserved bytes (0: no cap)
   uint32_t bytes_per_op;   // serving: log / version bytes one operation reserves
   uint32_t eager_install;  // OCC: store values in the validation round (undo on abort)
-  uint32_t pad4;
-  uint32_t precheck;       // OCC, TicToc, TO, MVCC: load-only round before any lock: 0 never, 1 on retries, 2 always
+  uint32_t chunk;          // queue positions a team claims at a time (set by the launcher)
+  uint32_t precheck;       // OCC, TicToc: load-only round before any lock: 0 never, 1 on retries, 2 always
   uint32_t wd_wait_limit;  // 2PL wait-die: waits of one attempt before it dies anyway
   uint32_t node_reuse;     // MVCC: 0 = a slot per op (op i keeps slot i, never reused); 1 = the ring protocol
   uint32_t *latch;         // CC_RUN_LATCH: one 32-bit latch per global row (else unused)

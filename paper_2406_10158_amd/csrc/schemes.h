@@ -508,17 +508,30 @@ __device__ __forceinline__ int tplwd_attempt(const Team<L> &t, Slots<K> &s, bool
 // word = commit/dirty bit, 31-bit RTS, 31-bit WTS, Table 2; MVCC adds a
 // 64-bit version pointer per row).  Layout: bit 63 dirty (an uncommitted
 // write holds the row), bits 61-31 RTS, bits 30-0 WTS.
-//   R0  draw a timestamp ts for this attempt (one global counter).
-//   R1  write rows: CAS loop -- abort if dirty or ts < RTS or ts < WTS, else
-//       set dirty.  read rows: CAS loop -- abort if dirty (no waiting for the
-//       writer) or ts < WTS (TO; MVCC instead reads an older version); else
-//       raise RTS to ts.
-//   R2  read values (MVCC, older version: also the version pointer).
-//   R3  re-check read rows: not dirty and the same WTS, so the value read
-//       belongs to the version checked in R1.  MVCC old-version reads walk
-//       the version chain back to the newest writer with timestamp <= ts.
+//   R1  load every row's word; abort if one is dirty (nothing to undo, no
+//       timestamp drawn).
+//   R2  read values; draw a timestamp ts for this attempt (one global counter),
+//       newer than every timestamp in the words of R1.
+//   R3  take the rows: one CAS from the word of R1, which sets dirty on a
+//       write row and raises RTS to ts on a read row.  If it succeeds, or the
+//       row only had its RTS raised in between, the value read in R2 is the
+//       version of R1's word: a writer changes a row's values while it holds it
+//       dirty and leaves a newer WTS.  Abort if the row is dirty, if ts < RTS
+//       (write rows) or if another version is current (MVCC: for a read row
+//       whose WTS is now above ts, read an older version).
 //   R4  (MVCC: record each write's pre-image in its history node and link
 //       it) store new values, wait, publish word = {RTS=ts, WTS=ts}.
+// So a row is dirty for two round trips (R3's CAS, R4's stores), which bound a
+// contended batch, and an attempt takes five.  Timestamp first, then word, CAS,
+// values, re-check and stores -- seven, a row dirty for four -- took 21.0 ms (TO)
+// and 23.6 ms (MVCC) for 65,536 transactions x 16 ops, half writes, Zipf 0.8 on
+// 10M rows, where this takes 14.3 and 18.7 ms.
+// MVCC old-version reads (R3b, only wavefronts that have one): the value
+// and the version pointer, then the word once more -- unchanged and clean, so
+// the chain is complete -- and the chain back to the newest writer with
+// timestamp <= ts.  An operation that shares its row with an earlier one of
+// the transaction follows it: it reads the current version as long as that one
+// did, and looks for itself where some row of the transaction went back.
 // Serial key (0, ts).  Timestamps are relative to the run and must stay
 // below 2^31; reaching it stops the run with CC_E_TS_OVERFLOW.
 // Version arena (MVCC): a ring of n_nodes slots of 4 words {tag, prev,
@@ -534,7 +547,7 @@ __device__ __forceinline__ int tplwd_attempt(const Team<L> &t, Slots<K> &s, bool
 // version is gone and the attempt aborts (its retry draws a newer ts).  A
 // node is complete before any reader can reach it: it is linked while its
 // writer holds the row dirty, and readers walk only chains they found clean
-// and unchanged in R3.  The ring is sized by the run: one slot per op of the
+// and unchanged after reading the pointer.  The ring is sized by the run: one slot per op of the
 // batch, or, when serving, hbm_cap_bytes / 32, which bounds the arena.
 // Each run starts with empty chains, so with a slot for every op of the batch
 // no slot is ever taken twice in a run: op i then writes its node into slot i
@@ -551,117 +564,147 @@ constexpr int MVCC_MAX_WALK = 1 << 16;
 
 template <int L, int K, bool STRICT, bool MV, bool LATCH>
 __device__ __forceinline__ int to_attempt(const Team<L> &t, Slots<K> &s, bool active, const RunArgs &a,
-                                          bool precheck, uint64_t *hi, uint64_t *lo) {
+                                          uint64_t *hi, uint64_t *lo) {
   uint32_t blk = ~0u;
-  bool pre_fail = false;
-  if (ballot(active && precheck)) {
-    // R0 (as OCC's, by default from a transaction's second attempt on): give
-    // up before taking a timestamp or marking any row if a row is dirty (an
-    // uncommitted write holds it), which R1 would abort on anyway
-    bool busy = false;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      if (active && precheck && s.valid[k] && op_leader(s.rowk[k])) {
-        const uint64_t o = ld_word(a.words + op_row(s.rowk[k]));
-        if ((o & TO_DIRTY) && blk == ~0u) blk = op_row(s.rowk[k]);
-        busy |= (o & TO_DIRTY) != 0;
-      }
-    }
-    order_point<STRICT>();
-    pre_fail = t.any(busy);
-  }
-  const bool go = active && !pre_fail;
-  const uint64_t ts = t.claim(&a.ctl->ticket, go, 1) + 1;
-  const bool overflow = go && ts > TO_MASK31;
-  bool fail = overflow || (active && pre_fail);
-  bool old_ver[K];  // MVCC: this op reads a version older than the current one
+  bool fail = false;
+  // R1
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     s.got[k] = false;
+    if (active && s.valid[k] && op_leader(s.rowk[k])) s.v[k] = ld_word(a.words + op_row(s.rowk[k]));
+  }
+  order_point<STRICT>();
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const bool dirty = active && s.valid[k] && op_leader(s.rowk[k]) && (s.v[k] & TO_DIRTY);
+    if (dirty && blk == ~0u) blk = op_row(s.rowk[k]);
+    fail |= dirty;
+  }
+  const bool go = active && !t.any(fail);
+  // R2; a row's version pointer changes with its word, so the one read here
+  // is the one a writer of this version links to
+  uint64_t ptr[K];
+  bool multi = false;  // MVCC: an operation writes a row that an earlier one also accesses
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    ptr[k] = 0;
+    if (go && s.valid[k]) {
+      s.x[k] = ld_val(a.data + s.elem[k]);
+      if (MV && op_kind(s.rowk[k]) != CC_READ) {
+        multi |= !op_leader(s.rowk[k]);
+        ptr[k] = ld_word(a.aux + op_row(s.rowk[k]));
+      }
+    }
+  }
+  const uint64_t ts = t.claim(&a.ctl->ticket, go, 1) + 1;
+  const bool overflow = go && ts > TO_MASK31;
+  order_point<STRICT>();
+  // R3: the first try of every row issued before any result is looked at
+  fail |= overflow;
+  bool stale = false;  // a row was free but not the version read, or newer than ts
+  uint64_t seen[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const uint64_t w = s.v[k];
+    seen[k] = w;
+    if (go && !overflow && s.valid[k] && op_leader(s.rowk[k]))
+      seen[k] = w_apply<LATCH, STRICT>(
+          a, a.words + op_row(s.rowk[k]), WOP_CAS, w,
+          op_written(s.rowk[k]) ? (w | TO_DIRTY) : to_word(to_rts(w) > ts ? to_rts(w) : ts, to_wts(w)));
+  }
+  order_point<STRICT>();
+  bool old_ver[K];  // MVCC: this op reads a version older than the current one
+  bool any_old = false;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
     old_ver[k] = false;
-    const bool lead = op_leader(s.rowk[k]);
-    // MVCC followers of read rows also look at the word, to pick the version
-    const bool look = lead || (MV && !op_written(s.rowk[k]));
-    if (go && !overflow && s.valid[k] && look) {
+    if (go && !overflow && s.valid[k] && op_leader(s.rowk[k])) {
+      const bool wr = op_written(s.rowk[k]);
       uint64_t *wp = a.words + op_row(s.rowk[k]);
-      uint64_t w = ld_word(wp);
-      bool done = false, bad = false;
+      uint64_t w = seen[k], want = s.v[k];
+      const uint64_t wts = to_wts(want);
+      bool done = w == want, bad = false;
+      s.got[k] = done && wr;
       for (int it = 0; it < CAS_RETRIES && !done && !bad; ++it) {
-        // a write marks the row dirty, a read raises RTS to ts: either way
-        // one CAS, issued from a single site (see w_apply)
-        bool try_cas = false;
-        uint64_t desired = 0;
         if (w & TO_DIRTY) {
           bad = true;
-        } else if (op_written(s.rowk[k])) {
-          if (ts < to_rts(w) || ts < to_wts(w)) {
-            bad = true;
-          } else {
-            try_cas = true;
-            desired = w | TO_DIRTY;
-          }
-        } else if (ts < to_wts(w)) {
-          if (MV) {
+          if (blk == ~0u) blk = op_row(s.rowk[k]);
+        } else if (to_wts(w) != wts) {
+          if (MV && !wr && ts < to_wts(w)) {
             old_ver[k] = true;
             done = true;
           } else {
+            stale = true;
             bad = true;
           }
-        } else if (!lead || to_rts(w) >= ts) {
+        } else if (wr && ts < to_rts(w)) {
+          stale = true;
+          bad = true;
+        } else if (!wr && to_rts(w) >= ts) {
           done = true;
         } else {
-          try_cas = true;
-          desired = to_word(ts, to_wts(w));
-        }
-        if (try_cas && w_cas<LATCH, STRICT>(a, wp, &w, desired)) {
-          done = true;
-          s.got[k] = op_written(s.rowk[k]);
+          // a read raised RTS in between: once more, from its word
+          want = w;
+          if (w_cas<LATCH, STRICT>(a, wp, &w, wr ? (w | TO_DIRTY) : to_word(ts, wts))) {
+            done = true;
+            s.got[k] = wr;
+          }
         }
       }
-      s.v[k] = w;
-      if ((w & TO_DIRTY) && bad && blk == ~0u) blk = op_row(s.rowk[k]);
+      s.v[k] = old_ver[k] ? w : want;
+      any_old |= old_ver[k];
       fail |= bad || !done;
     }
   }
   order_point<STRICT>();
   s.block = blocking_row(t, blk);
-  const bool lock_fail = t.any(fail);
-  const bool alive = active && !lock_fail;
+  const bool all_stale = t.any(stale);
+  bool lock_fail = t.any(fail), valid_fail = false;
   if (active && lock_fail) {
 #pragma unroll
     for (int k = 0; k < K; ++k)
       if (s.got[k]) w_st<LATCH, STRICT>(a, a.words + op_row(s.rowk[k]), s.v[k]);
   }
-  uint64_t ptr[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    ptr[k] = 0;
-    if (alive && s.valid[k]) {
-      s.x[k] = ld_val(a.data + s.elem[k]);
-      if (MV && old_ver[k]) ptr[k] = ld_word(a.aux + op_row(s.rowk[k]));
-    }
+  if (lock_fail && all_stale && s.block == ~0u) {
+    lock_fail = false;
+    valid_fail = true;
   }
-  order_point<STRICT>();
-  bool bad = false;
-  bool same[K];  // the row's word did not change between R1 and R3
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    same[k] = true;
-    const bool look = op_leader(s.rowk[k]) || (MV && !op_written(s.rowk[k]));
-    if (alive && s.valid[k] && look && !op_written(s.rowk[k])) {
-      const uint64_t w2 = ld_word(a.words + op_row(s.rowk[k]));
-      same[k] = !(w2 & TO_DIRTY) && to_wts(w2) == to_wts(s.v[k]);
-      bad |= !same[k];
-    }
-  }
-  if (MV) {
-    // Old-version reads walk the chain from the pointer read in R2.  Only
-    // when the word did not change: then no writer linked nodes before our
-    // R3 load, and writers after it link above that pointer, so the nodes
-    // walked are complete.  Indices and length are still bounded.
+  const bool alive = go && !lock_fail && !valid_fail;
+  if (MV && ballot(alive && any_old)) {
+    // R3b
+    const bool team_old = t.any(alive && any_old);
+    bool bad = false, look[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      if (alive && old_ver[k] && same[k]) {
+      look[k] = alive && team_old && s.valid[k] && !op_written(s.rowk[k]) && (old_ver[k] || !op_leader(s.rowk[k]));
+      if (look[k] && !old_ver[k]) s.v[k] = ld_word(a.words + op_row(s.rowk[k]));
+    }
+    order_point<STRICT>();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!look[k]) continue;
+      bad |= (s.v[k] & TO_DIRTY) != 0;
+      look[k] = !(s.v[k] & TO_DIRTY) && to_wts(s.v[k]) > ts;
+      if (look[k]) {
+        s.x[k] = ld_val(a.data + s.elem[k]);
+        ptr[k] = ld_word(a.aux + op_row(s.rowk[k]));
+      }
+    }
+    order_point<STRICT>();
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (!look[k]) continue;
+      const uint64_t w2 = ld_word(a.words + op_row(s.rowk[k]));
+      if ((w2 & TO_DIRTY) || to_wts(w2) != to_wts(s.v[k])) {
+        look[k] = false;
+        bad = true;
+      }
+    }
+    order_point<STRICT>();
+    // Indices and length of the walk are bounded.
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (look[k]) {
         const uint32_t cell = s.elem[k];
         int64_t val = s.x[k];
         uint64_t p = ptr[k];
@@ -693,8 +736,8 @@ __device__ __forceinline__ int to_attempt(const Team<L> &t, Slots<K> &s, bool ac
         s.x[k] = val;
       }
     }
+    valid_fail |= t.any(bad);
   }
-  bool valid_fail = t.any(bad);
   bool commit = alive && !valid_fail;
   uint64_t pos[K];
   if (MV && !a.node_reuse) {
@@ -757,18 +800,22 @@ __device__ __forceinline__ int to_attempt(const Team<L> &t, Slots<K> &s, bool ac
       if (s.got[k]) w_st<LATCH, STRICT>(a, a.words + op_row(s.rowk[k]), s.v[k]);
   }
   if (MV) {
+    const bool xchg = ballot(multi) != 0;  // wavefront-uniform
     // link each claimed node into its row's chain (we hold the row dirty, so
     // only our own lanes link it concurrently) and fill it; the tag that
     // validates it is stored with the installs, before the row is published
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (commit && s.valid[k] && op_kind(s.rowk[k]) != CC_READ) {
-        uint64_t *node = a.nodes + 4 * (pos[k] % a.n_nodes);
-        const uint64_t me = ((pos[k] / a.n_nodes + 1) << 32) | (pos[k] % a.n_nodes + 1);
+        const uint64_t lap = a.node_reuse ? pos[k] / a.n_nodes : 0, slot = a.node_reuse ? pos[k] % a.n_nodes : pos[k];
+        uint64_t *node = a.nodes + 4 * slot;
+        const uint64_t me = ((lap + 1) << 32) | (slot + 1);
         st_word(node + 2, ts | ((uint64_t)s.elem[k] << 32));
         st_word(node + 3, (uint64_t)s.x[k]);
-        const uint64_t prev = xchg_word(a.aux + op_row(s.rowk[k]), me);
-        st_word(node + 1, prev);
+        // the row's only write links to the pointer R2 read; several take turns
+        if (xchg) ptr[k] = xchg_word(a.aux + op_row(s.rowk[k]), me);
+        else st_word(a.aux + op_row(s.rowk[k]), me);
+        st_word(node + 1, ptr[k]);
       }
     }
     if (a.node_reuse) {
@@ -797,14 +844,16 @@ __device__ __forceinline__ int to_attempt(const Team<L> &t, Slots<K> &s, bool ac
 // Table 2).  Layout: bit 63 lock, bits 62-48 delta, bits 47-0 WTS.
 //   R1  write rows: try-lock with fetch_or (abort if held); read rows: load
 //       the word (abort if locked).
-//   R2  read values; draw a ticket (tie-breaker for equal commit
-//       timestamps); commit_ts = max over write rows of RTS+1 and over read
+//   R2  read values; commit_ts = max over write rows of RTS+1 and over read
 //       rows of WTS (team maximum).
 //   R3  every read row must still carry the observed WTS and be unlocked (so
 //       the value read in R2 is that version's); if its RTS < commit_ts,
 //       extend RTS to commit_ts by CAS (if the delta would not fit in 15
 //       bits, WTS is raised instead -- only other readers of the old WTS are
 //       affected, and they abort).
+//       In the same round draw a ticket, the tie-breaker for equal commit
+//       timestamps: only a reader of a row can share its writer's, and it draws
+//       after it has seen the word that the writer stored after its own draw.
 //   R4  store values, wait, publish word = {WTS = commit_ts, delta = 0}.
 // Serial key (commit_ts, ticket).
 // ===========================================================================
@@ -837,17 +886,25 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
     pre_fail = t.any(fail);
   }
   const bool go = active && !pre_fail;
-  // locks and loads all issued before any result is looked at (see OCC's R1)
+  // locks and loads all issued before any result is looked at (see OCC's R1).
+  // After R0 also the values: a read-only row's comes after the word R0 saw,
+  // which R3 validates; a written row's is issued beside its lock, and is the
+  // row's value under the lock if the lock returns the WTS R0 saw (every commit
+  // raises it, and a writer whose install the load could have seen held the
+  // lock until it had).  Rows are then held for R1, R3 and the installs only.
   bool issued[K];
+  uint64_t seen[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     s.got[k] = false;
+    seen[k] = s.v[k];
     issued[k] = go && s.valid[k] && op_leader(s.rowk[k]) && (!precheck || op_written(s.rowk[k]));
     if (issued[k]) {
       uint64_t *w = a.words + op_row(s.rowk[k]);
       if (op_written(s.rowk[k])) s.v[k] = w_or<LATCH, STRICT>(a, w, TT_LOCK);
       else s.v[k] = ld_word(w);
     }
+    if (precheck && go && s.valid[k]) s.x[k] = ld_val(a.data + s.elem[k]);
   }
   order_point<STRICT>();
 #pragma unroll
@@ -855,7 +912,10 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
     if (!issued[k]) continue;
     const uint64_t o = s.v[k];
     if ((o & TT_LOCK) && blk == ~0u) blk = op_row(s.rowk[k]);
-    if (op_written(s.rowk[k])) s.got[k] = !(o & TT_LOCK);
+    if (op_written(s.rowk[k])) {
+      s.got[k] = !(o & TT_LOCK);
+      fail |= precheck && tt_wts(o) != tt_wts(seen[k]);
+    }
     fail |= (o & TT_LOCK) != 0;
   }
   s.block = blocking_row(t, blk);
@@ -870,16 +930,24 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     if (alive && s.valid[k]) {
-      s.x[k] = ld_val(a.data + s.elem[k]);
+      if (!precheck) s.x[k] = ld_val(a.data + s.elem[k]);
       if (op_leader(s.rowk[k])) {
         const uint64_t c = op_written(s.rowk[k]) ? tt_rts(s.v[k]) + 1 : tt_wts(s.v[k]);
         cts = c > cts ? c : cts;
       }
     }
   }
-  const uint64_t ticket = t.claim(&a.ctl->ticket, alive, 1) + 1;
   cts = t.max(cts);
   const bool overflow = alive && cts > TT_WTS_MASK - TT_DELTA_MAX;
+  if (ballot(alive && !precheck)) order_point<STRICT>();
+  // R3: the words and the ticket in one round
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    seen[k] = 0;
+    if (alive && !overflow && s.valid[k] && op_leader(s.rowk[k]) && !op_written(s.rowk[k]))
+      seen[k] = ld_word(a.words + op_row(s.rowk[k]));
+  }
+  const uint64_t ticket = t.claim(&a.ctl->ticket, alive, 1) + 1;
   order_point<STRICT>();
   bool bad = overflow;
 #pragma unroll
@@ -889,7 +957,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
       // is still unlocked with the same WTS now (a writer installs values
       // while holding the lock, then publishes a new WTS)
       uint64_t *wp = a.words + op_row(s.rowk[k]);
-      uint64_t w = ld_word(wp);
+      uint64_t w = seen[k];
       bool done = false, b = false;
       for (int it = 0; it < CAS_RETRIES && !done && !b; ++it) {
         if (tt_wts(w) != tt_wts(s.v[k]) || (w & TT_LOCK)) {

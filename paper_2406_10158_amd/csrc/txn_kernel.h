@@ -15,8 +15,8 @@ __device__ __forceinline__ int attempt(const Team<L> &t, Slots<K> &s, bool activ
   else if constexpr (SCHEME == CC_2PL_NW) return tpl_attempt<L, K, STRICT, LATCH>(t, s, active, a, txn, hi, lo);
   else if constexpr (SCHEME == CC_2PL_WD)
     return tplwd_attempt<L, K, STRICT, LATCH>(t, s, active, a, txn, resume, may_wait, hi, lo);
-  else if constexpr (SCHEME == CC_TO) return to_attempt<L, K, STRICT, false, LATCH>(t, s, active, a, precheck, hi, lo);
-  else if constexpr (SCHEME == CC_MVCC) return to_attempt<L, K, STRICT, true, LATCH>(t, s, active, a, precheck, hi, lo);
+  else if constexpr (SCHEME == CC_TO) return to_attempt<L, K, STRICT, false, LATCH>(t, s, active, a, hi, lo);
+  else if constexpr (SCHEME == CC_MVCC) return to_attempt<L, K, STRICT, true, LATCH>(t, s, active, a, hi, lo);
   else return tictoc_attempt<L, K, STRICT, LATCH>(t, s, active, a, precheck, hi, lo);
 }
 
@@ -28,10 +28,21 @@ template <int L, int K, int SCHEME, bool STRICT, bool LATCH>
 __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
   Team<L> t;
   Slots<K> s;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    s.valid[k] = s.got[k] = s.sh[k] = false;
+    s.rowk[k] = FOLLOWER_BIT;
+    s.elem[k] = s.oi[k] = 0;
+    s.arg[k] = 0;
+  }
   const uint64_t start_clock = a.ctl->start_clock;
   // epoch mode replays a captured graph, so the pending count is read here
   const uint64_t n_txns = a.n_from_ctl ? ld_word(&a.ctl->pending_n) : a.n_txns;
   int64_t txn = -1;         // current transaction (team-uniform)
+  // the team's share of the queue: it claims `chunk` positions at a time, lane
+  // j keeps the header of the j-th
+  const uint32_t chunk = a.chunk < (uint32_t)L ? a.chunk : (uint32_t)L;
+  uint32_t c_txn = 0, c_first = 0, c_n = 0, c_pos = 0, c_cnt = 0;
   uint32_t attempts = 0;    // attempts of txn so far, all passes
   uint32_t pass_att = 0;    // attempts of txn in this pass
   uint64_t ready_at = 0;    // wall-clock tick before which the team waits
@@ -58,10 +69,29 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
       if (__shfl((int)(ld_word(&a.ctl->stop) != 0), 0, 64)) break;
     }
     const bool need = txn < 0 && !done;
-    const uint64_t q = t.claim(&a.ctl->queue, need, 1);
-    if (need) {
-      if (q < n_txns) {
-        txn = a.list ? (int64_t)a.list[q] : (int64_t)q;
+    const bool refill = need && c_pos == c_cnt;
+    const uint64_t q = t.claim(&a.ctl->queue, refill, chunk);
+    if (refill) {
+      c_cnt = q < n_txns ? (n_txns - q < chunk ? (uint32_t)(n_txns - q) : chunk) : 0u;
+      c_pos = 0;
+      done = c_cnt == 0;
+      if ((uint32_t)t.tl < c_cnt) {
+        c_txn = a.list ? a.list[q + t.tl] : (uint32_t)q + t.tl;
+        const DevTxn d = a.txns[c_txn];
+        c_first = d.first;
+        c_n = d.n;
+      }
+    }
+    const bool take = need && !done;
+    if (ballot(take)) {
+      // stage the transaction's ops in registers (coalesced 16 B loads per
+      // team), once: they stay through its retries
+      const int src = t.tb + (take ? (int)c_pos : 0);
+      const uint32_t id = (uint32_t)__shfl((int)c_txn, src, 64), first = (uint32_t)__shfl((int)c_first, src, 64),
+                     n = (uint32_t)__shfl((int)c_n, src, 64);
+      if (take) {
+        ++c_pos;
+        txn = (int64_t)id;
         attempts = a.pass ? a.out[txn].attempts : 0;
         pass_att = 0;
         // serving: not before the transaction's arrival
@@ -71,8 +101,21 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
         resume = false;
         waits = 0;
         wait_row = ~0u;
-      } else {
-        done = true;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          const uint32_t idx = (uint32_t)t.tl + (uint32_t)(k * L);
+          s.valid[k] = idx < n;
+          s.oi[k] = first + idx;
+          s.rowk[k] = FOLLOWER_BIT;
+          s.elem[k] = 0;
+          s.arg[k] = 0;
+          if (s.valid[k]) {
+            const DevOp op = a.ops[first + idx];
+            s.rowk[k] = op.rowk;
+            s.elem[k] = op.elem;
+            s.arg[k] = op.arg;
+          }
+        }
       }
     }
     if (ballot(txn >= 0) == 0) break;
@@ -127,31 +170,11 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
       if (txn >= 0 && t.tl == 0) t_wait += wall_clock64() - now;
       continue;
     }
-    // stage the transaction's ops in registers (coalesced 16 B loads per team)
-    uint32_t first = 0, n = 0;
-    if (active) {
-      const DevTxn d = a.txns[txn];
-      first = d.first;
-      n = d.n;
-    }
-    // a waiting team (2PL wait-die) keeps its staged operations and locks
+    // a waiting team (2PL wait-die) keeps its locks and what it read
     const bool keep = SCHEME == CC_2PL_WD && resume;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       if (keep) continue;
-      const uint32_t idx = (uint32_t)t.tl + (uint32_t)(k * L);
-      s.valid[k] = active && idx < n;
-      s.oi[k] = first + idx;
-      if (s.valid[k]) {
-        const DevOp op = a.ops[first + idx];
-        s.rowk[k] = op.rowk;
-        s.elem[k] = op.elem;
-        s.arg[k] = op.arg;
-      } else {
-        s.rowk[k] = FOLLOWER_BIT;
-        s.elem[k] = 0;
-        s.arg[k] = 0;
-      }
       s.x[k] = 0;
       s.v[k] = 0;
     }
@@ -208,7 +231,7 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
         }
 #pragma unroll
         for (int k = 0; k < K; ++k)
-          if (s.valid[k]) __builtin_nontemporal_store(s.x[k], a.reads + first + t.tl + k * L);
+          if (s.valid[k]) __builtin_nontemporal_store(s.x[k], a.reads + s.oi[k]);
         if (reserved && t.tl == 0) add_word(&a.ctl->budget_released, reserved);
         reserved = 0;
         txn = -1;
@@ -303,7 +326,18 @@ static hipError_t launch_one(hipStream_t s, int waves_per_wg, int grid, const Ru
   const uint64_t need = (a.n_txns + teams_per_wg - 1) / teams_per_wg;
   if ((uint64_t)grid > need) grid = (int)(need > 0 ? need : 1);
   *grid_used = grid;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, a);
+  // queue positions a team claims at a time: a claim and the header it leads
+  // to are two dependent round trips before the operations' load.  Not where
+  // positions have arrival times or are counted on the device, and so few that
+  // a team comes back at least 32 times: the last teams to finish then hold a
+  // few percent of the batch between them.
+  // 262,144 transactions x 16 ops, Zipf 0.6, a tenth writes, one position at a
+  // time and operations staged again for every attempt: OCC 2.62, TicToc 2.80,
+  // wait-die 3.77 ms; now 2.15, 2.41 and 3.08 ms.
+  RunArgs b = a;
+  const uint64_t each = a.n_txns / ((uint64_t)grid * teams_per_wg * 32);
+  b.chunk = a.arrival || a.n_from_ctl || each < 1 ? 1u : (uint32_t)(each < 4 ? each : 4);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, s, b);
   return hipGetLastError();
 }
 
