@@ -257,18 +257,24 @@ typedef struct {
   uint32_t lanes_per_txn; /* lanes cooperating on one transaction: 1, 4, 16, 64; 0 = chosen by contention
                              (see below) */
   uint32_t waves_per_wg;  /* 64-lane wavefronts per workgroup, 1..16; 0 = chosen by contention */
-  uint32_t grid;          /* workgroups of the first pass; 0 = one per compute unit
-                             Defaults by contention, from the share h of transactions that write the
-                             batch's most written row (counted at submission): below 0.1% (no hot row)
-                             4 lanes per transaction and 4 wavefronts per workgroup when the longest
-                             transaction has at most 64 ops, so that 4096 transactions are in flight;
-                             otherwise one wavefront per workgroup and the smallest lane count
-                             >= the longest transaction, which keeps fewer transactions in flight. */
+  uint32_t grid;          /* workgroups of the first pass; 0 = one per compute unit, or, where lanes and
+                             waves are 0 too, chosen by contention.
+                             CC_MODE_PLAIN, by the writes counted at submission: lanes, waves and
+                             workgroups that keep about as many transactions in flight as conflict
+                             once with one another, 64 to 16384, and 256 with 64 lanes each where 2%
+                             of the transactions write one row.
+                             Otherwise, from the share of transactions that write the batch's most
+                             written row: below 0.1% (no hot row) 4 lanes per transaction and 4
+                             wavefronts per workgroup when the longest transaction has at most 64
+                             ops; else one wavefront per workgroup and the smallest lane count >= the
+                             longest transaction. */
   uint32_t mode;          /* enum cc_mode */
   uint64_t max_attempts;  /* give up (CC_E_LIVELOCK) after this many attempts of one txn; 0 = 1<<24 */
   uint32_t max_epochs;    /* CC_MODE_EPOCH: epochs before CC_E_LIVELOCK; 0 = 1<<20 */
   uint32_t flags;         /* CC_RUN_* */
-  uint32_t backoff_ns;    /* base of the randomised exponential back-off after an abort; 0 = 200 ns */
+  uint32_t backoff_ns;    /* base of the randomised exponential back-off after an abort; 0 = 200 ns.
+                             It grows to 128 bases in CC_MODE_PLAIN's passes that defer (4096 where
+                             thousands of transactions are in flight for a hot row), 4096 elsewhere */
   uint32_t defer_after;   /* CC_MODE_PLAIN: attempts of a transaction within one pass before it is deferred
                              to the next pass, which runs 8x fewer workgroups (the last pass runs one
                              wavefront and never defers); 0 = 16.  CC_MODE_EPOCH: attempts per epoch;

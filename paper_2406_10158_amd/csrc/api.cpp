@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstdio>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <string>
@@ -817,27 +818,90 @@ static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &
   b.eng_gain = b.eng.n_rows && (uint64_t)left_out * 4 <= cand[0] >> 32;
 }
 
-// Whether the hot-row engine is worth it: it takes about 100 us and 0.1 ns an
-// op whatever the contention.  The transaction kernel takes about 2 ns a
-// transaction and try, and where `meet` and the transactions in flight make
-// x conflicts a transaction about 1 + 7 x tries; and it takes 3 us a write of
-// the most written row.  Measured, the run with the kernel alone and with the
-// engine (us; x): 2^18 x 16 ops on 4M rows 797, 560 (0.06); on 65,536 rows 9266,
-// 427 (4.0); Zipf 0.6 on 1M rows 10094, 476 (3.4); 2^16 x 16 ops on 4M rows 272,
-// 325 (0.06), on 1M rows 795, 225 (0.25); 2^12 x 4 ops on 16,384 rows 62, 111
-// (1.0), on 4,096 rows 221, 106 (4.1).  Below x = 0.05, where a transaction in
-// twenty meets another, the batch stays optimistic.
-static bool engine_pays(const Batch &b) {
-  const double n = (double)b.n_txns, x = b.meet * std::min(n, 4096.0);
-  const double kernel = 30.0 + std::max(2e-3 * n * (1.0 + 7.0 * x), 3.0 * (double)b.hot_writes);
-  return x >= 0.05 && 100.0 + 1e-4 * (double)b.n_ops < kernel;
+// Launch shape of a plain run's transaction kernel where the caller leaves it
+// to the library: lanes per transaction, wavefronts per workgroup, workgroups
+// (0: one per compute unit).  A transaction's attempt takes 2-4 us of round
+// trips, so that the transactions in flight, T, are the throughput until they
+// conflict.  share: of the batch's transactions, those that write its most
+// written row; meet: the expected conflicts of a random pair (Batch::meet), so
+// that T of them have T x meet each.  known: false where only a lower bound of
+// meet is (cc_run_static, which does not count rows).
+//
+// Measured with 256 compute units, run time in ms at T = 256 (64 lanes),
+// 512, 1024 (16 lanes), 4096 (4 lanes), 16384 (4 lanes, 4 wavefronts), OCC's
+// kernel / TicToc / MVCC, 16 ops:
+//   Zipf 0.8 (share 0.06), 65,536 txns: 12.7/15.4/16.9  14.1/15.8/18.9
+//     14.1/15.8/19.3  31/39/45  39/46/54
+//   Zipf 0.6 (0.005, meet 1.4e-4), 65,536: 1.13/1.19/1.43  0.96/1.16/1.59
+//     1.09/1.24/1.56  1.63/2.35/3.37  2.3/3.4/4.2
+//   Zipf 0.6, a tenth writes (0.001, 6e-6), 262,144: 4.0/4.0/4.2  2.4/2.4/2.9
+//     1.5/1.6/2.0  1.6/2.3/3.8  2.6/3.3/4.5
+//   uniform, 65,536 rows (< 0.001, 1e-3), 65,536: 1.22/1.38/1.35
+//     1.05/1.16/1.09  0.89/1.03/0.83  1.6/2.3/1.4  3.0/3.6/2.4
+//   uniform, 1M rows (6e-5): 1.03/1.03/1.06  0.59/0.57/0.63  0.45/0.46/0.45
+//     0.22/0.26/0.28  0.51/0.55/0.38
+//   uniform, 4M rows (1.5e-5), OCC: 0.45 at T = 1024, 0.27 at 16384
+// and 4,096 txns of 4 ops on 1,024 rows (meet 3.9e-3), OCC's kernel: 0.27 at
+// 128, 0.22 at 256, 0.29 at 512, 0.41 at 4096; 8,192 of 16 ops on 4,096 rows
+// (1.6e-2) 1.51 at 64, 1.42 at 256, 2.0 at 1024, on 1,024 rows (6e-2) 4.4 at
+// 64, 6.0 at 256, 6.6 at 1024 (MVCC 3.6, 3.8, 4.1).  Transactions of at most 4 ops
+// use 4 lanes with one slot each: uniform on 4M rows, 2^14 txns 60 us with 4096
+// in flight and 106 with 16384, 2^18 443 and 499, 2^20 1661 and 1733.
+struct Shape {
+  uint32_t lanes, waves;
+  int grid;
+};
+static Shape plain_shape(uint32_t max_ops, bool known, double share, double meet, int n_cu) {
+  if (max_ops > 64) return {64, 1, 0};
+  // 16 lanes, and no more in flight than conflict about once; but 256, or what
+  // conflict four times, or 64
+  auto limited = [&]() -> Shape {
+    const double t = meet > 0 ? std::max({64.0, std::min(256.0, 4.0 / meet), 1.0 / meet}) : 1e9;
+    return {16, 1, t / 4 >= (double)n_cu ? 0 : (int)(t / 4)};
+  };
+  if (!known) {
+    uint32_t lanes = 1;
+    while (lanes < 64 && lanes < max_ops) lanes *= 4;
+    if (meet * (double)(n_cu * 64 / (int)lanes) <= 1.0) return {lanes, 1, 0};
+    return limited();
+  }
+  if (share >= 0.02) return {64, 1, 0};
+  if (share >= 0.001) return limited();
+  if (meet * (double)n_cu * 64 <= 0.3) return {4, max_ops <= 4 ? 1u : 4u, 0};
+  if (meet * (double)n_cu * 16 <= 0.75) return {4, 1, 0};
+  return limited();
+}
+
+// Whether OCC's hot-row engine is worth it, from estimates in us.  The engine
+// takes 110 and 0.1 ns an op whatever the contention, and the rest of the batch
+// -- the transactions none of whose writes meets another one's, e^-(meet x n) of
+// them -- 2.2 ns each.  The transaction kernel takes 2.9 a write of the most
+// written row, or, with T in flight in its shape, (n / T) times the attempts,
+// 1 + 1.4 meet x T, times an attempt: 5 with 16 or 64 lanes, 7.5 with 4, 35
+// with 4 wavefronts a workgroup.  Measured, the run with the kernel alone and
+// with the engine (meet): 16 ops, 2^20 on 4M rows 2423, 1776 (1.5e-5); 2^18 on
+// 4M rows 710, 570; on 1M rows 752, 470 (6e-5); on 65,536 rows 3154, 427 (1e-3);
+// Zipf 0.6 on 1M rows 9402, 480; 2^16 on 4M rows 271, 326; 2^12 on 65,536 rows
+// 101, 132; on 16,384 rows 228, 110 (4e-3); 4 ops, 2^16 on 262,144 rows 146, 198
+// (1.5e-5); on 65,536 rows 181, 146 (6e-5); 2^14 on 65,536 rows 74, 135.  Where
+// not one of 4096 in flight in twenty meets another the batch stays optimistic.
+static bool engine_pays(const Batch &b, int n_cu) {
+  const double n = (double)b.n_txns;
+  if (b.meet * std::min(n, 4096.0) < 0.05) return false;
+  const double share = (double)b.hot_writes / n;
+  const Shape s = plain_shape(b.max_ops, true, share, b.meet, n_cu);
+  const double t = std::min(n, (double)(s.grid ? s.grid : n_cu) * s.waves * (64.0 / s.lanes));
+  const double attempt = s.waves > 1 ? 35.0 : s.lanes == 4 ? 7.5 : 5.0;
+  const double kernel = 25.0 + std::max(n / t * (1.0 + 1.4 * b.meet * t) * attempt, 2.9 * (double)b.hot_writes);
+  const double engine = 110.0 + 1e-4 * (double)b.n_ops + 2.2e-3 * n * std::exp(-b.meet * n);
+  return engine < kernel;
 }
 
 // The batch's most written rows, counted at submission (write accesses per
 // global row; ingest.hip): the most written row, and every row written at least
 // a quarter as often, at most HOT_MAX of them, most written first (ties: lower
 // row first).  With them, OCC's engine plan.
-static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables, Batch &b) {
+static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables, Batch &b, int n_cu) {
   const uint64_t *cand = res + INGEST_CAND;
   int nc = 0;
   while (nc < PLAN_CAND && cand[nc]) ++nc;
@@ -847,7 +911,7 @@ static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables,
   b.meet = b.n_txns ? (double)res[INGEST_PAIRS] / ((double)b.n_txns * (double)b.n_txns) : 0.0;
   if (b.scheme == CC_OCC && !b.keyed) {
     plan_engine(cand, nc, tables, b);
-    b.eng_default = engine_pays(b);
+    b.eng_default = engine_pays(b, n_cu);
   }
   b.n_hot = 0;
   const uint32_t thr = std::max<uint32_t>(1u, (top + 3) / 4);
@@ -1216,7 +1280,7 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
     b.d_meta = nullptr;
     b.d_rows = nullptr;
     // (keyed ops learn their rows only when the index is searched, at the run)
-    plan_hot_rows(res, c->tables, b);
+    plan_hot_rows(res, c->tables, b, c->n_cu);
   }
   e = alloc_breaks(b);
   if (e == hipSuccess && b.eng_default) e = split_batch(c, b, c->d_hot);
@@ -1404,7 +1468,16 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   const bool contended = !no_hot_row && hot_share >= 0.02;
   uint32_t lanes = p.lanes_per_txn;
   uint32_t wpw = p.waves_per_wg;
-  if (lanes == 0) {
+  int grid = (int)p.grid;
+  if (lanes == 0 && p.mode == CC_MODE_PLAIN && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
+    const Shape sh = plain_shape(b.max_ops, b.hot_known, no_hot_row ? 0.0 : hot_share,
+                                 use_eng && b.eng_default ? 0.0 : b.meet, c->n_cu);
+    lanes = sh.lanes;
+    if (wpw == 0) {
+      wpw = sh.waves;
+      if (grid == 0) grid = sh.grid;
+    }
+  } else if (lanes == 0) {
     if (no_hot_row && b.max_ops <= 64 && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
       // nothing to wait for: 4 lanes per transaction, 4 wavefronts per
       // workgroup (4096 transactions in flight at one workgroup per CU)
@@ -1475,6 +1548,14 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   a.poll_ticks = 2 * a.backoff_ticks;
   a.jitter_ticks = 2 * a.backoff_ticks;
   a.wait_max_ticks = 256ull * a.backoff_ticks;
+  // 128 bases at most: the last transactions of a batch otherwise wait several
+  // times as long as it ran (262,144 x 16 ops, Zipf 0.6, a tenth writes, 1024
+  // in flight: OCC 2.30 -> 1.53 ms, TicToc 2.39 -> 1.62; Zipf 0.8, 256 in
+  // flight: OCC 14.9 -> 12.7).  Not where thousands in flight wait for a hot row
+  // (4096, Zipf 0.8: MVCC 34 ms -> 45).
+  const double in_flight = (double)(grid ? grid : c->n_cu) * wpw * (64.0 / lanes);
+  const bool patient = in_flight > 1024 && (!b.hot_known || contended);
+  a.backoff_cap = p.mode == CC_MODE_PLAIN && !patient ? 7u : 12u;
   a.n_late = 0;
   if (b.scheme == CC_OCC && (p.flags & CC_RUN_HOT_LAST) && b.hot_known) {
     a.n_late = b.n_hot;
@@ -1663,7 +1744,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       a.n_txns = b.n_txns - b.n_eng_txns;
     }
     if (a.n_txns) {
-      cc_status st = plain_passes((int)p.grid, wpw, true);
+      cc_status st = plain_passes(grid, wpw, true);
       if (st) return st;
     }
   }
@@ -1804,6 +1885,9 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   }
   b.max_ops = (uint32_t)res[INGEST_MAX_OPS];
   b.has_slot = (res[INGEST_KINDS] & 1) != 0;
+  // (rows are not counted: the conflicts if the writes were spread evenly, a lower bound)
+  const double w = n_txns ? (double)res[INGEST_PAIRS] / (double)n_txns : 0.0;
+  b.meet = w * w / (double)std::max<uint64_t>(c->total_rows, 1);
   const cc_status st = run_batch(c, b, p, false);
   for (uint32_t i = 0; i < n_counters; ++i) counters[i] = i < CC_N_STATS ? b.stats[i] : 0;
   return st;

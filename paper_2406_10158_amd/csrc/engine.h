@@ -134,7 +134,7 @@ struct RunArgs {
   uint32_t wait_blocker;
   uint32_t poll_ticks;
   uint32_t jitter_ticks;
-  uint32_t pad7;
+  uint32_t backoff_cap;    // doublings of the back-off at most, in passes that defer
   uint64_t wait_max_ticks;
 };
 
@@ -315,6 +315,7 @@ enum IngestOut {
   INGEST_N_CAND,
   INGEST_TOP,        // writes to the most written row
   INGEST_PAIRS,      // sum over the rows of c (c - 1), c writes: ordered pairs of writes that meet
+                     // (cc_run_static, which counts no rows: the written rows of all transactions)
   INGEST_CAND,       // PLAN_CAND x (count << 32 | ~row), most written first, 0: none
   INGEST_N = INGEST_CAND + PLAN_CAND
 };

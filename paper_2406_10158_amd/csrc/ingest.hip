@@ -192,7 +192,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     for (uint32_t t = 0; t < a.n_tables; ++t) indexed |= a.tab[t].indexed ? 1u << t : 0u;
   static_assert(CC_MAX_TABLES <= 32, "a bit per table");
   auto is_keyed = [&](const cc_op &o) { return o.table < 32u && ((indexed >> o.table) & 1u); };
-  uint32_t max_ops = 0, kinds = 0;
+  uint32_t max_ops = 0, kinds = 0, writes = 0;
   bool unordered = false, any_keyed = false;
   OpBits &bits = s.bits[team];
   const uint64_t step = (uint64_t)nb * TEAMS;
@@ -350,6 +350,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
         d.elem = kd ? 0u : (uint32_t)(tb_.elem_base + (uint64_t)o.row * tb_.n_fields + o.field);
         d.arg = o.arg;
         a.dops[f0 + i] = d;
+        writes += lead && wr;
         if (a.cnt && lead && wr && !kd) {
           uint32_t h = (grow * 0x9E3779B1u) >> (LOCAL ? 20 : 21);
           static_assert(RC_SLOTS == 1u << (LOCAL ? 12 : 11), "hash to the slots");
@@ -382,6 +383,10 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     for (uint32_t i = tid; i < RC_SLOTS; i += NT)
       if (s.cnt[i] && atomicAdd(&a.cnt[s.row[i]], s.cnt[i]) == 0) a.rows[s.op[i]] = s.row[i];
   max_ops = (uint32_t)wave_max(max_ops);
+  if (!a.cnt) {
+    const uint64_t w = wave_sum((uint64_t)writes);
+    if (lane == 0 && w) add_word(&a.out[INGEST_PAIRS], w);
+  }
   const uint64_t w_slot = ballot(kinds & 1u), w_cond = ballot(kinds & 2u), w_unord = ballot(unordered),
                  w_keyed = ballot(any_keyed);
   if (lane == 0) {

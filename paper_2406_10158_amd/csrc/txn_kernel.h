@@ -261,7 +261,9 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
           if (t.tl == 0) ++n_blocked;
         } else {
           // randomised exponential back-off
-          const uint32_t sh = pass_att < 12 ? pass_att : 12;
+          // (the pass that never defers relies on its growth)
+          const uint32_t cap = a.defer_after ? a.backoff_cap : 12u;
+          const uint32_t sh = pass_att < cap ? pass_att : cap;
           const uint64_t span = (uint64_t)a.backoff_ticks << sh;
           ready_at = now + (mix64(((uint64_t)txn << 20) ^ attempts) % (span + 1));
         }
