@@ -58,6 +58,10 @@ struct Batch {
   // nobody counted (cc_run_static), which then runs with the contended defaults
   bool hot_known = false;
   uint64_t hot_writes = 0;
+  // what the launch shape goes by: writes of the most written row, and whether
+  // they are known (of a keyed batch from its first plain run on)
+  bool shape_known = false;
+  uint64_t shape_writes = 0;
   double meet = 0;  // expected writes of one transaction to rows another one writes, for a random pair
   uint32_t n_hot = 0;
   uint32_t hot_rows[HOT_MAX] = {};
@@ -172,6 +176,9 @@ cc_status freeze(cc_ctx *c) {
   return CC_OK;
 }
 
+static hipError_t need_sub(cc_ctx *c, size_t bytes);
+static void trim_sub(cc_ctx *c);
+
 cc_status launch_error(cc_ctx *c, hipError_t e) {
   if (e == hipErrorInvalidValue) return fail(c, CC_E_INVAL, "scheme or (lanes_per_txn, ops per txn) not supported");
   if (e == hipErrorInvalidConfiguration)
@@ -191,6 +198,24 @@ cc_status resolve_keys(cc_ctx *c, Batch &b, const cc_run_params &p, float *ms) {
   HIP_OR(c, hipStreamSynchronize(c->stream));
   HIP_OR(c, hipEventElapsedTime(ms, c->ev[6], c->ev[7]));
   if (miss) return fail(c, CC_E_RANGE, std::to_string(miss) + " keys name no row of their table's index");
+  return CC_OK;
+}
+
+// Counts the writes of a keyed batch's rows, which its first lookup found, for
+// the launch shape.  The counts per row are the submissions' (0 in between).
+cc_status count_keyed(cc_ctx *c, Batch &b) {
+  if (!c->d_cnt || need_sub(c, b.n_ops * sizeof(uint32_t)) != hipSuccess) {
+    (void)hipGetLastError();
+    return CC_OK;  // the shape for unknown rows will do
+  }
+  uint64_t res[2] = {};
+  HIP_OR(c, launch_count_writes(c->stream, b.d_ops, b.n_ops, c->d_cnt, (uint32_t *)c->d_sub, c->d_ingest, c->n_cu));
+  HIP_OR(c, hipMemcpyAsync(res, c->d_ingest, sizeof res, hipMemcpyDeviceToHost, c->stream));
+  HIP_OR(c, hipStreamSynchronize(c->stream));
+  trim_sub(c);
+  b.shape_known = true;
+  b.shape_writes = res[0];
+  b.meet = (double)res[1] / ((double)b.n_txns * (double)b.n_txns);
   return CC_OK;
 }
 
@@ -908,6 +933,8 @@ static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables,
   const uint32_t top = (uint32_t)res[INGEST_TOP];
   b.hot_known = true;
   b.hot_writes = top;
+  b.shape_known = true;
+  b.shape_writes = top;
   b.meet = b.n_txns ? (double)res[INGEST_PAIRS] / ((double)b.n_txns * (double)b.n_txns) : 0.0;
   if (b.scheme == CC_OCC && !b.keyed) {
     plan_engine(cand, nc, tables, b);
@@ -1453,7 +1480,8 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
     return fail(c, CC_E_STATE, "CC_MODE_SERVE needs cc_set_arrivals first");
   // contention of the batch: the share of transactions that write its most
   // written row (unknown: treated as contended)
-  const double hot_share = b.hot_known && b.n_txns ? (double)b.hot_writes / (double)b.n_txns : 1.0;
+  double hot_share = 1.0;
+  bool no_hot_row = false, contended = true;
   // OCC's hot-row engine (plain mode only: it knows no arrivals).  It has the
   // scope of the launch shapes of at most 4 ops per lane (64 lanes unless the
   // caller chose)
@@ -1463,32 +1491,38 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
                        b.n_txns &&
                        ((p.flags & CC_RUN_HOT_ENGINE) ? b.eng.n_rows || b.eng_default
                                                       : !(p.flags & CC_RUN_NO_HOT_ENGINE) && b.eng_default);
-  // (after the engine by the hot-row map nothing is left to conflict)
-  const bool no_hot_row = hot_share < 0.001 || (use_eng && b.eng_default);
-  const bool contended = !no_hot_row && hot_share >= 0.02;
-  uint32_t lanes = p.lanes_per_txn;
-  uint32_t wpw = p.waves_per_wg;
-  int grid = (int)p.grid;
-  if (lanes == 0 && p.mode == CC_MODE_PLAIN && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
-    const Shape sh = plain_shape(b.max_ops, b.hot_known, no_hot_row ? 0.0 : hot_share,
-                                 use_eng && b.eng_default ? 0.0 : b.meet, c->n_cu);
-    lanes = sh.lanes;
-    if (wpw == 0) {
-      wpw = sh.waves;
-      if (grid == 0) grid = sh.grid;
+  uint32_t lanes = 0, wpw = 0;
+  int grid = 0;
+  auto choose_shape = [&]() {
+    hot_share = b.shape_known && b.n_txns ? (double)b.shape_writes / (double)b.n_txns : 1.0;
+    // (after the engine by the hot-row map nothing is left to conflict)
+    no_hot_row = hot_share < 0.001 || (use_eng && b.eng_default);
+    contended = !no_hot_row && hot_share >= 0.02;
+    lanes = p.lanes_per_txn;
+    wpw = p.waves_per_wg;
+    grid = (int)p.grid;
+    if (lanes == 0 && p.mode == CC_MODE_PLAIN && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
+      const Shape sh = plain_shape(b.max_ops, b.shape_known, no_hot_row ? 0.0 : hot_share,
+                                   use_eng && b.eng_default ? 0.0 : b.meet, c->n_cu);
+      lanes = sh.lanes;
+      if (wpw == 0) {
+        wpw = sh.waves;
+        if (grid == 0) grid = sh.grid;
+      }
+    } else if (lanes == 0) {
+      if (no_hot_row && b.max_ops <= 64 && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
+        // nothing to wait for: 4 lanes per transaction, 4 wavefronts per
+        // workgroup (4096 transactions in flight at one workgroup per CU)
+        lanes = 4;
+        if (wpw == 0) wpw = 4;
+      } else {
+        lanes = 1;
+        while (lanes < 64 && lanes < b.max_ops) lanes *= 4;
+      }
     }
-  } else if (lanes == 0) {
-    if (no_hot_row && b.max_ops <= 64 && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
-      // nothing to wait for: 4 lanes per transaction, 4 wavefronts per
-      // workgroup (4096 transactions in flight at one workgroup per CU)
-      lanes = 4;
-      if (wpw == 0) wpw = 4;
-    } else {
-      lanes = 1;
-      while (lanes < 64 && lanes < b.max_ops) lanes *= 4;
-    }
-  }
-  if (wpw == 0) wpw = 1;
+    if (wpw == 0) wpw = 1;
+  };
+  choose_shape();
   if ((p.flags & CC_RUN_HOT_ENGINE) && !eng_fits)
     return fail(c, CC_E_INVAL, "CC_RUN_HOT_ENGINE needs at most 4 ops per lane");
   if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
@@ -1542,7 +1576,6 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   a.ns_per_tick_q16 = (uint32_t)((1000000ull << 16) / c->wallclock_khz);
   a.has_slot = b.has_slot ? 1u : 0u;
   a.eager_install = (p.flags & CC_RUN_EAGER_INSTALL) ? 1u : 0u;
-  a.precheck = (p.flags & CC_RUN_PRECHECK) ? 2u : ((p.flags & CC_RUN_NO_PRECHECK) ? 0u : (contended ? 1u : 0u));
   a.hot0 = b.n_hot ? b.hot_rows[0] : ~0u;
   a.wait_blocker = (p.flags & CC_RUN_WAIT_BLOCKER) ? 1u : 0u;
   a.poll_ticks = 2 * a.backoff_ticks;
@@ -1553,9 +1586,13 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   // in flight: OCC 2.30 -> 1.53 ms, TicToc 2.39 -> 1.62; Zipf 0.8, 256 in
   // flight: OCC 14.9 -> 12.7).  Not where thousands in flight wait for a hot row
   // (4096, Zipf 0.8: MVCC 34 ms -> 45).
-  const double in_flight = (double)(grid ? grid : c->n_cu) * wpw * (64.0 / lanes);
-  const bool patient = in_flight > 1024 && (!b.hot_known || contended);
-  a.backoff_cap = p.mode == CC_MODE_PLAIN && !patient ? 7u : 12u;
+  auto choose_retries = [&]() {
+    a.precheck = (p.flags & CC_RUN_PRECHECK) ? 2u : ((p.flags & CC_RUN_NO_PRECHECK) ? 0u : (contended ? 1u : 0u));
+    const double in_flight = (double)(grid ? grid : c->n_cu) * wpw * (64.0 / lanes);
+    const bool patient = in_flight > 1024 && (!b.shape_known || contended);
+    a.backoff_cap = p.mode == CC_MODE_PLAIN && !patient ? 7u : 12u;
+  };
+  choose_retries();
   a.n_late = 0;
   if (b.scheme == CC_OCC && (p.flags & CC_RUN_HOT_LAST) && b.hot_known) {
     a.n_late = b.n_hot;
@@ -1592,6 +1629,15 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   if (b.keyed) {
     cc_status st = resolve_keys(c, b, p, &ms_index);
     if (st) return st;
+    // the rows are known now: counted once a batch, which pays where not all of
+    // it is in flight at once (262,144 x 16 ops on 1M rows: 0.1 ms, and the
+    // kernel's 1.48 ms become 0.75)
+    if (!b.shape_known && p.mode == CC_MODE_PLAIN && p.lanes_per_txn == 0 && b.n_txns > 4096) {
+      st = count_keyed(c, b);
+      if (st) return st;
+      choose_shape();
+      choose_retries();
+    }
   }
   Ctl h{};
   const RunTail *tail = (const RunTail *)c->h_pin;

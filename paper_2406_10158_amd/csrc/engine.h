@@ -359,6 +359,12 @@ struct IngestArgs {
 // Resets out, then validates and packs; the host reads `out` afterwards.
 hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu);
 
+// Counts a batch's writes per global row from its descriptors: out[0] = the most
+// written row's, out[1] = sum of c (c - 1) over the rows.  cnt: a count per
+// global row, 0 before and after; rows: n_ops scratch words.
+hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
+                               uint64_t *out, int n_cu);
+
 // The transactions that write one of the engine's rows -- those of `map` (a bit
 // per global row), or e's where map is nullptr -- in batch order: part (n_txns
 // entries; nullptr: only count) lists them and then the others, desc describes

@@ -650,6 +650,61 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
   if (tid == 0) a.out[INGEST_TOP] = ld_word(&a.out[INGEST_CAND]) >> 32;
 }
 
+// The counts of a batch whose rows are known only at the run (keyed): as the
+// pack and count parts above, without the candidates.  262,144 x 16 ops, half
+// writes, uniform: 0.1 ms, once a batch.
+__global__ void __launch_bounds__(256) count_mark_kernel(const DevOp *ops, uint64_t n_ops, uint32_t *cnt,
+                                                         uint32_t *rows, uint64_t *out) {
+  if (blockIdx.x == 0 && threadIdx.x < 2) out[threadIdx.x] = 0;
+  const uint64_t step = (uint64_t)gridDim.x * 256;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_ops; i += step) {
+    const uint32_t rk = ops[i].rowk;
+    uint32_t mark = RC_NONE;
+    if (rk != GAP_OP && op_leader(rk) && op_written(rk) && atomicAdd(&cnt[op_row(rk)], 1u) == 0) mark = op_row(rk);
+    rows[i] = mark;
+  }
+}
+__global__ void __launch_bounds__(256) count_sum_kernel(const uint32_t *rows, uint64_t n_ops, uint32_t *cnt,
+                                                        uint64_t *out) {
+  __shared__ uint32_t s_top;
+  __shared__ unsigned long long s_pairs;
+  if (threadIdx.x == 0) {
+    s_top = 0;
+    s_pairs = 0;
+  }
+  __syncthreads();
+  uint32_t top = 0;
+  uint64_t pairs = 0;
+  const uint64_t step = (uint64_t)gridDim.x * 256;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_ops; i += step) {
+    const uint32_t r = rows[i];
+    if (r == RC_NONE) continue;
+    const uint32_t c = cnt[r];
+    cnt[r] = 0;
+    pairs += (uint64_t)c * (c - 1);
+    top = c > top ? c : top;
+  }
+  top = (uint32_t)wave_max(top);
+  pairs = wave_sum(pairs);
+  if (__lane_id() == 0) {
+    atomicMax(&s_top, top);
+    atomicAdd(&s_pairs, (unsigned long long)pairs);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0 && s_top) {
+    atomicMax((unsigned long long *)&out[0], (unsigned long long)s_top);
+    add_word(&out[1], (uint64_t)s_pairs);
+  }
+}
+hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
+                               uint64_t *out, int n_cu) {
+  const uint64_t most = (uint64_t)n_cu * 8, b = (n_ops + 255) / 256;
+  const dim3 g((unsigned)(b < 1 ? 1 : (b < most ? b : most)));
+  hipLaunchKernelGGL(count_mark_kernel, g, dim3(256), 0, s, ops, n_ops, cnt, rows, out);
+  hipLaunchKernelGGL(count_sum_kernel, g, dim3(256), 0, s, rows, n_ops, cnt, out);
+  return hipGetLastError();
+}
+
 hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu) {
   if (a.n_txns <= (uint64_t)INGEST_LOCAL / 4 && a.n_ops <= (uint64_t)INGEST_LOCAL) {
     hipLaunchKernelGGL(ingest_local_kernel, dim3(1), dim3(1024), 0, s, a);

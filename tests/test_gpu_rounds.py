@@ -9,7 +9,8 @@ counted conflicts, with and without operations a scan cannot see through.
 """
 import pytest
 
-from helpers import binding, run_and_check
+import oracle
+from helpers import binding, check, run_and_check
 from paper_2406_10158_amd import workload as wl
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +45,27 @@ def test_hot_engine_by_counted_conflicts(n, kind_p):
     tabs, b = wl.mixed_workload(n_txns=n, kind_p=kind_p, seed=n)
     st = run_and_check(tabs, b, "occ")[3]
     assert st["engine_txns"] > 0
+
+
+@pytest.mark.parametrize("theta", [0.0, 0.9])
+@pytest.mark.parametrize("n", [4096, 4097, 9000])
+def test_keyed_batch_counted_at_its_first_run(n, theta):
+    # more than 4,096 transactions: the rows the lookup found are counted behind it; the launch shape
+    # then goes by them, and the counts are 0 again for the submission that follows
+    b_ = binding()
+    print(f"[gpu] keyed count n={n} theta={theta}", flush=True)
+    tabs, b = wl.kv_workload(n_rows=5_000, n_fields=2, n_txns=n, ops=4, theta=theta, seed=n)
+    keys = wl.index_keys(5_000, seed=3)
+    op_keys = wl.keyed_ops(b, [keys])
+    rb = oracle.with_rows(b, oracle.resolve_keys([keys], b, op_keys))
+    with b_.Engine(tabs) as eng:
+        eng.create_index(0, keys)
+        bid = eng.submit_keyed(b, op_keys, "to")
+        for _ in range(2):
+            eng.load(tabs)
+            eng.run(bid)
+            out, reads = eng.outcomes(bid, b.n_txns, b.total_ops)
+            rep = check(tabs, rb, out, reads, eng.tables())
+            assert rep.ok, rep
+        st = eng.run(eng.submit(b, "to"))
+    assert st["hot_writes"] == wl.hottest_row_writes(b)[1]
