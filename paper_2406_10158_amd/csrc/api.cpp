@@ -753,6 +753,19 @@ cc_status run_gacco(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
 // another paid a hand-off of a done counter for each: 12.7 of 16.9 ms at 2^18
 // transactions x 16 ops, 10M rows, Zipf 0.6.  Every transaction runs exactly once.
 // (mode and flags were checked by check_run_params)
+// Whether GPUTx's rank pass resolves rows ahead of their turns (gputx.hip): where
+// a transaction waits for one row at a time.  Either few of the thousand or so
+// in flight meet, or the most written row is most of what they meet.  Measured,
+// the pass with and without (ms; 1024 x meet, share of the most written row): 16
+// ops, half writes, Zipf 0.6 on 10M rows 1.74, 4.0 (0.1, 0.005); Zipf 0.7 3.1, 5.4
+// (1, 0.02); Zipf 0.8 7.2, 8.4 (9, 0.06); Zipf 0.9 53, 46 (59, 0.17); uniform on
+// 65,536 rows 1.40, 1.0 (1, < 0.001); 4 ops on 1,024 rows 2.8, 2.1 (4, 0.002).
+static bool gputx_ahead(const Batch &b) {
+  if (!b.shape_known || !b.n_txns) return false;
+  const double x = b.meet * 1024.0, share = (double)b.shape_writes / (double)b.n_txns;
+  return x <= 0.5 || (share >= 0.01 && x <= 10.0);
+}
+
 cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes, uint32_t wpw) {
   if (!c->d_kstate) HIP_OR(c, hipMalloc(&c->d_kstate, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint64_t)));
   const uint64_t n = b.n_txns;
@@ -769,7 +782,7 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   const uint64_t poll_ns = p.backoff_ns ? p.backoff_ns : 200;
   a.poll_ticks = (uint32_t)std::max<uint64_t>(1, poll_ns * c->wallclock_khz / 1000000ull);
   // the rank pass keeps each row's rank state in its turn word when both fit
-  // (rank + 1 in 20 bits, a row's place in its list in 24)
+  // (rank + 1 in 20 bits, a sorted position in 24)
   const bool packed = n < (1ull << 20) && b.n_ops < (1ull << 24);
   a.packed = packed ? 1u : 0u;
   const bool strict = (p.flags & CC_RUN_STRICT_FENCES) != 0;
@@ -783,9 +796,14 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
   }
   HIP_OR(c, hipEventRecord(c->ev[4], c->stream));
   HIP_OR(c, gacco_prepare(c->stream, b.d_ops, b.n_ops, (uint32_t)c->total_rows, c->d_words, b.d_rank, b.d_gscratch,
-                          c->d_ctl, packed ? PREP_LOCAL : PREP_TURNS));
+                          c->d_ctl, packed ? PREP_HIGH : PREP_TURNS));
   int grid_used = 0;
   if (n) {
+    // (the sort's buffers are free again)
+    if (packed && gputx_ahead(b)) {
+      a.known = b.d_gscratch;
+      HIP_OR(c, gputx_init_state(c->stream, (uint64_t *)a.known, (b.n_ops + 1) / 2));
+    }
     if (!packed) HIP_OR(c, gputx_init_state(c->stream, c->d_kstate, c->total_rows));
     hipError_t e = launch_gputx_rank(c->stream, (int)lanes, (int)b.max_ops, (int)wpw, (int)p.grid, strict, a, c->n_cu,
                                      &grid_used);

@@ -28,6 +28,12 @@ __device__ __forceinline__ uint64_t add_word(uint64_t *p, uint64_t v) {
 __device__ __forceinline__ uint64_t xchg_word(uint64_t *p, uint64_t v) {
   return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void max_word(uint64_t *p, uint64_t v) {
+  (void)__hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_u32(uint32_t *p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // compare-and-swap; on failure *expected receives the current value
 __device__ __forceinline__ bool cas_word(uint64_t *p, uint64_t *expected, uint64_t desired) {
   return __hip_atomic_compare_exchange_strong(p, expected, desired, __ATOMIC_RELAXED, __ATOMIC_RELAXED,

@@ -216,9 +216,9 @@ hipError_t radix_sort_pairs(hipStream_t s, uint32_t *keys, uint32_t *vals, uint6
 //               leader's rank is its threshold: accesses before it in its row
 //               for a write, writes before it for a read (reads between two
 //               writes share the row);
-//  PREP_LOCAL   every accessed row's word is 0 and a leader's rank is its
-//               place in its row's list (GPUTx's packed rank state).
-enum PrepMode { PREP_TURNS = 0, PREP_SHARED = 1, PREP_LOCAL = 2 };
+//  PREP_HIGH    as PREP_TURNS, in the word's bits from PREP_HIGH_SHIFT on
+constexpr int PREP_HIGH_SHIFT = 40;
+enum PrepMode { PREP_TURNS = 0, PREP_SHARED = 1, PREP_HIGH = 2 };
 hipError_t gacco_prepare(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t sentinel, uint64_t *words,
                          uint32_t *rank, uint32_t *scratch, Ctl *ctl, int mode);
 // GaccO execution; hipErrorInvalidValue for an unsupported (lanes, ops per txn).
@@ -261,7 +261,7 @@ struct GputxArgs {
   const DevOp *ops;
   const DevTxn *txns;
   uint64_t n_txns;
-  const uint32_t *rank;       // per row-group leader: its place in its row's list (the turn it waits for)
+  const uint32_t *rank;       // per row-group leader: its sorted position (the turn it waits for)
   uint64_t *words;            // per row: the turn
   uint64_t *kstate;           // per row: (largest rank + 1 of its accessors so far) << 32 | (last writer's rank + 1)
   uint32_t *txn_rank;         // output: per transaction
@@ -269,6 +269,8 @@ struct GputxArgs {
   uint64_t wait_limit_ticks;
   uint32_t poll_ticks;
   uint32_t packed;            // turn and rank state share the row's word (see gputx.hip)
+  uint32_t *known;            // packed: per sorted position, what is known of the access before its turn, 0 at
+                              // first (nullptr: rows pass from team to team)
 };
 hipError_t launch_gputx_rank(hipStream_t s, int lanes, int max_ops, int waves_per_wg, int grid, bool strict,
                              const GputxArgs &a, int n_cu, int *grid_used);

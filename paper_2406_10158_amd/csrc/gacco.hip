@@ -220,12 +220,13 @@ __global__ void __launch_bounds__(RS_THREADS) rs_scatter_kernel(const uint32_t *
 // lock table: turn counters and per-access ranks
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) gacco_lock_table_kernel(const uint32_t *keys, const uint32_t *vals, uint64_t n,
-                                                               uint32_t sentinel, uint64_t *words, uint32_t *rank) {
+                                                               uint32_t sentinel, uint64_t *words, uint32_t *rank,
+                                                               int shift) {
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const uint32_t k = keys[i], v = vals[i];
   if (k >= sentinel || v >= n) return;  // followers (and nothing else) carry the sentinel
-  if (i == 0 || keys[i - 1] != k) words[k] = i;  // the row's first access owns it
+  if (i == 0 || keys[i - 1] != k) words[k] = i << shift;  // the row's first access owns it
   rank[v] = (uint32_t)i;
 }
 
@@ -260,21 +261,6 @@ __global__ void __launch_bounds__(256) gacco_shared_rank_kernel(const uint32_t *
   const uint64_t start = words[k];
   if (start > i) return;  // not reachable for a consistent table
   rank[v] = op_written(ops[v].rowk) ? (uint32_t)(i - start) : wbefore[i] - wbefore[start];
-}
-
-// Per-row positions (PREP_LOCAL, GPUTx's packed rank state): after the lock
-// table has put each row's first position in its word, every leader's place
-// in its row's list becomes its position minus that start.
-__global__ void __launch_bounds__(256) gacco_local_rank_kernel(const uint32_t *keys, const uint32_t *vals, uint64_t n,
-                                                               uint32_t sentinel, const uint64_t *words,
-                                                               uint32_t *rank) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t k = keys[i], v = vals[i];
-  if (k >= sentinel || v >= n) return;
-  const uint64_t start = words[k];
-  if (start > i) return;  // not reachable for a consistent table
-  rank[v] = (uint32_t)(i - start);
 }
 
 // Third pass: both counters of every accessed row start at zero.
@@ -345,13 +331,7 @@ hipError_t gacco_prepare(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32
   if (e != hipSuccess) return e;
   if (mode != PREP_SHARED) {
     hipLaunchKernelGGL(gacco_lock_table_kernel, dim3(blocks), dim3(256), 0, s, sorted_k, sorted_v, n_ops, sentinel,
-                       words, rank);
-    if (mode == PREP_LOCAL) {
-      // places within each row, and every accessed row's word starts at zero
-      hipLaunchKernelGGL(gacco_local_rank_kernel, dim3(blocks), dim3(256), 0, s, sorted_k, sorted_v, n_ops, sentinel,
-                         words, rank);
-      hipLaunchKernelGGL(gacco_shared_clear_kernel, dim3(blocks), dim3(256), 0, s, sorted_k, n_ops, sentinel, words);
-    }
+                       words, rank, mode == PREP_HIGH ? PREP_HIGH_SHIFT : 0);
     return hipGetLastError();
   }
   // the key/value pair the sort did not end in is free, and so is the histogram
