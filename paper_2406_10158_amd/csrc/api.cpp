@@ -1599,16 +1599,20 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   a.poll_ticks = 2 * a.backoff_ticks;
   a.jitter_ticks = 2 * a.backoff_ticks;
   a.wait_max_ticks = 256ull * a.backoff_ticks;
-  // 128 bases at most: the last transactions of a batch otherwise wait several
+  // 128 bases at most, 256 with a hot row: the last transactions of a batch otherwise wait several
   // times as long as it ran (262,144 x 16 ops, Zipf 0.6, a tenth writes, 1024
   // in flight: OCC 2.30 -> 1.53 ms, TicToc 2.39 -> 1.62; Zipf 0.8, 256 in
-  // flight: OCC 14.9 -> 12.7).  Not where thousands in flight wait for a hot row
-  // (4096, Zipf 0.8: MVCC 34 ms -> 45).
+  // flight: OCC 14.9 -> 12.7).  More where nearly all of a batch meets (16 ops,
+  // 9 of 10 writes, Zipf 0.99 on 154,835 rows: 2PL 46.6 ms at 128, 38.1 at 4096; OCC
+  // 47.5 at 128, 46.8 at 1024, 48.7 at 4096), and where thousands in flight wait
+  // for a hot row (4096, Zipf 0.8: MVCC 45 ms at 128, 34 at 4096).
   auto choose_retries = [&]() {
     a.precheck = (p.flags & CC_RUN_PRECHECK) ? 2u : ((p.flags & CC_RUN_NO_PRECHECK) ? 0u : (contended ? 1u : 0u));
     const double in_flight = (double)(grid ? grid : c->n_cu) * wpw * (64.0 / lanes);
-    const bool patient = in_flight > 1024 && (!b.shape_known || contended);
-    a.backoff_cap = p.mode == CC_MODE_PLAIN && !patient ? 7u : 12u;
+    if (p.mode != CC_MODE_PLAIN || (in_flight > 1024 && (!b.shape_known || contended))) a.backoff_cap = 12;
+    else if (!b.shape_known) a.backoff_cap = in_flight <= 256 ? 7u : 10u;
+    else if (b.meet > 0.1) a.backoff_cap = b.scheme == CC_2PL_NW || b.scheme == CC_2PL_WD ? 12u : 10u;
+    else a.backoff_cap = contended ? 8u : 7u;
   };
   choose_retries();
   a.n_late = 0;
