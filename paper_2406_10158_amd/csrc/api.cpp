@@ -55,7 +55,7 @@ struct Batch {
   uint64_t stats[CC_N_STATS] = {};
   // counted at submission (plan_hot_rows): writes to the most written row,
   // and the most written rows (most first); hot_known is false for a batch
-  // nobody counted (cc_run_static), which then runs with the contended defaults
+  // without a submission by row (cc_run_static, keyed)
   bool hot_known = false;
   uint64_t hot_writes = 0;
   // what the launch shape goes by: writes of the most written row, and whether
@@ -172,6 +172,13 @@ cc_status freeze(cc_ctx *c) {
   }
   c->d_data = data;
   c->d_words = words;
+  // the counts per row, here for cc_run_static, which does not allocate (without
+  // them it uses the shape for unknown rows, and a submission tries again)
+  if (c->d_static && hipMalloc(&c->d_cnt, std::max<uint64_t>(rows, 1) * sizeof(uint32_t)) != hipSuccess) {
+    (void)hipGetLastError();
+    c->d_cnt = nullptr;
+  }
+  if (c->d_cnt) HIP_OR(c, hipMemsetAsync(c->d_cnt, 0, std::max<uint64_t>(rows, 1) * sizeof(uint32_t), c->stream));
   c->frozen = true;
   return CC_OK;
 }
@@ -209,7 +216,8 @@ cc_status count_keyed(cc_ctx *c, Batch &b) {
     return CC_OK;  // the shape for unknown rows will do
   }
   uint64_t res[2] = {};
-  HIP_OR(c, launch_count_writes(c->stream, b.d_ops, b.n_ops, c->d_cnt, (uint32_t *)c->d_sub, c->d_ingest, c->n_cu));
+  HIP_OR(c, launch_count_writes(c->stream, b.d_ops, b.n_ops, c->d_cnt, (uint32_t *)c->d_sub, c->d_ingest, nullptr,
+                                c->n_cu));
   HIP_OR(c, hipMemcpyAsync(res, c->d_ingest, sizeof res, hipMemcpyDeviceToHost, c->stream));
   HIP_OR(c, hipStreamSynchronize(c->stream));
   trim_sub(c);
@@ -867,8 +875,8 @@ static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &
 // trips, so that the transactions in flight, T, are the throughput until they
 // conflict.  share: of the batch's transactions, those that write its most
 // written row; meet: the expected conflicts of a random pair (Batch::meet), so
-// that T of them have T x meet each.  known: false where only a lower bound of
-// meet is (cc_run_static, which does not count rows).
+// that T of them have T x meet each.  known: false where the rows were not
+// counted (a keyed batch of few transactions).
 //
 // Measured with 256 compute units, run time in ms at T = 256 (64 lanes),
 // 512, 1024 (16 lanes), 4096 (4 lanes), 16384 (4 lanes, 4 wavefronts), OCC's
@@ -905,8 +913,7 @@ static Shape plain_shape(uint32_t max_ops, bool known, double share, double meet
   if (!known) {
     uint32_t lanes = 1;
     while (lanes < 64 && lanes < max_ops) lanes *= 4;
-    if (meet * (double)(n_cu * 64 / (int)lanes) <= 1.0) return {lanes, 1, 0};
-    return limited();
+    return {lanes, 1, 0};
   }
   if (share >= 0.02) return {64, 1, 0};
   if (share >= 0.001) return limited();
@@ -1941,10 +1948,19 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   ia.out = (uint64_t *)(sc + STATIC_OFF_INGEST);
   uint64_t res[INGEST_N] = {};
   hipError_t e = launch_ingest(c->stream, ia, c->n_cu);
+  // the rows' writes, for the launch shape (the owner words are free again)
+  static_assert(INGEST_PAIRS == INGEST_TOP + 1, "the counts' results");
+  if (e == hipSuccess && c->d_cnt && n_ops)
+    e = launch_count_writes(c->stream, b.d_ops, n_ops, c->d_cnt, ia.owner, ia.out + INGEST_TOP, ia.out + INGEST_ERR,
+                            c->n_cu);
   if (e == hipSuccess) e = launch_fill_zero(c->stream, per_op_read, n_ops);
   if (e == hipSuccess) e = hipMemcpyAsync(res, ia.out, sizeof res, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "batch ingest");
+  if (e != hipSuccess) {
+    (void)hipFree(c->d_cnt);  // the counts may be anything now
+    c->d_cnt = nullptr;
+    return hip_fail(c, e, "batch ingest");
+  }
   if (res[INGEST_ERR] != ~0ull) {
     const uint64_t w = res[INGEST_ERR];
     const cc_status code = -(cc_status)(w & 15u);
@@ -1953,9 +1969,11 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   }
   b.max_ops = (uint32_t)res[INGEST_MAX_OPS];
   b.has_slot = (res[INGEST_KINDS] & 1) != 0;
-  // (rows are not counted: the conflicts if the writes were spread evenly, a lower bound)
-  const double w = n_txns ? (double)res[INGEST_PAIRS] / (double)n_txns : 0.0;
-  b.meet = w * w / (double)std::max<uint64_t>(c->total_rows, 1);
+  if (c->d_cnt && n_txns) {
+    b.shape_known = true;
+    b.shape_writes = res[INGEST_TOP];
+    b.meet = (double)res[INGEST_PAIRS] / ((double)n_txns * (double)n_txns);
+  }
   const cc_status st = run_batch(c, b, p, false);
   for (uint32_t i = 0; i < n_counters; ++i) counters[i] = i < CC_N_STATS ? b.stats[i] : 0;
   return st;

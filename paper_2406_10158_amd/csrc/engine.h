@@ -317,7 +317,6 @@ enum IngestOut {
   INGEST_N_CAND,
   INGEST_TOP,        // writes to the most written row
   INGEST_PAIRS,      // sum over the rows of c (c - 1), c writes: ordered pairs of writes that meet
-                     // (cc_run_static, which counts no rows: the written rows of all transactions)
   INGEST_CAND,       // PLAN_CAND x (count << 32 | ~row), most written first, 0: none
   INGEST_N = INGEST_CAND + PLAN_CAND
 };
@@ -363,9 +362,10 @@ hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu);
 
 // Counts a batch's writes per global row from its descriptors: out[0] = the most
 // written row's, out[1] = sum of c (c - 1) over the rows.  cnt: a count per
-// global row, 0 before and after; rows: n_ops scratch words.
+// global row, 0 before and after; rows: n_ops scratch words; err: nothing is
+// counted unless it holds ~0 (nullptr: well formed).
 hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
-                               uint64_t *out, int n_cu);
+                               uint64_t *out, const uint64_t *err, int n_cu);
 
 // The transactions that write one of the engine's rows -- those of `map` (a bit
 // per global row), or e's where map is nullptr -- in batch order: part (n_txns

@@ -192,7 +192,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     for (uint32_t t = 0; t < a.n_tables; ++t) indexed |= a.tab[t].indexed ? 1u << t : 0u;
   static_assert(CC_MAX_TABLES <= 32, "a bit per table");
   auto is_keyed = [&](const cc_op &o) { return o.table < 32u && ((indexed >> o.table) & 1u); };
-  uint32_t max_ops = 0, kinds = 0, writes = 0;
+  uint32_t max_ops = 0, kinds = 0;
   bool unordered = false, any_keyed = false;
   OpBits &bits = s.bits[team];
   const uint64_t step = (uint64_t)nb * TEAMS;
@@ -350,7 +350,6 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
         d.elem = kd ? 0u : (uint32_t)(tb_.elem_base + (uint64_t)o.row * tb_.n_fields + o.field);
         d.arg = o.arg;
         a.dops[f0 + i] = d;
-        writes += lead && wr;
         if (a.cnt && lead && wr && !kd) {
           uint32_t h = (grow * 0x9E3779B1u) >> (LOCAL ? 20 : 21);
           static_assert(RC_SLOTS == 1u << (LOCAL ? 12 : 11), "hash to the slots");
@@ -383,10 +382,6 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     for (uint32_t i = tid; i < RC_SLOTS; i += NT)
       if (s.cnt[i] && atomicAdd(&a.cnt[s.row[i]], s.cnt[i]) == 0) a.rows[s.op[i]] = s.row[i];
   max_ops = (uint32_t)wave_max(max_ops);
-  if (!a.cnt) {
-    const uint64_t w = wave_sum((uint64_t)writes);
-    if (lane == 0 && w) add_word(&a.out[INGEST_PAIRS], w);
-  }
   const uint64_t w_slot = ballot(kinds & 1u), w_cond = ballot(kinds & 2u), w_unord = ballot(unordered),
                  w_keyed = ballot(any_keyed);
   if (lane == 0) {
@@ -650,11 +645,12 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
   if (tid == 0) a.out[INGEST_TOP] = ld_word(&a.out[INGEST_CAND]) >> 32;
 }
 
-// The counts of a batch whose rows are known only at the run (keyed): as the
-// pack and count parts above, without the candidates.  262,144 x 16 ops, half
-// writes, uniform: 0.1 ms, once a batch.
+// The counts of a batch whose rows are known only at the run (keyed), or which
+// has no submission (cc_run_static): as the pack and count parts above, without
+// the candidates.  262,144 x 16 ops, half writes, uniform: 0.1 ms.
 __global__ void __launch_bounds__(256) count_mark_kernel(const DevOp *ops, uint64_t n_ops, uint32_t *cnt,
-                                                         uint32_t *rows, uint64_t *out) {
+                                                         uint32_t *rows, uint64_t *out, const uint64_t *err) {
+  if (err && ld_word(err) != ~0ull) return;  // malformed: the descriptors are not the batch's
   if (blockIdx.x == 0 && threadIdx.x < 2) out[threadIdx.x] = 0;
   const uint64_t step = (uint64_t)gridDim.x * 256;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_ops; i += step) {
@@ -665,7 +661,8 @@ __global__ void __launch_bounds__(256) count_mark_kernel(const DevOp *ops, uint6
   }
 }
 __global__ void __launch_bounds__(256) count_sum_kernel(const uint32_t *rows, uint64_t n_ops, uint32_t *cnt,
-                                                        uint64_t *out) {
+                                                        uint64_t *out, const uint64_t *err) {
+  if (err && ld_word(err) != ~0ull) return;
   __shared__ uint32_t s_top;
   __shared__ unsigned long long s_pairs;
   if (threadIdx.x == 0) {
@@ -697,11 +694,11 @@ __global__ void __launch_bounds__(256) count_sum_kernel(const uint32_t *rows, ui
   }
 }
 hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
-                               uint64_t *out, int n_cu) {
+                               uint64_t *out, const uint64_t *err, int n_cu) {
   const uint64_t most = (uint64_t)n_cu * 8, b = (n_ops + 255) / 256;
   const dim3 g((unsigned)(b < 1 ? 1 : (b < most ? b : most)));
-  hipLaunchKernelGGL(count_mark_kernel, g, dim3(256), 0, s, ops, n_ops, cnt, rows, out);
-  hipLaunchKernelGGL(count_sum_kernel, g, dim3(256), 0, s, rows, n_ops, cnt, out);
+  hipLaunchKernelGGL(count_mark_kernel, g, dim3(256), 0, s, ops, n_ops, cnt, rows, out, err);
+  hipLaunchKernelGGL(count_sum_kernel, g, dim3(256), 0, s, rows, n_ops, cnt, out, err);
   return hipGetLastError();
 }
 
