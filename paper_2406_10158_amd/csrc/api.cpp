@@ -1335,7 +1335,15 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
     plan_hot_rows(res, c->tables, b, c->n_cu);
   }
   e = alloc_breaks(b);
-  if (e == hipSuccess && b.eng_default) e = split_batch(c, b, c->d_hot);
+  if (e == hipSuccess && b.eng_default) {
+    const hipError_t es = split_batch(c, b, c->d_hot);
+    if (es == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      b.eng_default = false;  // no room for its lists
+    } else {
+      e = es;
+    }
+  }
   if (e != hipSuccess) {
     drop();
     return hip_fail(c, e, "batch allocation");
@@ -1512,10 +1520,21 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   // caller chose)
   const uint32_t eng_lanes = p.lanes_per_txn ? p.lanes_per_txn : 64;
   const bool eng_fits = (b.max_ops + eng_lanes - 1) / eng_lanes <= 4;
-  const bool use_eng = b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !(p.flags & CC_RUN_LATCH) && eng_fits &&
+  bool use_eng = b.scheme == CC_OCC && p.mode == CC_MODE_PLAIN && !(p.flags & CC_RUN_LATCH) && eng_fits &&
                        b.n_txns &&
                        ((p.flags & CC_RUN_HOT_ENGINE) ? b.eng.n_rows || b.eng_default
                                                       : !(p.flags & CC_RUN_NO_HOT_ENGINE) && b.eng_default);
+  if (use_eng) {
+    if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
+    hipError_t e = split_batch(c, b, nullptr);
+    if (e == hipSuccess) e = need_sub(c, engine_scratch_bytes(b.n_eng_ops, b.has_slot || b.has_cond, b.has_slot));
+    if (e != hipSuccess && (e != hipErrorOutOfMemory || (p.flags & CC_RUN_HOT_ENGINE)))
+      return hip_fail(c, e, "hot-row engine");
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // no room for its lists: the transaction kernel needs none
+      use_eng = false;
+    }
+  }
   uint32_t lanes = 0, wpw = 0;
   int grid = 0;
   auto choose_shape = [&]() {
@@ -1635,11 +1654,6 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       HIP_OR(c, hipMemsetAsync(c->d_latch, 0, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint32_t), c->stream));
     }
     a.latch = c->d_latch;
-  }
-
-  if (use_eng) {
-    HIP_OR(c, split_batch(c, b, nullptr));
-    HIP_OR(c, need_sub(c, engine_scratch_bytes(b.n_eng_ops, b.has_slot || b.has_cond, b.has_slot)));
   }
 
   const uint32_t defer = p.defer_after ? p.defer_after : (p.mode == CC_MODE_SERVE ? 256 : 16);
