@@ -7,6 +7,7 @@ their words and its claim of them; batches whose size is around what a few
 teams claim from the queue at a time; OCC's hot-row engine chosen by the
 counted conflicts, with and without operations a scan cannot see through.
 """
+import numpy as np
 import pytest
 
 import oracle
@@ -69,3 +70,16 @@ def test_keyed_batch_counted_at_its_first_run(n, theta):
             assert rep.ok, rep
         st = eng.run(eng.submit(b, "to"))
     assert st["hot_writes"] == wl.hottest_row_writes(b)[1]
+
+
+@pytest.mark.parametrize("n", [3, 255, 511, 512, 513])
+def test_percentiles_around_the_direct_ranks(n):
+    # up to 512 transactions every latency counts those below it; 513 go through the histograms
+    print(f"[gpu] direct ranks n={n}", flush=True)
+    tabs, b = wl.kv_workload(n_rows=2_000, n_fields=2, n_txns=n, ops=4, theta=0.5, seed=n)
+    with binding().Engine(tabs) as eng:
+        bid = eng.submit(b, "2pl_nw")
+        st = eng.run(bid)
+        out, _ = eng.outcomes(bid, n, 0)
+    lat = np.sort(out["commit_ns"])
+    assert [st["lat_p50_ns"], st["lat_p99_ns"]] == [int(lat[int(q * (n - 1) + 0.5)]) for q in (0.5, 0.99)]
