@@ -102,13 +102,22 @@ __global__ void __launch_bounds__(256) chain_keys_kernel(const DevOp *ops, uint6
 // Tile states for the look-back: meta is 0 until the tile has published, then
 // 1 with its sum relative to its entry in sum[], or 2 | f << 2 | b << 32 with
 // its value at the end in total[].  A value is performed before its meta.
-constexpr uint64_t CHM_SUM = 1, CHM_TOTAL = 2;
+// CHM_SETTLED: the chain at the tile's end has its initial value loaded, by a
+// tile that the chain begins in.  A constant slot write or a break gives a tile
+// its total whatever comes before it, so that a total alone does not say so; a
+// workgroup that ends a chain it did not begin stores the cell only once a tile
+// before it is settled, or the first tile could load what the last one stored.
+constexpr uint64_t CHM_SUM = 1, CHM_TOTAL = 2, CHM_SETTLED = 16;
+__device__ __forceinline__ uint64_t chm_total(const ChainVal &x, bool settled) {
+  return CHM_TOTAL | (settled ? CHM_SETTLED : 0) | ((uint64_t)x.f << 2) | ((uint64_t)x.b << 32);
+}
 
 template <bool BREAKS, bool STRICT>
 __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
   __shared__ uint32_t tile_s;
   __shared__ ChainVal wave_s[CH_THREADS / 64];
   __shared__ ChainVal entry_s;
+  __shared__ uint32_t mark_s[CH_THREADS / 64];  // 1: a chain begins among the wavefront's accesses, 2: one ends there
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   if (ld_word(&a.ctl->stop)) return;  // GPUTx: the rank pass was stopped (not changed while this kernel runs)
   // tiles are taken in order, so the tiles a look-back waits for belong to
@@ -147,11 +156,14 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
     if (head[j]) init[j] = a.data[key[j]];
   }
   // the thread's accesses, then the wavefront's and the workgroup's prefix
+  bool begins = false, ends = false;
   ChainVal run{0, CH_REL, 0};
 #pragma unroll
   for (int j = 0; j < CH_ITEMS; ++j) {
     if (head[j]) run = ChainVal{(uint64_t)init[j], CH_ABS, 0};
     run = ch_then(run, ch_effect(kind[j], arg[j], op[j]));
+    begins |= head[j];
+    ends |= last[j];
   }
   ChainVal inc = run;
 #pragma unroll
@@ -162,12 +174,17 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
   ChainVal pre = ch_shfl_up(inc, 1);
   if (lane == 0) pre = ChainVal{0, CH_REL, 0};
   if (lane == 63) wave_s[w] = inc;
+  const uint32_t mark = (ballot(begins) ? 1u : 0u) | (ballot(ends) ? 2u : 0u);
+  if (lane == 0) mark_s[w] = mark;
+  order_point<STRICT>();  // the initial values are in registers before the workgroup publishes (CHM_SETTLED) or stores
   __syncthreads();
   ChainVal all{0, CH_REL, 0}, waves{0, CH_REL, 0};
+  uint32_t marks = 0;
 #pragma unroll
   for (int i = 0; i < CH_THREADS / 64; ++i) {
     if (i == w) waves = all;
     all = ch_then(all, wave_s[i]);
+    marks |= mark_s[i];
   }
   if (w == 0) {
     // (only wavefront 0: lane 0 holds the tile's first access)
@@ -178,16 +195,16 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
     }
     order_point<STRICT>();
     if (lane == 0 && (all.f != CH_REL || cont))
-      st_word(a.meta + tile, all.f == CH_REL ? CHM_SUM
-                                             : CHM_TOTAL | ((uint64_t)all.f << 2) | ((uint64_t)all.b << 32));
+      st_word(a.meta + tile, all.f == CH_REL ? CHM_SUM : chm_total(all, marks & 1u));
     ChainVal entry{0, CH_REL, 0};
     if (cont) {
       // look back, 64 tiles at a time, to the nearest one whose value at its
       // end is known; the tiles between give their sums
       int64_t at = (int64_t)tile - 1;
+      bool settled = false;
       for (;;) {
         const int64_t t = at - lane;
-        const uint64_t m = t >= 0 ? ld_word(a.meta + t) : CHM_TOTAL;
+        const uint64_t m = t >= 0 ? ld_word(a.meta + t) : CHM_TOTAL | CHM_SETTLED;
         const uint64_t done = ballot((m & 3) == CHM_TOTAL), none = ballot((m & 3) == 0);
         const uint64_t upto = done ? (done & -done) | ((done & -done) - 1) : ~0ull;
         if (none & upto) {
@@ -202,6 +219,7 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
           const uint64_t md = readlane64(m, __ffsll((unsigned long long)done) - 1);
           entry.f = (uint32_t)(md >> 2) & 3u;
           entry.b = (uint32_t)(md >> 32);
+          settled = (md & CHM_SETTLED) != 0;
           break;
         }
         at -= 64;
@@ -209,8 +227,25 @@ __global__ void __launch_bounds__(CH_THREADS) chain_scan_kernel(ChainArgs a) {
       if (all.f == CH_REL) {
         if (lane == 0) st_word(a.total + tile, entry.v + all.v);
         order_point<STRICT>();
-        if (lane == 0) st_word(a.meta + tile, CHM_TOTAL | ((uint64_t)entry.f << 2) | ((uint64_t)entry.b << 32));
+        if (lane == 0) st_word(a.meta + tile, chm_total(entry, settled));
       }
+      // the chain ends here: on to the nearest settled tile.  Those between
+      // belong to the chain, as one that a chain begins in is settled; every
+      // tile is, or publishes without a wait, so that this one ends
+      at = (int64_t)tile - 1;
+      while ((marks & 2u) && !settled) {
+        const int64_t t = at - lane;
+        const uint64_t m = t >= 0 ? ld_word(a.meta + t) : CHM_SETTLED;
+        const uint64_t found = ballot((m & CHM_SETTLED) != 0), none = ballot(m == 0);
+        const uint64_t upto = found ? (found & -found) | ((found & -found) - 1) : ~0ull;
+        if (none & upto) {
+          __builtin_amdgcn_s_sleep(1);
+          continue;
+        }
+        settled = found != 0;
+        at -= 64;
+      }
+      order_point<STRICT>();
     }
     if (lane == 0) entry_s = entry;
   }
