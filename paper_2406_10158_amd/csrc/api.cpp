@@ -1284,7 +1284,8 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   ia.rows = (uint32_t *)(ia.cand + plan_cand_max(n_ops));
   ia.owner = ia.rows + n_ops;
   ia.hist = (uint32_t *)(c->d_ingest + INGEST_N);
-  if (scheme == CC_OCC && !maybe_keyed) {
+  if (scheme == CC_OCC) {
+    // (with keys too: a batch none of whose ops is on an indexed table is one by row)
     const size_t words = (n_rows + 31) / 32;
     if (!c->d_hot) e = hipMalloc(&c->d_hot, words * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemsetAsync(c->d_hot, 0, words * sizeof(uint32_t), c->stream);
