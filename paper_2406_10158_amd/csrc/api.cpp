@@ -621,10 +621,11 @@ uint64_t wait_limit_ticks(const cc_ctx *c, const cc_run_params &p) {
   return std::max<uint64_t>(1, p.wait_limit_us * c->wallclock_khz / 1000ull);
 }
 
-// Launch shapes of the ordered schemes: the ones whose transactions' operations
-// fit the register slots of the hand-off kernel's variants.  The chain scan has
-// one shape and takes every batch, but refuses what those refuse.
-hipError_t ordered_shape(uint32_t lanes, uint32_t max_ops, uint32_t wpw) {
+// Whether a launch shape exists: the kernels' variants hold 1, 4 or 16 operations
+// a lane in registers, with room for fewer wavefronts the more they hold.  (The
+// ordered schemes' chain scan has one shape and takes every batch, but refuses
+// what their hand-off kernels refuse.)
+hipError_t shape_exists(uint32_t lanes, uint32_t max_ops, uint32_t wpw) {
   const uint32_t k = (max_ops + lanes - 1) / lanes;
   const uint32_t most = lanes <= 4 ? 16u : 4u;
   if (k > most) return hipErrorInvalidValue;
@@ -692,7 +693,7 @@ cc_status ordered_stats(cc_ctx *c, Batch &b, bool chain, int grid_used, float ms
 cc_status run_gacco(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes, uint32_t wpw) {
   const bool strict = (p.flags & CC_RUN_STRICT_FENCES) != 0;
   const bool chain = p.wait_limit_us == 0;
-  const hipError_t shape = b.n_txns ? ordered_shape(lanes, b.max_ops, wpw) : hipSuccess;
+  const hipError_t shape = b.n_txns ? shape_exists(lanes, b.max_ops, wpw) : hipSuccess;
   if (shape != hipSuccess) return launch_error(c, shape);
   const uint32_t ns_per_tick_q16 = (uint32_t)((1000000ull << 16) / c->wallclock_khz);
 
@@ -1553,6 +1554,9 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
       if (wpw == 0) {
         wpw = sh.waves;
         if (grid == 0) grid = sh.grid;
+      } else {
+        // the caller's wavefronts, with as many lanes as they need to exist
+        while (lanes < 64 && shape_exists(lanes, b.max_ops, wpw) != hipSuccess) lanes *= 4;
       }
     } else if (lanes == 0) {
       if (no_hot_row && b.max_ops <= 64 && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
