@@ -1288,7 +1288,7 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   if (scheme == CC_OCC) {
     // (with keys too: a batch none of whose ops is on an indexed table is one by row)
     const size_t words = (n_rows + 31) / 32;
-    if (!c->d_hot) e = hipMalloc(&c->d_hot, words * sizeof(uint32_t));
+    if (e == hipSuccess && !c->d_hot) e = hipMalloc(&c->d_hot, words * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemsetAsync(c->d_hot, 0, words * sizeof(uint32_t), c->stream);
     ia.hot_map = c->d_hot;
   }

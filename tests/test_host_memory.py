@@ -1,0 +1,79 @@
+"""The engine's host side under failing copies and allocations, without a GPU.
+
+libcc.so runs on a HIP runtime of host memory (tests/fake_hip), loaded before
+it in a child process: allocations are counted against a capacity, a chosen
+call fails, and kernels only write the results that the host reads.  What is
+checked is the host's own work: which status a call returns, what stays
+allocated, and that memory kept for later batches never makes a call fail.
+"""
+import os
+import subprocess
+import sys
+
+import pytest
+
+from helpers import ROOT
+
+SETUP = r'''
+import ctypes, sys
+import numpy as np
+fake = ctypes.CDLL(FAKE, mode=ctypes.RTLD_GLOBAL)
+sys.path.insert(0, ROOT)
+from paper_2406_10158_amd import binding as B
+fake.fake_capacity.argtypes = [ctypes.c_size_t]
+fake.fake_used.restype = fake.fake_peak.restype = ctypes.c_size_t
+fake.fake_fail.argtypes = [ctypes.c_char_p, ctypes.c_long]
+fake.fake_batch.argtypes = [ctypes.c_uint64] * 3
+MB = 1 << 20
+
+def engine(rows=4096):
+    fake.fake_reset()
+    return B.Engine([np.zeros((rows, 1), np.int64)])
+
+def submit(eng, scheme="occ", txns=256, ops=4, ordered=True):
+    t = np.zeros(txns, B.TXN_DTYPE)
+    t["first_op"], t["n_ops"] = np.arange(txns) * ops, ops
+    return B.cc_submit_batch(eng.ctx, t, np.zeros(txns * ops, B.OP_DTYPE), B.SCHEMES[scheme])
+
+def status(f, *a, **k):
+    try:
+        f(*a, **k)
+    except B.CCError as e:
+        return e.status
+    return B.CC_OK
+'''
+
+
+@pytest.fixture(scope="module")
+def child(tmp_path_factory):
+    from paper_2406_10158_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    lib = str(tmp_path_factory.mktemp("fake_hip") / "libfake.so")
+    src = os.path.join(ROOT, "tests", "fake_hip", "fake_hip.cpp")
+    r = subprocess.run([build.HIPCC, *build.COMMON, "-shared", src, "-o", lib], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(code):
+        r = subprocess.run([sys.executable, "-c", f"ROOT, FAKE = {ROOT!r}, {lib!r}\n" + SETUP + code + "\nprint('ok')"],
+                           capture_output=True, text=True, timeout=100, cwd=ROOT)
+        assert r.returncode == 0 and r.stdout.endswith("ok\n"), r.stdout + r.stderr
+    return run
+
+
+@pytest.mark.parametrize("scheme", ["occ", "tictoc", "gacco"])
+def test_failed_copy_of_the_batch_is_reported(child, scheme):
+    # of a context's first submission, small (from pinned memory) and large, and of a later one
+    child(f'''
+for txns in (256, 1 << 15):
+    for copy in (0, 1):
+        if txns == 256 and copy:
+            continue  # one copy
+        with engine() as eng:
+            fake.fake_fail(b"hipMemcpyHtoD", copy)
+            assert status(submit, eng, {scheme!r}, txns) == B.CC_E_HIP, (txns, copy)
+            fake.fake_fail(b"", 0)
+            B.cc_release_batch(eng.ctx, submit(eng, {scheme!r}, txns))
+            fake.fake_fail(b"hipMemcpyHtoD", copy)
+            assert status(submit, eng, {scheme!r}, txns) == B.CC_E_HIP, (txns, copy)
+''')
