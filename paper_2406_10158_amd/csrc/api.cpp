@@ -131,7 +131,9 @@ cc_status fail(cc_ctx *c, cc_status st, const std::string &msg) {
   return st;
 }
 
+// (a launch asks for the thread's last error: one that has been reported is not left for the next call to find)
 cc_status hip_fail(cc_ctx *c, hipError_t e, const char *what) {
+  (void)hipGetLastError();
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
   if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) return fail(c, CC_E_NOMEM, m);
   return fail(c, CC_E_HIP, m);

@@ -77,3 +77,22 @@ for txns in (256, 1 << 15):
             fake.fake_fail(b"hipMemcpyHtoD", copy)
             assert status(submit, eng, {scheme!r}, txns) == B.CC_E_HIP, (txns, copy)
 ''')
+
+
+@pytest.mark.parametrize("scheme", ["occ", "mvcc", "gputx"])
+def test_a_failed_call_does_not_fail_the_next(child, scheme):
+    # out of memory in a submission and in a run; the same calls then succeed
+    child(f'''
+for nth in range(8):
+    with engine() as eng:
+        fake.fake_fail(b"hipMalloc", nth)
+        st = status(submit, eng, {scheme!r})
+        fake.fake_fail(b"", 0)
+        assert st in (B.CC_OK, B.CC_E_NOMEM), st
+        bid = submit(eng, {scheme!r})
+        fake.fake_fail(b"hipMalloc", 0)
+        st = status(eng.run, bid)
+        fake.fake_fail(b"", 0)
+        assert st in (B.CC_OK, B.CC_E_NOMEM), st
+        eng.run(bid)
+''')
