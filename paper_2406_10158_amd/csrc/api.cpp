@@ -147,6 +147,28 @@ cc_status hip_fail(cc_ctx *c, hipError_t e, const char *what) {
 
 bool activate(cc_ctx *c) { return hipSetDevice(c->device) == hipSuccess; }
 
+// Device memory for a context.  Out of memory, what the context only keeps for
+// later is given back first: the released batches' arenas and, where the caller
+// does not need it now, the submission scratch.
+hipError_t dev_malloc(cc_ctx *c, void **p, size_t bytes, bool keep_scratch) {
+  hipError_t e = hipMalloc(p, bytes);
+  const bool scratch = c->d_sub && !keep_scratch;
+  if (e != hipErrorOutOfMemory || (c->pool.empty() && !scratch)) return e;
+  (void)hipGetLastError();
+  for (auto &a : c->pool) (void)hipFree(a.first);
+  c->pool.clear();
+  if (scratch) {
+    (void)hipFree(c->d_sub);
+    c->d_sub = nullptr;
+    c->sub_bytes = 0;
+  }
+  return hipMalloc(p, bytes);
+}
+template <class T>
+hipError_t dev_malloc(cc_ctx *c, T **p, size_t bytes, bool keep_scratch = false) {
+  return dev_malloc(c, (void **)p, bytes, keep_scratch);
+}
+
 cc_status freeze(cc_ctx *c) {
   if (c->frozen) return CC_OK;
   if (c->tables.empty()) return fail(c, CC_E_STATE, "no tables declared");
@@ -778,7 +800,7 @@ static bool gputx_ahead(const Batch &b) {
 }
 
 cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes, uint32_t wpw) {
-  if (!c->d_kstate) HIP_OR(c, hipMalloc(&c->d_kstate, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint64_t)));
+  if (!c->d_kstate) HIP_OR(c, dev_malloc(c, &c->d_kstate, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint64_t)));
   const uint64_t n = b.n_txns;
   GputxArgs a{};
   a.ops = b.d_ops;
@@ -980,7 +1002,7 @@ static hipError_t need_sub(cc_ctx *c, size_t bytes) {
   if (c->d_sub) (void)hipFree(c->d_sub);
   c->d_sub = nullptr;
   c->sub_bytes = 0;
-  const hipError_t e = hipMalloc(&c->d_sub, bytes);
+  const hipError_t e = dev_malloc(c, &c->d_sub, bytes);
   if (e == hipSuccess) c->sub_bytes = bytes;
   return e;
 }
@@ -1002,8 +1024,8 @@ static hipError_t split_batch(cc_ctx *c, Batch &b, const uint32_t *map) {
   EngineDesc *desc = nullptr;
   hipError_t e = need_sub(c, split_scratch_words(b.n_txns) * sizeof(uint32_t));
   uint32_t *w = (uint32_t *)c->d_sub;
-  if (e == hipSuccess) e = hipMalloc(&part, b.n_txns * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(&desc, b.n_txns * sizeof(EngineDesc));
+  if (e == hipSuccess) e = dev_malloc(c, &part, b.n_txns * sizeof(uint32_t), true);
+  if (e == hipSuccess) e = dev_malloc(c, &desc, b.n_txns * sizeof(EngineDesc), true);
   if (e == hipSuccess) e = launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, map, w, part, desc, c->n_cu);
   if (e == hipSuccess) e = hipMemcpyAsync(&behind, w, sizeof behind, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipMemcpyAsync(&n_eng, w + 2 + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream);
@@ -1141,14 +1163,7 @@ static hipError_t alloc_batch(cc_ctx *c, Batch &b, bool keyed) {
     b.arena_bytes = best->second;
     c->pool.erase(best);
   } else {
-    hipError_t e = hipMalloc(&b.arena, bytes);
-    if (e == hipErrorOutOfMemory && !c->pool.empty()) {
-      // the kept arenas first
-      (void)hipGetLastError();
-      for (auto &a : c->pool) (void)hipFree(a.first);
-      c->pool.clear();
-      e = hipMalloc(&b.arena, bytes);
-    }
+    const hipError_t e = dev_malloc(c, &b.arena, bytes, true);
     if (e != hipSuccess) {
       b.arena = nullptr;
       return e;
@@ -1160,10 +1175,10 @@ static hipError_t alloc_batch(cc_ctx *c, Batch &b, bool keyed) {
 }
 
 // The buffers of an ordered batch's breaks (chain.hip), once its kinds of operations are known.
-static hipError_t alloc_breaks(Batch &b) {
+static hipError_t alloc_breaks(cc_ctx *c, Batch &b) {
   const bool ordered_scheme = b.scheme == CC_GACCO || b.scheme == CC_GPUTX;
   if (!ordered_scheme || !(b.has_slot || b.has_cond) || b.n_ops == 0) return hipSuccess;
-  return hipMalloc(&b.d_breaks, b.n_ops * (sizeof(uint64_t) + 2 * sizeof(uint32_t)));
+  return dev_malloc(c, &b.d_breaks, b.n_ops * (sizeof(uint64_t) + 2 * sizeof(uint32_t)));
 }
 
 // True if [p, p + bytes) lies inside one allocation of the context's device.
@@ -1244,10 +1259,10 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   b.n_txns = n_txns;
   b.n_ops = n_ops;
   if (!c->d_ingest)
-    HIP_OR(c, hipMalloc(&c->d_ingest, INGEST_N * sizeof(uint64_t) + (PLAN_COUNTS + PLAN_BINS) * sizeof(uint32_t)));
+    HIP_OR(c, dev_malloc(c, &c->d_ingest, INGEST_N * sizeof(uint64_t) + (PLAN_COUNTS + PLAN_BINS) * sizeof(uint32_t)));
   const uint64_t n_rows = std::max<uint64_t>(c->total_rows, 1);
   if (!c->d_cnt) {
-    HIP_OR(c, hipMalloc(&c->d_cnt, n_rows * sizeof(uint32_t)));
+    HIP_OR(c, dev_malloc(c, &c->d_cnt, n_rows * sizeof(uint32_t)));
     HIP_OR(c, hipMemsetAsync(c->d_cnt, 0, n_rows * sizeof(uint32_t), c->stream));
   }
   // scratch: [the host's arrays], keys, candidates, marked rows, owners
@@ -1290,7 +1305,7 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
   if (scheme == CC_OCC) {
     // (with keys too: a batch none of whose ops is on an indexed table is one by row)
     const size_t words = (n_rows + 31) / 32;
-    if (e == hipSuccess && !c->d_hot) e = hipMalloc(&c->d_hot, words * sizeof(uint32_t));
+    if (e == hipSuccess && !c->d_hot) e = dev_malloc(c, &c->d_hot, words * sizeof(uint32_t), true);
     if (e == hipSuccess) e = hipMemsetAsync(c->d_hot, 0, words * sizeof(uint32_t), c->stream);
     ia.hot_map = c->d_hot;
   }
@@ -1338,7 +1353,7 @@ static cc_status submit_impl(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, con
     // (keyed ops learn their rows only when the index is searched, at the run)
     plan_hot_rows(res, c->tables, b, c->n_cu);
   }
-  e = alloc_breaks(b);
+  e = alloc_breaks(c, b);
   if (e == hipSuccess && b.eng_default) {
     const hipError_t es = split_batch(c, b, c->d_hot);
     if (es == hipErrorOutOfMemory) {
@@ -1428,10 +1443,10 @@ cc_status cc_create_index(cc_ctx *c, uint32_t tid, const int64_t *keys, uint64_t
     if (x.tree) (void)hipFree(x.tree);
     x = DevIndex{};
   };
-  if (!c->d_idx) HIP_OR(c, hipMalloc(&c->d_idx, CC_MAX_TABLES * sizeof(IndexDesc)));
-  hipError_t e = hipMalloc(&nx.keys, level0.size() * sizeof(int64_t));
-  if (e == hipSuccess) e = hipMalloc(&nx.rows, rows.size() * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMalloc(&nx.tree, std::max<size_t>(tree.size(), 1) * sizeof(int64_t));
+  if (!c->d_idx) HIP_OR(c, dev_malloc(c, &c->d_idx, CC_MAX_TABLES * sizeof(IndexDesc)));
+  hipError_t e = dev_malloc(c, &nx.keys, level0.size() * sizeof(int64_t));
+  if (e == hipSuccess) e = dev_malloc(c, &nx.rows, rows.size() * sizeof(uint32_t));
+  if (e == hipSuccess) e = dev_malloc(c, &nx.tree, std::max<size_t>(tree.size(), 1) * sizeof(int64_t));
   if (e == hipSuccess)
     e = hipMemcpyAsync(nx.keys, level0.data(), level0.size() * sizeof(int64_t), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess)
@@ -1587,7 +1602,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   a.data = c->d_data;
   a.words = c->d_words;
   if (b.scheme == CC_MVCC && !c->d_aux) {
-    HIP_OR(c, hipMalloc(&c->d_aux, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint64_t)));
+    HIP_OR(c, dev_malloc(c, &c->d_aux, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint64_t)));
   }
   a.aux = c->d_aux;
   if (b.scheme == CC_MVCC) {
@@ -1608,7 +1623,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
         b.epoch_graph = nullptr;
       }
       const uint64_t bytes = 32 + slots * 4 * sizeof(uint64_t);
-      HIP_OR(c, hipMalloc(&b.d_nodes, bytes));
+      HIP_OR(c, dev_malloc(c, &b.d_nodes, bytes));
       HIP_OR(c, hipMemsetAsync(b.d_nodes, 0, bytes, c->stream));  // tags 0 (lap 0), ring counter 0
       b.node_slots = slots;
     }
@@ -1657,7 +1672,7 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   if (p.flags & CC_RUN_LATCH) {
     if (!c->d_latch) {
       // latches are free between critical sections, so they are cleared once
-      HIP_OR(c, hipMalloc(&c->d_latch, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint32_t)));
+      HIP_OR(c, dev_malloc(c, &c->d_latch, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint32_t)));
       HIP_OR(c, hipMemsetAsync(c->d_latch, 0, std::max<uint64_t>(c->total_rows, 1) * sizeof(uint32_t), c->stream));
     }
     a.latch = c->d_latch;
@@ -2028,7 +2043,7 @@ cc_status cc_set_arrivals(cc_ctx *c, uint64_t batch_id, const int64_t *arrival_n
     ticks[n + t] = arrival_ns[t];
   }
   if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
-  if (!b.d_arrival) HIP_OR(c, hipMalloc(&b.d_arrival, ticks.size() * sizeof(int64_t)));
+  if (!b.d_arrival) HIP_OR(c, dev_malloc(c, &b.d_arrival, ticks.size() * sizeof(int64_t)));
   HIP_OR(c, hipMemcpyAsync(b.d_arrival, ticks.data(), 2 * n * sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
   HIP_OR(c, hipStreamSynchronize(c->stream));
   b.arrival_ns.assign(arrival_ns, arrival_ns + n);

@@ -96,3 +96,71 @@ for nth in range(8):
         assert st in (B.CC_OK, B.CC_E_NOMEM), st
         eng.run(bid)
 ''')
+
+
+KEPT = r'''
+def keep(eng):
+    """Four released batches, whose arenas the context keeps, and the scratch of their submission."""
+    for bid in [submit(eng, "gacco", 1 << 14, 16) for _ in range(4)]:
+        B.cc_release_batch(eng.ctx, bid)
+
+def room(megabytes):
+    fake.fake_capacity(fake.fake_used() + int(megabytes * MB))
+'''
+
+
+@pytest.mark.parametrize("what,code", [
+    ("submission scratch", """
+    keep(eng)
+    room(20)
+    submit(eng, "occ", 1 << 16, 16)"""),
+    ("arena", """
+    keep(eng)
+    room(1)
+    submit(eng, "gacco", 1 << 16, 4)
+    submit(eng, "mvcc", 256, 4)"""),
+    ("breaks", """
+    keep(eng)
+    room(1)
+    fake.fake_batch(0, 1, 0)
+    submit(eng, "gacco", 1 << 14, 16)"""),
+    ("hot-row engine's lists", """
+    keep(eng)
+    room(0.1)
+    fake.fake_batch(1 << 24, 0, 1 << 16)
+    assert eng.run(submit(eng, "occ", 1 << 14, 16))["engine_txns"] == 1 << 14"""),
+    ("hot-row engine's scratch", """
+    fake.fake_batch(1 << 24, 0, 1 << 20)
+    bid = submit(eng, "occ", 1 << 14, 16)
+    fake.fake_batch(0, 0, 0)
+    keep(eng)
+    room(10)
+    assert eng.run(bid)["engine_txns"] == 1 << 14"""),
+    ("version pointers", """
+    bid = submit(eng, "mvcc")
+    keep(eng)
+    room(1)
+    eng.run(bid)"""),
+    ("rank states", """
+    bid = submit(eng, "gputx")
+    keep(eng)
+    room(1)
+    eng.run(bid)"""),
+    ("latches", """
+    bid = submit(eng, "tictoc")
+    keep(eng)
+    room(1)
+    eng.run(bid, flags=B.CC_RUN_LATCH)"""),
+    ("arrivals", """
+    bid = submit(eng, "tictoc", 1 << 17, 1)
+    keep(eng)
+    room(1)
+    B.cc_set_arrivals(eng.ctx, bid, np.arange(1 << 17))"""),
+    ("index", """
+    keep(eng)
+    room(20)
+    eng.create_index(0, np.arange(1 << 21))"""),
+], ids=lambda v: v.replace(" ", "-") if "\n" not in v else "")
+def test_kept_memory_makes_room(child, what, code):
+    # with little room beside it, so that the call succeeds only with what the context keeps given back
+    child(KEPT + "with engine(1 << 21) as eng:" + code + "\nassert fake.fake_used() == 0")
