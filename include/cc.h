@@ -539,7 +539,12 @@ cc_status cc_set_arrivals(cc_ctx *ctx, uint64_t batch_id, const int64_t *arrival
  */
 cc_status cc_stats(cc_ctx *ctx, uint64_t batch_id, uint64_t *counters, uint32_t n);
 
-/* Free a batch's device buffers. */
+/*
+ * Free a batch's device buffers.  For the next batches the context keeps at
+ * most 512 MiB of them, and at most 1 GiB of scratch of the submissions and of
+ * OCC's hot-row engine; it frees both when an allocation of its own would
+ * otherwise fail, and with cc_destroy.
+ */
 cc_status cc_release_batch(cc_ctx *ctx, uint64_t batch_id);
 
 /*

@@ -995,8 +995,10 @@ static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables,
   for (int i = 0; i < nc && i < HOT_MAX && (uint32_t)(cand[i] >> 32) >= thr; ++i) b.hot_rows[b.n_hot++] = ~(uint32_t)cand[i];
 }
 
-// At least `bytes` of submission scratch.  It grows to the largest batch's
-// need; a very large one is given back when the submission is over (trim_sub).
+// At least `bytes` of submission scratch, which the hot-row engine uses too.  It
+// grows to the largest batch's need; a very large one is given back when the
+// submission is over, and the engine's, which a batch that runs again needs
+// again, when a batch is released (trim_sub).
 static hipError_t need_sub(cc_ctx *c, size_t bytes) {
   if (bytes <= c->sub_bytes) return hipSuccess;
   if (c->d_sub) (void)hipFree(c->d_sub);
@@ -2066,6 +2068,7 @@ cc_status cc_release_batch(cc_ctx *c, uint64_t batch_id) {
   (void)hipStreamSynchronize(c->stream);
   free_batch(c, it->second);
   c->batches.erase(it);
+  trim_sub(c);
   return CC_OK;
 }
 

@@ -164,3 +164,26 @@ def room(megabytes):
 def test_kept_memory_makes_room(child, what, code):
     # with little room beside it, so that the call succeeds only with what the context keeps given back
     child(KEPT + "with engine(1 << 21) as eng:" + code + "\nassert fake.fake_used() == 0")
+
+
+def test_released_batches_leave_at_most_what_the_header_says(child):
+    # a hot-row engine of 40M operations, whose scratch is above the gibibyte that is kept
+    child('''
+with engine() as eng:
+    used = fake.fake_used()
+    fake.fake_batch(1 << 24, 0, 40 << 20)
+    bid = submit(eng, "occ", 1 << 14, 16)
+    for _ in range(2):
+        peak = fake.fake_used()
+        assert eng.run(bid)["engine_txns"] == 1 << 14
+    assert peak - used > 1 << 30  # (kept for the batch's next run)
+    B.cc_release_batch(eng.ctx, bid)
+    assert fake.fake_used() - used <= 512 * MB
+    for _ in range(6):  # five released batches of up to 250 MB
+        fake.fake_batch(0, 0, 0)
+        ids = [submit(eng, "gacco", 1 << 16, 32 + i) for i in range(5)]
+        for b in ids:
+            B.cc_release_batch(eng.ctx, b)
+        assert fake.fake_used() - used <= (512 + 1024) * MB
+assert fake.fake_used() == 0
+''')
