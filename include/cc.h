@@ -466,9 +466,12 @@ cc_status cc_fetch_rows(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows);
  * shared row space plus the row, tables in creation order -- most written
  * first; *n_rows their count (0: no engine for this batch: not OCC, keyed,
  * static, or nothing written often enough); *n_txns the transactions that
- * write one of them (counted by each call, a kernel over the batch);
- * *by_default 1 if no row left out is written more than a quarter as often as
- * the most written one.
+ * write one of them (counted by a batch's first call, by kernels over the
+ * batch); *by_default 1 if cc_run uses the engine for this batch without being
+ * told to (in CC_MODE_PLAIN, without CC_RUN_LATCH and with at most 4 ops a
+ * lane).  By default it takes every row that is written more than once, of
+ * which these are the most written; with CC_RUN_HOT_ENGINE on another batch,
+ * these.
  */
 #define CC_ENGINE_MAX_ROWS 32
 cc_status cc_engine_plan(cc_ctx *ctx, uint64_t batch_id, uint32_t *rows, uint32_t *n_rows, uint64_t *n_txns,

@@ -68,10 +68,11 @@ struct Batch {
   // OCC's hot-row engine (hot_engine.hip): the plan's rows, and whether the
   // batch's hot rows are worth it (decided at submission).  d_part, from the
   // split (split_batch): the engine's transactions (n_eng_txns), then the
-  // others; d_eng_desc: the engine's.  eng_gain: every row left out of the plan
-  // is written at most a quarter as often as the most written row
+  // others; d_eng_desc: the engine's.  plan_txns: the transactions that write one
+  // of the plan's rows (~0: not counted yet, cc_engine_plan)
   EngineRows eng{};
-  bool eng_gain = false, eng_default = false;
+  bool eng_default = false;
+  uint64_t plan_txns = ~0ull;
   uint64_t n_eng_txns = 0, n_eng_ops = 0, eng_behind = 0;
   uint32_t *d_part = nullptr;
   EngineDesc *d_eng_desc = nullptr;
@@ -869,29 +870,17 @@ cc_status run_gputx(cc_ctx *c, Batch &b, const cc_run_params &p, uint32_t lanes,
 // most ENG_FIELDS fields and ENG_VALS cells in all.
 static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &tables, Batch &b) {
   b.eng = EngineRows{};
-  b.eng_gain = false;
   const uint32_t thr = (uint32_t)std::max<uint64_t>(2, b.n_txns / 4096);
-  if (nc == 0 || (uint32_t)(cand[0] >> 32) < thr) return;
-  uint32_t left_out = 0, cells = 0;  // left_out: writes of the most written row not taken
-  bool full = false;
-  for (int i = 0; i < nc; ++i) {
+  uint32_t cells = 0;
+  for (int i = 0; i < nc && b.eng.n_rows < (uint32_t)ENG_MAX; ++i) {
     const uint32_t r = ~(uint32_t)cand[i], writes = (uint32_t)(cand[i] >> 32);
     const Table *tb = nullptr;
     for (const Table &t : tables)
       if (r >= t.row_base && r < t.row_base + t.n_rows) tb = &t;
-    const bool take = !full && writes >= thr && tb && tb->n_fields <= (uint32_t)ENG_FIELDS &&
-                      cells + tb->n_fields <= (uint32_t)ENG_VALS;
-    if (take) {
-      b.eng.row[b.eng.n_rows++] = r;
-      cells += tb->n_fields;
-      full = b.eng.n_rows == (uint32_t)ENG_MAX;
-    } else if (!left_out) {
-      left_out = writes;
-    }
+    if (writes < thr || !tb || tb->n_fields > (uint32_t)ENG_FIELDS || cells + tb->n_fields > (uint32_t)ENG_VALS) continue;
+    b.eng.row[b.eng.n_rows++] = r;
+    cells += tb->n_fields;
   }
-  // a row below the candidates is written at most as often as the last candidate
-  if (!left_out && nc == PLAN_CAND) left_out = (uint32_t)(cand[nc - 1] >> 32);
-  b.eng_gain = b.eng.n_rows && (uint64_t)left_out * 4 <= cand[0] >> 32;
 }
 
 // Launch shape of a plain run's transaction kernel where the caller leaves it
@@ -1489,12 +1478,12 @@ cc_status cc_engine_plan(cc_ctx *c, uint64_t batch_id, uint32_t *rows, uint32_t 
   if (!c || !rows || !n_rows || !n_txns || !by_default) return CC_E_INVAL;
   auto it = c->batches.find(batch_id);
   if (it == c->batches.end()) return fail(c, CC_E_NOBATCH, "unknown batch");
-  const Batch &b = it->second;
+  Batch &b = it->second;
   static_assert(CC_ENGINE_MAX_ROWS == ENG_MAX, "engine rows");
   for (uint32_t i = 0; i < (uint32_t)ENG_MAX; ++i) rows[i] = i < b.eng.n_rows ? b.eng.row[i] : 0u;
   *n_rows = b.eng.n_rows;
   *n_txns = 0;
-  if (b.eng.n_rows) {
+  if (b.eng.n_rows && b.plan_txns == ~0ull) {
     if (!activate(c)) return fail(c, CC_E_HIP, "hipSetDevice failed");
     uint32_t n_eng = 0;
     HIP_OR(c, need_sub(c, split_scratch_words(b.n_txns) * sizeof(uint32_t)));
@@ -1502,9 +1491,11 @@ cc_status cc_engine_plan(cc_ctx *c, uint64_t batch_id, uint32_t *rows, uint32_t 
     HIP_OR(c, launch_split(c->stream, b.d_ops, b.d_txns, b.n_txns, b.eng, nullptr, w, nullptr, nullptr, c->n_cu));
     HIP_OR(c, hipMemcpyAsync(&n_eng, w + 2 + b.n_txns, sizeof n_eng, hipMemcpyDeviceToHost, c->stream));
     HIP_OR(c, hipStreamSynchronize(c->stream));
-    *n_txns = n_eng;
+    trim_sub(c);
+    b.plan_txns = n_eng;
   }
-  *by_default = b.eng.n_rows && b.eng_gain ? 1 : 0;
+  if (b.eng.n_rows) *n_txns = b.plan_txns;
+  *by_default = b.eng_default ? 1 : 0;
   return CC_OK;
 }
 
