@@ -31,6 +31,11 @@ KERNEL_SOURCES = {"txn_kernel": ("kernels.hip", "schemes.h", "txn_kernel.h", "de
                   "hot_engine": ("hot_engine.hip", "chain.hip", "gacco.hip", "engine.h", "device.h")}
 
 
+def engine_transactions(serial_lo, n: int) -> np.ndarray:
+    """The transactions that OCC's hot-row engine ran: it drew the run's first n tickets, 1 to n."""
+    return np.nonzero(np.asarray(serial_lo) <= n)[0]
+
+
 def algorithmic_bytes(batch) -> int:
     """Bytes the OCC hot path must move for one committed pass over the batch.
 
@@ -564,7 +569,7 @@ def main():
     # sort and its scan) over its own share of the batch: the first tickets
     eng_txns = np.zeros(0, np.int64)
     if args.scheme == "occ" and st["engine_txns"]:
-        eng_txns = np.nonzero(out_last["serial_lo"] < st["engine_txns"])[0]
+        eng_txns = engine_transactions(out_last["serial_lo"], st["engine_txns"])
     k_step_s = float(np.mean(kernel_ns)) * 1e-9
     if len(eng_txns):
         alg = algorithmic_bytes(batch.subset(eng_txns))
