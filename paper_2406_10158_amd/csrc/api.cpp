@@ -199,11 +199,16 @@ cc_status freeze(cc_ctx *c) {
   c->d_words = words;
   // the counts per row, here for cc_run_static, which does not allocate (without
   // them it uses the shape for unknown rows, and a submission tries again)
-  if (c->d_static && hipMalloc(&c->d_cnt, std::max<uint64_t>(rows, 1) * sizeof(uint32_t)) != hipSuccess) {
-    (void)hipGetLastError();
-    c->d_cnt = nullptr;
+  if (c->d_static) {
+    const size_t bytes = std::max<uint64_t>(rows, 1) * sizeof(uint32_t);
+    e = hipMalloc(&c->d_cnt, bytes);
+    if (e == hipSuccess) e = hipMemsetAsync(c->d_cnt, 0, bytes, c->stream);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipFree(c->d_cnt);
+      c->d_cnt = nullptr;
+    }
   }
-  if (c->d_cnt) HIP_OR(c, hipMemsetAsync(c->d_cnt, 0, std::max<uint64_t>(rows, 1) * sizeof(uint32_t), c->stream));
   c->frozen = true;
   return CC_OK;
 }

@@ -187,3 +187,21 @@ with engine() as eng:
         assert fake.fake_used() - used <= (512 + 1024) * MB
 assert fake.fake_used() == 0
 ''')
+
+
+def test_tables_are_allocated_once_whatever_fails_behind_them(child):
+    # the fills of the values and of the counts per row, failing one after the other
+    child('''
+fake.fake_reset()
+for nth in range(3):
+    ctx = B.cc_init()
+    t = B.cc_create_table(ctx, 1 << 16, 4)
+    rows = np.ones((1 << 16, 4), np.int64)
+    fake.fake_fail(b"hipMemsetAsync", nth)
+    st = status(B.cc_load, ctx, t, rows)
+    fake.fake_fail(b"", 0)
+    assert st in (B.CC_OK, B.CC_E_HIP), st
+    B.cc_load(ctx, t, rows)
+    B.cc_destroy(ctx)
+    assert fake.fake_used() == 0, nth
+''')
