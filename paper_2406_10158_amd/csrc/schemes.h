@@ -892,6 +892,11 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
   // row's value under the lock if the lock returns the WTS R0 saw (every commit
   // raises it, and a writer whose install the load could have seen held the
   // lock until it had).  Rows are then held for R1, R3 and the installs only.
+  // Not with several operations a lane: those transactions' attempts mostly
+  // fail on a lock, after which the values were loaded for nothing (100-256 ops
+  // on 5,000 rows, Zipf 0.3: 24.5 ms with the early values, 22.7 without; 256 ops on
+  // 20,000 rows, Zipf 0.6: 14.9 and 13.0).
+  const bool early = precheck && K == 1;
   bool issued[K];
   uint64_t seen[K];
 #pragma unroll
@@ -904,7 +909,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
       if (op_written(s.rowk[k])) s.v[k] = w_or<LATCH, STRICT>(a, w, TT_LOCK);
       else s.v[k] = ld_word(w);
     }
-    if (precheck && go && s.valid[k]) s.x[k] = ld_val(a.data + s.elem[k]);
+    if (early && go && s.valid[k]) s.x[k] = ld_val(a.data + s.elem[k]);
   }
   order_point<STRICT>();
 #pragma unroll
@@ -914,7 +919,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
     if ((o & TT_LOCK) && blk == ~0u) blk = op_row(s.rowk[k]);
     if (op_written(s.rowk[k])) {
       s.got[k] = !(o & TT_LOCK);
-      fail |= precheck && tt_wts(o) != tt_wts(seen[k]);
+      fail |= early && tt_wts(o) != tt_wts(seen[k]);
     }
     fail |= (o & TT_LOCK) != 0;
   }
@@ -930,7 +935,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     if (alive && s.valid[k]) {
-      if (!precheck) s.x[k] = ld_val(a.data + s.elem[k]);
+      if (!early) s.x[k] = ld_val(a.data + s.elem[k]);
       if (op_leader(s.rowk[k])) {
         const uint64_t c = op_written(s.rowk[k]) ? tt_rts(s.v[k]) + 1 : tt_wts(s.v[k]);
         cts = c > cts ? c : cts;
@@ -939,7 +944,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
   }
   cts = t.max(cts);
   const bool overflow = alive && cts > TT_WTS_MASK - TT_DELTA_MAX;
-  if (ballot(alive && !precheck)) order_point<STRICT>();
+  if (ballot(alive && !early)) order_point<STRICT>();
   // R3: the words and the ticket in one round
 #pragma unroll
   for (int k = 0; k < K; ++k) {
