@@ -62,7 +62,9 @@ struct Batch {
   // they are known (of a keyed batch from its first plain run on)
   bool shape_known = false;
   uint64_t shape_writes = 0;
-  double meet = 0;  // expected writes of one transaction to rows another one writes, for a random pair
+  double meet = 0;   // expected writes of one transaction to rows another one writes, for a random pair
+  double clash = 0;  // meet, raised where there are more reads than writes, which meet writes too
+  double rest_clash = 0;  // the same of the transactions that the hot-row engine leaves: their reads and writes
   uint32_t n_hot = 0;
   uint32_t hot_rows[HOT_MAX] = {};
   // OCC's hot-row engine (hot_engine.hip): the plan's rows, and whether the
@@ -238,6 +240,28 @@ cc_status resolve_keys(cc_ctx *c, Batch &b, const cc_run_params &p, float *ms) {
   return CC_OK;
 }
 
+// What the counted rows say of the batch's conflicts.  Reads are not counted per
+// row: they are taken to be distributed as the writes are, so that a row has as
+// many reads a write as the batch (the pairs of a read and a write, counted, were
+// within 2% of this on Zipf 0.3 and 0.6, half and a tenth writes).  clash is meet
+// up to as many reads as writes, for which the rules below were measured, and
+// grows with the pairs beyond (but not for short transactions of a skewed batch:
+// 16 ops, Zipf 0.8 on 2M rows, a tenth writes, 2PL 0.75 ms with 1024 in flight, 0.80
+// with 256).  Behind the hot-row engine no two write one row: what is left is the
+// reads of rows written once, few where the batch is skewed (32 ops, Zipf 0.8 on
+// 2M rows, OCC 0.23 ms with all of it in flight, 0.25 with 1024; 64 ops, Zipf 0.3
+// on 262,144 rows, share 0.0013, 0.36 with all of it, 0.23 with 256).
+void set_conflicts(Batch &b, uint64_t top, uint64_t pairs, uint64_t writes) {
+  const double n = std::max(1.0, (double)b.n_txns), w = (double)writes, r = (double)b.n_ops - w;
+  b.shape_known = true;
+  b.shape_writes = top;
+  b.meet = (double)pairs / (n * n);
+  const double share = (double)top / n;
+  b.clash = b.meet;
+  if (writes && (b.max_ops > 16 || share < 0.001)) b.clash *= std::max(1.0, (1.0 + 2.0 * r / w) / 3.0);
+  b.rest_clash = writes && share < 0.002 ? b.meet * 2.0 * r / w / 3.0 : 0.0;
+}
+
 // Counts the writes of a keyed batch's rows, which its first lookup found, for
 // the launch shape.  The counts per row are the submissions' (0 in between).
 cc_status count_keyed(cc_ctx *c, Batch &b) {
@@ -245,15 +269,13 @@ cc_status count_keyed(cc_ctx *c, Batch &b) {
     (void)hipGetLastError();
     return CC_OK;  // the shape for unknown rows will do
   }
-  uint64_t res[2] = {};
+  uint64_t res[3] = {};
   HIP_OR(c, launch_count_writes(c->stream, b.d_ops, b.n_ops, c->d_cnt, (uint32_t *)c->d_sub, c->d_ingest, nullptr,
                                 c->n_cu));
   HIP_OR(c, hipMemcpyAsync(res, c->d_ingest, sizeof res, hipMemcpyDeviceToHost, c->stream));
   HIP_OR(c, hipStreamSynchronize(c->stream));
   trim_sub(c);
-  b.shape_known = true;
-  b.shape_writes = res[0];
-  b.meet = (double)res[1] / ((double)b.n_txns * (double)b.n_txns);
+  set_conflicts(b, res[0], res[1], res[2]);
   return CC_OK;
 }
 
@@ -893,8 +915,8 @@ static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &
 // (0: one per compute unit).  A transaction's attempt takes 2-4 us of round
 // trips, so that the transactions in flight, T, are the throughput until they
 // conflict.  share: of the batch's transactions, those that write its most
-// written row; meet: the expected conflicts of a random pair (Batch::meet), so
-// that T of them have T x meet each.  known: false where the rows were not
+// written row; clash: the expected conflicts of a random pair (Batch::clash), so
+// that T of them have T x clash each.  known: false where the rows were not
 // counted (a keyed batch of few transactions).
 //
 // Measured with 256 compute units, run time in ms at T = 256 (64 lanes),
@@ -902,31 +924,51 @@ static void plan_engine(const uint64_t *cand, int nc, const std::vector<Table> &
 // kernel / TicToc / MVCC, 16 ops:
 //   Zipf 0.8 (share 0.06), 65,536 txns: 12.7/15.4/16.9  14.1/15.8/18.9
 //     14.1/15.8/19.3  31/39/45  39/46/54
-//   Zipf 0.6 (0.005, meet 1.4e-4), 65,536: 1.13/1.19/1.43  0.96/1.16/1.59
+//   Zipf 0.6 (0.005, clash 1.4e-4), 65,536: 1.13/1.19/1.43  0.96/1.16/1.59
 //     1.09/1.24/1.56  1.63/2.35/3.37  2.3/3.4/4.2
-//   Zipf 0.6, a tenth writes (0.001, 6e-6), 262,144: 4.0/4.0/4.2  2.4/2.4/2.9
+//   Zipf 0.6, a tenth writes (0.001, 4e-5), 262,144: 4.0/4.0/4.2  2.4/2.4/2.9
 //     1.5/1.6/2.0  1.6/2.3/3.8  2.6/3.3/4.5
 //   uniform, 65,536 rows (< 0.001, 1e-3), 65,536: 1.22/1.38/1.35
 //     1.05/1.16/1.09  0.89/1.03/0.83  1.6/2.3/1.4  3.0/3.6/2.4
 //   uniform, 1M rows (6e-5): 1.03/1.03/1.06  0.59/0.57/0.63  0.45/0.46/0.45
 //     0.22/0.26/0.28  0.51/0.55/0.38
 //   uniform, 4M rows (1.5e-5), OCC: 0.45 at T = 1024, 0.27 at 16384
-// and 4,096 txns of 4 ops on 1,024 rows (meet 3.9e-3), OCC's kernel: 0.27 at
+//   Zipf 0.3 on 65,536 rows, a tenth writes (< 0.001, 3e-4), 16,384:
+//     0.21/0.22/0.24  0.12/0.13/0.16  0.12/0.13/0.12  0.13/0.20/0.16
+// and 4,096 txns of 4 ops on 1,024 rows (clash 3.9e-3), OCC's kernel: 0.27 at
 // 128, 0.22 at 256, 0.29 at 512, 0.41 at 4096; 8,192 of 16 ops on 4,096 rows
 // (1.6e-2) 1.51 at 64, 1.42 at 256, 2.0 at 1024, on 1,024 rows (6e-2) 4.4 at
-// 64, 6.0 at 256, 6.6 at 1024 (MVCC 3.6, 3.8, 4.1).  Transactions of at most 4 ops
-// use 4 lanes with one slot each: uniform on 4M rows, 2^14 txns 60 us with 4096
-// in flight and 106 with 16384, 2^18 443 and 499, 2^20 1661 and 1733.
+// 64, 6.0 at 256, 6.6 at 1024 (MVCC 3.6, 3.8, 4.1).
+//
+// Where few are in flight they have 64 lanes each, rather than 16 on a quarter
+// of the compute units (but not the shortest: 4,096 txns of 1 op on 300 rows, OCC
+// 0.12 with 16 lanes and 0.15 with 64); those of more than 16 ops, which 16 lanes
+// hold in four slots with longer attempts, up to where 900 could be.
+// T = 256 with 64 lanes, 256 and 1024 with 16; OCC's kernel / TicToc / wait-die / TO:
+//   16 ops, uniform on 16,384 rows (4e-3), 16,384 txns: 0.72/0.93/0.62/0.60
+//     0.84/0.98/0.82/0.68  0.79/1.02/0.80/0.59
+//   64 ops, Zipf 0.3 on 262,144 rows, a tenth writes (1.2e-3), 8,192:
+//     0.27/0.27/0.26/0.25  0.39/0.50/0.37/0.32  0.35/0.46/0.37/0.20
+//   33-64 ops, half writes (2.7e-3): 0.27/0.41/0.28/0.25  0.47/0.69/0.60/0.27
+//     0.45/0.72/0.67/0.24
+//   64 ops, Zipf 0.3 on 2M rows, half writes (6e-4): 0.23/0.24/0.21/0.23
+//     0.30/0.37/0.26/0.25  0.17/0.22/0.16/0.13
+// Timestamp ordering, whose rows are held shortest, prefers more in flight.
+// Transactions of at most 4 ops use 4 lanes with one slot each: uniform on 4M
+// rows, 2^14 txns 60 us with 4096 in flight and 106 with 16384, 2^18 443 and
+// 499, 2^20 1661 and 1733.
 struct Shape {
   uint32_t lanes, waves;
   int grid;
 };
-static Shape plain_shape(uint32_t max_ops, bool known, double share, double meet, int n_cu) {
+static Shape plain_shape(int scheme, uint32_t max_ops, bool known, double share, double clash, int n_cu) {
   if (max_ops > 64) return {64, 1, 0};
-  // 16 lanes, and no more in flight than conflict about once; but 256, or what
-  // conflict four times, or 64
+  // no more in flight than conflict about once; but 256, or what conflict four
+  // times, or 64
   auto limited = [&]() -> Shape {
-    const double t = meet > 0 ? std::max({64.0, std::min(256.0, 4.0 / meet), 1.0 / meet}) : 1e9;
+    const double t = clash > 0 ? std::max({64.0, std::min(256.0, 4.0 / clash), 1.0 / clash}) : 1e9;
+    const double few = max_ops <= 4 ? 0.0 : max_ops <= 16 ? 256.0 : scheme == CC_TO ? 400.0 : 900.0;
+    if (t <= few) return {64, 1, t >= (double)n_cu ? 0 : (int)t};
     return {16, 1, t / 4 >= (double)n_cu ? 0 : (int)(t / 4)};
   };
   if (!known) {
@@ -936,8 +978,8 @@ static Shape plain_shape(uint32_t max_ops, bool known, double share, double meet
   }
   if (share >= 0.02) return {64, 1, 0};
   if (share >= 0.001) return limited();
-  if (meet * (double)n_cu * 64 <= 0.3) return {4, max_ops <= 4 ? 1u : 4u, 0};
-  if (meet * (double)n_cu * 16 <= 0.75) return {4, 1, 0};
+  if (clash * (double)n_cu * 64 <= 0.3) return {4, max_ops <= 4 ? 1u : 4u, 0};
+  if (clash * (double)n_cu * 16 <= 0.75) return {4, 1, 0};
   return limited();
 }
 
@@ -958,7 +1000,7 @@ static bool engine_pays(const Batch &b, int n_cu) {
   const double n = (double)b.n_txns;
   if (b.meet * std::min(n, 4096.0) < 0.05) return false;
   const double share = (double)b.hot_writes / n;
-  const Shape s = plain_shape(b.max_ops, true, share, b.meet, n_cu);
+  const Shape s = plain_shape(b.scheme, b.max_ops, true, share, b.clash, n_cu);
   const double t = std::min(n, (double)(s.grid ? s.grid : n_cu) * s.waves * (64.0 / s.lanes));
   const double attempt = s.waves > 1 ? 35.0 : s.lanes == 4 ? 7.5 : 5.0;
   const double kernel = 25.0 + std::max(n / t * (1.0 + 1.4 * b.meet * t) * attempt, 2.9 * (double)b.hot_writes);
@@ -977,9 +1019,7 @@ static void plan_hot_rows(const uint64_t *res, const std::vector<Table> &tables,
   const uint32_t top = (uint32_t)res[INGEST_TOP];
   b.hot_known = true;
   b.hot_writes = top;
-  b.shape_known = true;
-  b.shape_writes = top;
-  b.meet = b.n_txns ? (double)res[INGEST_PAIRS] / ((double)b.n_txns * (double)b.n_txns) : 0.0;
+  set_conflicts(b, top, res[INGEST_PAIRS], res[INGEST_WRITES]);
   if (b.scheme == CC_OCC && !b.keyed) {
     plan_engine(cand, nc, tables, b);
     b.eng_default = engine_pays(b, n_cu);
@@ -1556,15 +1596,15 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   int grid = 0;
   auto choose_shape = [&]() {
     hot_share = b.shape_known && b.n_txns ? (double)b.shape_writes / (double)b.n_txns : 1.0;
-    // (after the engine by the hot-row map nothing is left to conflict)
+    // (after the engine by the hot-row map no two transactions write one row)
     no_hot_row = hot_share < 0.001 || (use_eng && b.eng_default);
     contended = !no_hot_row && hot_share >= 0.02;
     lanes = p.lanes_per_txn;
     wpw = p.waves_per_wg;
     grid = (int)p.grid;
     if (lanes == 0 && p.mode == CC_MODE_PLAIN && b.scheme != CC_GACCO && b.scheme != CC_GPUTX) {
-      const Shape sh = plain_shape(b.max_ops, b.shape_known, no_hot_row ? 0.0 : hot_share,
-                                   use_eng && b.eng_default ? 0.0 : b.meet, c->n_cu);
+      const Shape sh = plain_shape(b.scheme, b.max_ops, b.shape_known, no_hot_row ? 0.0 : hot_share,
+                                   use_eng && b.eng_default ? b.rest_clash : b.clash, c->n_cu);
       lanes = sh.lanes;
       if (wpw == 0) {
         wpw = sh.waves;
@@ -1983,7 +2023,6 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   uint64_t res[INGEST_N] = {};
   hipError_t e = launch_ingest(c->stream, ia, c->n_cu);
   // the rows' writes, for the launch shape (the owner words are free again)
-  static_assert(INGEST_PAIRS == INGEST_TOP + 1, "the counts' results");
   if (e == hipSuccess && c->d_cnt && n_ops)
     e = launch_count_writes(c->stream, b.d_ops, n_ops, c->d_cnt, ia.owner, ia.out + INGEST_TOP, ia.out + INGEST_ERR,
                             c->n_cu);
@@ -2003,11 +2042,7 @@ cc_status cc_run_static(cc_ctx *c, const cc_txn *txns, uint64_t n_txns, const cc
   }
   b.max_ops = (uint32_t)res[INGEST_MAX_OPS];
   b.has_slot = (res[INGEST_KINDS] & 1) != 0;
-  if (c->d_cnt && n_txns) {
-    b.shape_known = true;
-    b.shape_writes = res[INGEST_TOP];
-    b.meet = (double)res[INGEST_PAIRS] / ((double)n_txns * (double)n_txns);
-  }
+  if (c->d_cnt && n_txns) set_conflicts(b, res[INGEST_TOP], res[INGEST_PAIRS], res[INGEST_WRITES]);
   const cc_status st = run_batch(c, b, p, false);
   for (uint32_t i = 0; i < n_counters; ++i) counters[i] = i < CC_N_STATS ? b.stats[i] : 0;
   return st;

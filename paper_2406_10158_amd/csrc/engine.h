@@ -317,6 +317,7 @@ enum IngestOut {
   INGEST_N_CAND,
   INGEST_TOP,        // writes to the most written row
   INGEST_PAIRS,      // sum over the rows of c (c - 1), c writes: ordered pairs of writes that meet
+  INGEST_WRITES,     // sum over the rows of c
   INGEST_CAND,       // PLAN_CAND x (count << 32 | ~row), most written first, 0: none
   INGEST_N = INGEST_CAND + PLAN_CAND
 };
@@ -361,7 +362,7 @@ struct IngestArgs {
 hipError_t launch_ingest(hipStream_t s, const IngestArgs &a, int n_cu);
 
 // Counts a batch's writes per global row from its descriptors: out[0] = the most
-// written row's, out[1] = sum of c (c - 1) over the rows.  cnt: a count per
+// written row's, out[1] = sum of c (c - 1) over the rows, out[2] = sum of c.  cnt: a count per
 // global row, 0 before and after; rows: n_ops scratch words; err: nothing is
 // counted unless it holds ~0 (nullptr: well formed).
 hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
@@ -442,9 +443,9 @@ constexpr uint64_t STATIC_OFF_TXNS = STATIC_OFF_OPS + (uint64_t)CC_STATIC_MAX_OP
 constexpr uint64_t STATIC_OFF_LIST = STATIC_OFF_TXNS + (uint64_t)CC_STATIC_MAX_TXNS * sizeof(DevTxn);
 constexpr uint64_t STATIC_OFF_OWNER = STATIC_OFF_LIST + (uint64_t)CC_STATIC_MAX_TXNS * sizeof(uint32_t);
 constexpr uint64_t STATIC_OFF_INGEST = STATIC_OFF_OWNER + (uint64_t)CC_STATIC_MAX_OPS * sizeof(uint32_t);
-constexpr uint64_t STATIC_SCRATCH_BYTES = STATIC_OFF_INGEST + 512;
+constexpr uint64_t STATIC_SCRATCH_BYTES = STATIC_OFF_INGEST + 1024;
 static_assert(STATIC_OFF_TXNS % 256 == 0 && STATIC_OFF_LIST % 256 == 0 && STATIC_OFF_OWNER % 256 == 0 &&
-                  STATIC_OFF_INGEST % 256 == 0 && INGEST_N * sizeof(uint64_t) <= 512,
+                  STATIC_OFF_INGEST % 256 == 0 && INGEST_N * sizeof(uint64_t) <= 1024,
               "static scratch regions are 256-byte aligned");
 // Device address of `device`'s array; `device` must be current.  Resolved
 // with hipGetSymbolAddress on a device's first call, then kept.

@@ -402,6 +402,35 @@ __device__ __forceinline__ uint32_t count_bin(uint32_t c) { return c < (uint32_t
 __device__ __forceinline__ uint64_t plan_key(uint32_t row, uint32_t c) { return ((uint64_t)c << 32) | (uint32_t)~row; }
 __device__ __forceinline__ uint32_t key_row(uint64_t k) { return ~(uint32_t)k; }
 
+// A workgroup's largest count and its sums of c (c - 1) and of c into out[0], [1]
+// and [2], by one thread: atomics of every wavefront on the same words took 10 us
+// a word with 8,192 of them.
+template <int NT>
+__device__ __forceinline__ void add_counts(uint64_t *out, uint32_t top, uint64_t pairs, uint64_t writes) {
+  __shared__ uint64_t part[3 * (NT / 64)];
+  const int w = threadIdx.x / 64;
+  top = (uint32_t)wave_max(top);
+  pairs = wave_sum(pairs);
+  writes = wave_sum(writes);
+  if (__lane_id() == 0) {
+    part[3 * w] = top;
+    part[3 * w + 1] = pairs;
+    part[3 * w + 2] = writes;
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int i = 1; i < NT / 64; ++i) {
+    top = (uint32_t)part[3 * i] > top ? (uint32_t)part[3 * i] : top;
+    pairs += part[3 * i + 1];
+    writes += part[3 * i + 2];
+  }
+  if (!writes) return;
+  atomicMax((unsigned long long *)&out[0], (unsigned long long)top);
+  if (pairs) add_word(&out[1], pairs);
+  add_word(&out[2], writes);
+}
+static_assert(INGEST_PAIRS == INGEST_TOP + 1 && INGEST_WRITES == INGEST_TOP + 2, "the counts' results");
+
 // Four ops a thread and step, so that four rows' counts are on their way at once.
 constexpr int PLAN_STEP = 4;
 
@@ -415,7 +444,7 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
   for (uint32_t i = tid; i < (uint32_t)PLAN_COUNTS; i += NT) lds[i] = 0;
   __syncthreads();
   uint32_t top = 0;
-  uint64_t pairs = 0;
+  uint64_t pairs = 0, writes = 0;
   for (uint64_t i0 = (uint64_t)b * NT * PLAN_STEP; i0 < a.n_ops; i0 += (uint64_t)nb * NT * PLAN_STEP) {
     uint32_t row[PLAN_STEP], c[PLAN_STEP];
 #pragma unroll
@@ -431,6 +460,7 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
       if (row[j] != RC_NONE) {
         a.cnt[row[j]] = 0;
         pairs += (uint64_t)c[j] * (c[j] - 1);
+        writes += c[j];
         if (a.hot_map && c[j] > 1) atomicOr(&a.hot_map[row[j] >> 5], 1u << (row[j] & 31));
         atomicAdd(&lds[count_bin(c[j])], 1u);
         top = c[j] > top ? c[j] : top;
@@ -441,10 +471,7 @@ __device__ __forceinline__ void part_counts(const IngestArgs &a, uint32_t *lds, 
   __syncthreads();
   for (uint32_t i = tid; i < (uint32_t)PLAN_COUNTS; i += NT)
     if (lds[i]) atomicAdd(&a.hist[i], lds[i]);
-  top = (uint32_t)wave_max(top);
-  pairs = wave_sum(pairs);
-  if (__lane_id() == 0 && top) atomicMax((unsigned long long *)&a.out[INGEST_TOP], (unsigned long long)top);
-  if (__lane_id() == 0 && pairs) add_word(&a.out[INGEST_PAIRS], pairs);
+  add_counts<NT>(&a.out[INGEST_TOP], top, pairs, writes);
   if (!last_block(&a.out[INGEST_DONE1], nb)) return;
   if (tid < 64) {
     uint32_t cut = 0;
@@ -617,9 +644,13 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
   __shared__ PackLds<1024, true> s;
   __shared__ uint64_t keys[INGEST_LOCAL];
   __shared__ uint32_t n_keys;
+  __shared__ unsigned long long all_sums;
   const uint32_t tid = threadIdx.x;
   part_reset(a, tid, 1024);
-  if (tid == 0) n_keys = 0;
+  if (tid == 0) {
+    n_keys = 0;
+    all_sums = 0;
+  }
   const bool loose = __syncthreads_or(part_headers(a, tid, 1024));
   if (loose) {
     part_fill(a, tid, 1024);
@@ -630,19 +661,25 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
   part_pack<1024, true>(a, s, loose, 0, 1);
   if (!a.cnt) return;
   __syncthreads();
-  uint64_t pairs = 0;
+  // (at most INGEST_LOCAL writes: their sum and their pairs' fit one word)
+  static_assert((uint64_t)INGEST_LOCAL * INGEST_LOCAL < (1ull << 32), "pairs below bit 32");
+  uint64_t sums = 0;
   for (uint32_t i = tid; i < rc_slots<true>; i += 1024)
     if (s.cnt[i]) {
       keys[atomicAdd(&n_keys, 1u)] = plan_key(s.row[i], s.cnt[i]);
-      pairs += (uint64_t)s.cnt[i] * (s.cnt[i] - 1);
+      sums += (uint64_t)s.cnt[i] * (s.cnt[i] - 1) + ((uint64_t)s.cnt[i] << 32);
       if (a.hot_map && s.cnt[i] > 1) atomicOr(&a.hot_map[s.row[i] >> 5], 1u << (s.row[i] & 31));
     }
-  pairs = wave_sum(pairs);
-  if (__lane_id() == 0 && pairs) add_word(&a.out[INGEST_PAIRS], pairs);
+  sums = wave_sum(sums);
+  if (__lane_id() == 0 && sums) atomicAdd(&all_sums, (unsigned long long)sums);
   __syncthreads();
   sort_candidates<1024>(a, keys, n_keys);
   __syncthreads();
-  if (tid == 0) a.out[INGEST_TOP] = ld_word(&a.out[INGEST_CAND]) >> 32;
+  if (tid == 0) {
+    a.out[INGEST_TOP] = ld_word(&a.out[INGEST_CAND]) >> 32;
+    a.out[INGEST_PAIRS] = all_sums & 0xFFFFFFFFull;
+    a.out[INGEST_WRITES] = all_sums >> 32;
+  }
 }
 
 // The counts of a batch whose rows are known only at the run (keyed), or which
@@ -651,7 +688,7 @@ __global__ void __launch_bounds__(1024) ingest_local_kernel(IngestArgs a) {
 __global__ void __launch_bounds__(256) count_mark_kernel(const DevOp *ops, uint64_t n_ops, uint32_t *cnt,
                                                          uint32_t *rows, uint64_t *out, const uint64_t *err) {
   if (err && ld_word(err) != ~0ull) return;  // malformed: the descriptors are not the batch's
-  if (blockIdx.x == 0 && threadIdx.x < 2) out[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x < 3) out[threadIdx.x] = 0;
   const uint64_t step = (uint64_t)gridDim.x * 256;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_ops; i += step) {
     const uint32_t rk = ops[i].rowk;
@@ -663,15 +700,8 @@ __global__ void __launch_bounds__(256) count_mark_kernel(const DevOp *ops, uint6
 __global__ void __launch_bounds__(256) count_sum_kernel(const uint32_t *rows, uint64_t n_ops, uint32_t *cnt,
                                                         uint64_t *out, const uint64_t *err) {
   if (err && ld_word(err) != ~0ull) return;
-  __shared__ uint32_t s_top;
-  __shared__ unsigned long long s_pairs;
-  if (threadIdx.x == 0) {
-    s_top = 0;
-    s_pairs = 0;
-  }
-  __syncthreads();
   uint32_t top = 0;
-  uint64_t pairs = 0;
+  uint64_t pairs = 0, writes = 0;
   const uint64_t step = (uint64_t)gridDim.x * 256;
   for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n_ops; i += step) {
     const uint32_t r = rows[i];
@@ -679,19 +709,10 @@ __global__ void __launch_bounds__(256) count_sum_kernel(const uint32_t *rows, ui
     const uint32_t c = cnt[r];
     cnt[r] = 0;
     pairs += (uint64_t)c * (c - 1);
+    writes += c;
     top = c > top ? c : top;
   }
-  top = (uint32_t)wave_max(top);
-  pairs = wave_sum(pairs);
-  if (__lane_id() == 0) {
-    atomicMax(&s_top, top);
-    atomicAdd(&s_pairs, (unsigned long long)pairs);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0 && s_top) {
-    atomicMax((unsigned long long *)&out[0], (unsigned long long)s_top);
-    add_word(&out[1], (uint64_t)s_pairs);
-  }
+  add_counts<256>(out, top, pairs, writes);
 }
 hipError_t launch_count_writes(hipStream_t s, const DevOp *ops, uint64_t n_ops, uint32_t *cnt, uint32_t *rows,
                                uint64_t *out, const uint64_t *err, int n_cu) {

@@ -1,4 +1,4 @@
-"""The library's choice of lanes where the caller sets the wavefronts per workgroup.
+"""The library's choice of a launch shape, alone and beside the caller's wavefronts per workgroup.
 
 A kernel's variant holds so many operations a lane that at most 4, 8 or 16
 wavefronts fit.  With lanes_per_txn 0 the lanes follow the batch's contention,
@@ -39,6 +39,19 @@ def _batch(share, ops):
 def test_lanes_leave_room_for_the_callers_wavefronts(scheme, share, ops, waves):
     tabs, b = _batch(share, ops)
     run_and_check(tabs, b, scheme, waves_per_wg=waves, flags=_flags(scheme))
+
+
+@pytest.mark.parametrize("rows,ops", [(300, 4), (300, 5), (4_096, 16), (4_096, 17), (20_000, 64), (20_000, 65),
+                                      (262_144, 64), (2_000_000, 64)])
+@pytest.mark.parametrize("read_ratio", [0.1, 0.5, 0.9])
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_shapes_by_the_counted_conflicts(scheme, read_ratio, rows, ops):
+    # on both sides of the numbers of operations and of the conflicts at which the shape changes
+    tabs, b = wl.kv_workload(n_rows=rows, n_fields=1, n_txns=3_000, ops=(max(1, ops - 30), ops), theta=0.0,
+                             read_ratio=read_ratio, seed=rows + ops)
+    run_and_check(tabs, b, scheme)
+    if scheme == "occ":
+        run_and_check(tabs, b, scheme, flags=_flags(scheme))
 
 
 @pytest.mark.parametrize("waves", [9, 16])
