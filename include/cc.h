@@ -273,8 +273,11 @@ typedef struct {
   uint32_t max_epochs;    /* CC_MODE_EPOCH: epochs before CC_E_LIVELOCK; 0 = 1<<20 */
   uint32_t flags;         /* CC_RUN_* */
   uint32_t backoff_ns;    /* base of the randomised exponential back-off after an abort; 0 = 200 ns.
-                             It grows to 128 bases in CC_MODE_PLAIN's passes that defer (4096 where
-                             thousands of transactions are in flight for a hot row), 4096 elsewhere */
+                             It grows to 128 bases in CC_MODE_PLAIN's passes that defer, 256 with a hot
+                             row, 1024 where the counted conflicts are dense or nothing was counted
+                             and more than 256 transactions are in flight, 4096 under two-phase
+                             locking where they are dense and where thousands are in flight for a hot
+                             row; to 4096 elsewhere */
   uint32_t defer_after;   /* CC_MODE_PLAIN: attempts of a transaction within one pass before it is deferred
                              to the next pass, which runs 8x fewer workgroups (the last pass runs one
                              wavefront and never defers); 0 = 16.  CC_MODE_EPOCH: attempts per epoch;

@@ -1690,15 +1690,23 @@ static cc_status run_batch(cc_ctx *c, Batch &b, const cc_run_params &p, bool hos
   // in flight: OCC 2.30 -> 1.53 ms, TicToc 2.39 -> 1.62; Zipf 0.8, 256 in
   // flight: OCC 14.9 -> 12.7).  More where nearly all of a batch meets (16 ops,
   // 9 of 10 writes, Zipf 0.99 on 154,835 rows: 2PL 46.6 ms at 128, 38.1 at 4096; OCC
-  // 47.5 at 128, 46.8 at 1024, 48.7 at 4096), and where thousands in flight wait
-  // for a hot row (4096, Zipf 0.8: MVCC 45 ms at 128, 34 at 4096).
+  // 47.5 at 128, 46.8 at 1024, 48.7 at 4096), where that goes for most operations of
+  // a long transaction, whose attempts take as long (65-256 ops, a tenth writes,
+  // uniform on 50,000 rows: OCC 3.5 ms at 128, 2.9 at 1024, 3.4 at 4096; 2PL 3.7, 3.1,
+  // 3.4; on 5,000 rows 2PL 15.2, 14.8, 14.1; on 200,000 OCC 0.81, 0.92, 1.36; half
+  // writes on 100,000 OCC 1.24, 1.27; not TO and MVCC, 1.4 and 1.6 ms on 50,000), and
+  // where thousands in flight wait for a hot row (4096, Zipf 0.8: MVCC 45 ms at
+  // 128, 34 at 4096).
   auto choose_retries = [&]() {
     a.precheck = (p.flags & CC_RUN_PRECHECK) ? 2u : ((p.flags & CC_RUN_NO_PRECHECK) ? 0u : (contended ? 1u : 0u));
     const double in_flight = (double)(grid ? grid : c->n_cu) * wpw * (64.0 / lanes);
     if (p.mode != CC_MODE_PLAIN || (in_flight > 1024 && (!b.shape_known || contended))) a.backoff_cap = 12;
     else if (!b.shape_known) a.backoff_cap = in_flight <= 256 ? 7u : 10u;
     else if (b.meet > 0.1) a.backoff_cap = b.scheme == CC_2PL_NW || b.scheme == CC_2PL_WD ? 12u : 10u;
-    else a.backoff_cap = contended ? 8u : 7u;
+    else if (contended) a.backoff_cap = 8;
+    else if (b.clash * (double)b.n_ops > 4.0 * (double)b.n_txns && b.scheme != CC_TO && b.scheme != CC_MVCC)
+      a.backoff_cap = b.clash > 0.1 && (b.scheme == CC_2PL_NW || b.scheme == CC_2PL_WD) ? 12u : 10u;
+    else a.backoff_cap = 7;
   };
   choose_retries();
   a.n_late = 0;
