@@ -120,6 +120,18 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
     }
     if (ballot(txn >= 0) == 0) break;
     uint64_t now = wall_clock64();
+    if (a.n_from_ctl && take && attempts) {
+      // an epoch's retries all begin with its kernel: two that blocked each other
+      // would meet again, epoch after epoch.  They begin over a span that grows
+      // to 256 back-off bases, 51 us.  Run time in us without and with: 816 txns x
+      // 16 ops, uniform on 50,187 rows, OCC 272 and 201, TO 169 and 174; 10,489 x 7
+      // ops, 9 of 10 writes, Zipf 0.3 on 4,530 rows, TicToc 4500 and 1160; 32,768 x 8
+      // ops, Zipf 0.8 on 100,000 rows, wait-die 16,830 and 11,550, 2PL 17,220 and 8,590
+      // (25,180 and 18,130 with 64 bases, whose epochs go on as most of their
+      // retries fail); 202 txns that hardly meet 59.0 and 59.7
+      const uint32_t sh = attempts < 9 ? attempts - 1 : 8;
+      ready_at = now + mix64(((uint64_t)txn << 20) ^ attempts) % (((uint64_t)a.backoff_ticks << sh) + 1);
+    }
     if (a.budget_cap && txn >= 0 && now >= ready_at && !admitted) {
       // serving admission, first come first served on bytes: an arrived
       // transaction takes a position in a byte queue with one fetch_add on
