@@ -844,18 +844,24 @@ __device__ __forceinline__ int to_attempt(const Team<L> &t, Slots<K> &s, bool ac
 // Table 2).  Layout: bit 63 lock, bits 62-48 delta, bits 47-0 WTS.
 //   R1  write rows: try-lock with fetch_or (abort if held); read rows: load
 //       the word (abort if locked).
-//   R2  read values; commit_ts = max over write rows of RTS+1 and over read
-//       rows of WTS (team maximum).
+//   R2  read values; draw a ticket (tie-breaker for equal commit timestamps:
+//       only a reader of a row can share its writer's, and it draws after it has
+//       seen the word that the writer stored after its own draw); commit_ts = max
+//       over write rows of RTS+1 and over read rows of WTS (team maximum).
 //   R3  every read row must still carry the observed WTS and be unlocked (so
 //       the value read in R2 is that version's); if its RTS < commit_ts,
 //       extend RTS to commit_ts by CAS (if the delta would not fit in 15
 //       bits, WTS is raised instead -- only other readers of the old WTS are
 //       affected, and they abort).
-//       In the same round draw a ticket, the tie-breaker for equal commit
-//       timestamps: only a reader of a row can share its writer's, and it draws
-//       after it has seen the word that the writer stored after its own draw.
 //   R4  store values, wait, publish word = {WTS = commit_ts, delta = 0}.
 // Serial key (commit_ts, ticket).
+// The values beside the locks (on retries) and the ticket in R3 were tried: locks
+// are held for as many rounds, the longer ones, and what is loaded for an attempt
+// that fails on a lock is lost.  Run time in ms so and this way: 16 ops, half
+// writes, 100,000 txns, Zipf 0.99 on 10M rows 180 and 175; 9 of 10 writes on 150,000
+// rows 133 and 123; 64 ops, Zipf 0.9 on 1M rows 92 and 82; 100-256 ops on 5,000 rows
+// 22.8 and 20.4; Zipf 0.8 15.4 and 15.5; without contention 2-4% less (1M rows, 0.47
+// and 0.49; a tenth writes, Zipf 0.6, 1.57 and 1.62).
 // ===========================================================================
 constexpr uint64_t TT_LOCK = 1ull << 63;
 constexpr uint64_t TT_WTS_MASK = (1ull << 48) - 1ull;
@@ -886,30 +892,17 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
     pre_fail = t.any(fail);
   }
   const bool go = active && !pre_fail;
-  // locks and loads all issued before any result is looked at (see OCC's R1).
-  // After R0 also the values: a read-only row's comes after the word R0 saw,
-  // which R3 validates; a written row's is issued beside its lock, and is the
-  // row's value under the lock if the lock returns the WTS R0 saw (every commit
-  // raises it, and a writer whose install the load could have seen held the
-  // lock until it had).  Rows are then held for R1, R3 and the installs only.
-  // Not with several operations a lane: those transactions' attempts mostly
-  // fail on a lock, after which the values were loaded for nothing (100-256 ops
-  // on 5,000 rows, Zipf 0.3: 24.5 ms with the early values, 22.7 without; 256 ops on
-  // 20,000 rows, Zipf 0.6: 14.9 and 13.0).
-  const bool early = precheck && K == 1;
+  // locks and loads all issued before any result is looked at (see OCC's R1)
   bool issued[K];
-  uint64_t seen[K];
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     s.got[k] = false;
-    seen[k] = s.v[k];
     issued[k] = go && s.valid[k] && op_leader(s.rowk[k]) && (!precheck || op_written(s.rowk[k]));
     if (issued[k]) {
       uint64_t *w = a.words + op_row(s.rowk[k]);
       if (op_written(s.rowk[k])) s.v[k] = w_or<LATCH, STRICT>(a, w, TT_LOCK);
       else s.v[k] = ld_word(w);
     }
-    if (early && go && s.valid[k]) s.x[k] = ld_val(a.data + s.elem[k]);
   }
   order_point<STRICT>();
 #pragma unroll
@@ -917,10 +910,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
     if (!issued[k]) continue;
     const uint64_t o = s.v[k];
     if ((o & TT_LOCK) && blk == ~0u) blk = op_row(s.rowk[k]);
-    if (op_written(s.rowk[k])) {
-      s.got[k] = !(o & TT_LOCK);
-      fail |= early && tt_wts(o) != tt_wts(seen[k]);
-    }
+    if (op_written(s.rowk[k])) s.got[k] = !(o & TT_LOCK);
     fail |= (o & TT_LOCK) != 0;
   }
   s.block = blocking_row(t, blk);
@@ -935,24 +925,16 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     if (alive && s.valid[k]) {
-      if (!early) s.x[k] = ld_val(a.data + s.elem[k]);
+      s.x[k] = ld_val(a.data + s.elem[k]);
       if (op_leader(s.rowk[k])) {
         const uint64_t c = op_written(s.rowk[k]) ? tt_rts(s.v[k]) + 1 : tt_wts(s.v[k]);
         cts = c > cts ? c : cts;
       }
     }
   }
+  const uint64_t ticket = t.claim(&a.ctl->ticket, alive, 1) + 1;
   cts = t.max(cts);
   const bool overflow = alive && cts > TT_WTS_MASK - TT_DELTA_MAX;
-  if (ballot(alive && !early)) order_point<STRICT>();
-  // R3: the words and the ticket in one round
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    seen[k] = 0;
-    if (alive && !overflow && s.valid[k] && op_leader(s.rowk[k]) && !op_written(s.rowk[k]))
-      seen[k] = ld_word(a.words + op_row(s.rowk[k]));
-  }
-  const uint64_t ticket = t.claim(&a.ctl->ticket, alive, 1) + 1;
   order_point<STRICT>();
   bool bad = overflow;
 #pragma unroll
@@ -962,7 +944,7 @@ __device__ __forceinline__ int tictoc_attempt(const Team<L> &t, Slots<K> &s, boo
       // is still unlocked with the same WTS now (a writer installs values
       // while holding the lock, then publishes a new WTS)
       uint64_t *wp = a.words + op_row(s.rowk[k]);
-      uint64_t w = seen[k];
+      uint64_t w = ld_word(wp);
       bool done = false, b = false;
       for (int it = 0; it < CAS_RETRIES && !done && !b; ++it) {
         if (tt_wts(w) != tt_wts(s.v[k]) || (w & TT_LOCK)) {
