@@ -63,6 +63,42 @@ def algorithmic_bytes(batch) -> int:
             + batch.n_txns * (8 + 32))
 
 
+def engine_counts(batch, n_cells: int) -> dict:
+    """What OCC's hot-row engine does with its share of a batch: it takes no lock and draws no ticket from
+    memory, but sorts the accesses by cell (8 bits of the cell a pass) and scans them.
+
+    Streamed bytes: per op its descriptor read and listed (16 + 16 B) with its sort key and place (8 B),
+    per pass a histogram's read of the keys (4 B) and a pair read and written (8 + 8 B), the scan's read of
+    the pair (8 B); per transaction its descriptor and its outcome (16 + 32 B).  Random accesses: per op
+    the listed descriptor and the store of its read value, per cell its value, per written cell its store.
+    ``bytes`` is the least any execution moves: descriptors, read values, cells and outcomes once.
+    """
+    cell = (batch.table.astype(np.uint64) << np.uint64(40)) | (batch.row.astype(np.uint64) << np.uint64(8)) | batch.field
+    m, cells, written = batch.total_ops, len(np.unique(cell)), len(np.unique(cell[batch.kind != 0]))
+    passes = -(-max(n_cells - 1, 0).bit_length() // 8)
+    return {"passes": passes, "random_loads": m + cells, "random_stores": m + written,
+            "stream_bytes": m * (40 + 20 * passes + 8) + batch.n_txns * 48,
+            "bytes": m * (16 + 8) + cells * 8 + written * 8 + batch.n_txns * (8 + 32)}
+
+
+def access_seconds(acc: dict, probes: dict) -> float:
+    """Time of a batch's accesses (access_counts) at the probed rates: control words at the 80 MB
+    footprint's, values at the 880 MB footprint's."""
+    return (acc["word_loads"] / (probes["gather_80MB_Gops"] * 1e9)
+            + acc["value_loads"] / (probes["gather_880MB_Gops"] * 1e9)
+            + acc["word_atomics"] / (probes["atomic_80MB_Gops"] * 1e9)
+            + acc["value_stores"] / (probes["scatter_880MB_Gops"] * 1e9)
+            + acc["word_stores"] / (probes["scatter_80MB_Gops"] * 1e9)
+            + acc["stream_bytes"] / (probes["stream_GBps"] * 1e9))
+
+
+def engine_seconds(cnt: dict, probes: dict) -> float:
+    """The same for the hot-row engine's share (engine_counts)."""
+    return (cnt["random_loads"] / (probes["gather_880MB_Gops"] * 1e9)
+            + cnt["random_stores"] / (probes["scatter_880MB_Gops"] * 1e9)
+            + cnt["stream_bytes"] / (probes["stream_GBps"] * 1e9))
+
+
 def access_counts(batch) -> dict:
     """Memory operations one committed pass of the OCC hot path must issue, from the batch itself.
 
@@ -521,6 +557,21 @@ def main():
     torch.cuda.init()
     stream = torch.cuda.Stream()  # default priority; the engine issues all its work on it
     eng = binding.Engine(tables, device=0, stream=stream.cuda_stream)
+    # submission (outside the steps) from host arrays, and again from device arrays: it validates, packs, counts
+    # the rows' writes and, for OCC, splits off the hot-row engine's share
+    submission = {}
+    packed = binding.pack_batch(batch)
+    on_gpu = [torch.from_numpy(a.view(np.uint8).reshape(-1)).to("cuda") for a in packed]
+    torch.cuda.synchronize()
+    for name, arrays in (("host_arrays_ms", packed), ("device_arrays_ms", on_gpu)):
+        took = []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            one = binding.cc_submit_batch(eng.ctx, *arrays, binding.SCHEMES[args.scheme])
+            took.append((time.perf_counter() - t0) * 1e3)
+            eng.release(one)
+        submission[name] = round(min(took), 3)
+    del on_gpu, packed
     bid = eng.submit(batch, args.scheme)
     params = dict(lanes_per_txn=args.lanes, waves_per_wg=args.waves, grid=args.grid, flags=args.flags,
                   defer_after=args.defer_after, backoff_ns=args.backoff_ns)
@@ -572,7 +623,7 @@ def main():
         eng_txns = engine_transactions(out_last["serial_lo"], st["engine_txns"])
     k_step_s = float(np.mean(kernel_ns)) * 1e-9
     if len(eng_txns):
-        alg = algorithmic_bytes(batch.subset(eng_txns))
+        alg = engine_counts(batch.subset(eng_txns), 1)["bytes"]
         dom_s, launches, dom_kernel = float(np.mean(engine_ns)) * 1e-9, 1.0, "hot_engine"
     else:
         alg = algorithmic_bytes(batch)
@@ -601,13 +652,13 @@ def main():
     # measured random-access / atomic roofline and hot-row contention bound
     probes = run_probes(eng.ctx, binding, batch=batch, quick=True)
     acc = access_counts(batch)
-    # control words at the 80 MB rates, values at the 880 MB rates
-    t_roof = (acc["word_loads"] / (probes["gather_80MB_Gops"] * 1e9)
-              + acc["value_loads"] / (probes["gather_880MB_Gops"] * 1e9)
-              + acc["word_atomics"] / (probes["atomic_80MB_Gops"] * 1e9)
-              + acc["value_stores"] / (probes["scatter_880MB_Gops"] * 1e9)
-              + acc["word_stores"] / (probes["scatter_80MB_Gops"] * 1e9)
-              + acc["stream_bytes"] / (probes["stream_GBps"] * 1e9))
+    eng_cnt = None
+    if len(eng_txns):
+        # the engine sorts and scans its share; the rest runs the protocol
+        eng_cnt = engine_counts(batch.subset(eng_txns), sum(t.shape[0] * t.shape[1] for t in tables))
+        rest = batch.subset(np.setdiff1d(np.arange(batch.n_txns), eng_txns))
+        acc = access_counts(rest)
+    t_roof = access_seconds(acc, probes) + (engine_seconds(eng_cnt, probes) if eng_cnt else 0.0)
     x_roof = batch.n_txns / t_roof
     if args.scheme == "gacco":
         # the scan hands no row from transaction to transaction
@@ -625,11 +676,11 @@ def main():
     if len(eng_txns):
         # the engine hands no row from commit to commit; the rest runs after
         # it: its own hottest row at OCC's commit hand-off
-        rest = batch.subset(np.setdiff1d(np.arange(batch.n_txns), eng_txns))
         _, h_rest = workload.hottest_row_writes(rest)
         t_rest = h_rest * probes["commit_handoff_ns"] * 1e-9
         x_cont = batch.n_txns / t_rest if h_rest else float("inf")
-        engine_bound = {"engine_txns": int(len(eng_txns)), "rest_hot_row_writes": int(h_rest),
+        h = h_rest
+        engine_bound = {"engine_txns": int(len(eng_txns)), "accesses": eng_cnt, "rest_hot_row_writes": int(h_rest),
                         "rest_min_ms": round(t_rest * 1e3, 3),
                         "engine_ms": round(float(np.mean(engine_ns)) / 1e6, 3)}
     eff = min(x_roof, x_cont)
@@ -645,21 +696,38 @@ def main():
                           "peak_from": ("hot-row engine, then the rest of the batch: the rest's hottest row x the "
                                         "commit hand-off"
                                         if engine_bound and measured["active_bound"] == "contention" else
+                                        "the hot-row engine's sort and scan, then the rest's accesses, at the probed rates"
+                                        if engine_bound else
                                         "H x t_h: writes to the hottest row times the measured commit hand-off"
                                         if measured["active_bound"] == "contention" else
                                         "random loads, atomics, stores and streamed bytes at the probed rates")}
 
-    # the batch's most written row during the last step (OCC's lock-hold counters)
+    # the batch's most written row during the last step (OCC's lock-hold counters); in the engine
+    # nobody holds it, and its writes' share of the time is not measured
     hot_row = None
-    if args.scheme == "occ" and st["hot_acq"]:
-        # with the engine, the row is written only while the engine runs
-        span = st["engine_ns"] if st["engine_txns"] else st["kernel_ns"]
+    if args.scheme == "occ" and st["engine_txns"]:
+        hot_row = {"writes_H": st["hot_writes"], "in": "hot_engine"}
+    elif args.scheme == "occ" and st["hot_acq"]:
+        span = st["kernel_ns"]
         held = st["hot_hold_ns"] / max(span, 1)
         hot_row = {"writes_H": st["hot_writes"], "lock_acquisitions": st["hot_acq"],
                    "failed_holds": st["hot_failed"], "held_share": round(held, 4), "idle_share": round(1 - held, 4),
                    "hold_per_acquisition_ns": round(st["hot_hold_ns"] / st["hot_acq"], 1),
-                   "kernel_ns_per_hot_commit": round(span / max(st["hot_writes"], 1), 1),
-                   "in": "hot_engine" if st["engine_txns"] else "txn_kernel"}
+                   "kernel_ns_per_hot_commit": round(span / max(st["hot_writes"], 1), 1), "in": "txn_kernel"}
+
+    # the same batch through OCC's transaction kernel alone: the engine orders the transactions that write
+    # rows written more than once (found at submission) and runs them by a sort and a scan
+    protocol = None
+    if args.scheme == "occ" and st["engine_txns"]:
+        ms, att = [], []
+        for _ in range(4):
+            restore()
+            st2 = eng.run(bid, **dict(params, flags=args.flags | binding.CC_RUN_NO_HOT_ENGINE))
+            ms.append(st2["run_ns"] / 1e6)
+            att.append(st2["attempts"])
+        m = float(np.median(ms[1:]))
+        protocol = {"txn_per_s": round(batch.n_txns / (m / 1e3), 1), "run_ms": round(m, 3),
+                    "abort_rate": round((float(np.mean(att[1:])) - batch.n_txns) / batch.n_txns, 4)}
 
     cpu = None
     if not args.no_cpu_baseline:
@@ -685,6 +753,8 @@ def main():
         "roofline": roofline,
         "measured_roofline": measured,
         "hot_row": hot_row,
+        "submission": submission,
+        "occ_without_hot_engine": protocol,
         "cpu_baseline": cpu,
         "host_wall_s": round(wall, 3),
     }
