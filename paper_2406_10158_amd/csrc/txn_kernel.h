@@ -47,6 +47,25 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
   uint32_t pass_att = 0;    // attempts of txn in this pass
   uint64_t ready_at = 0;    // wall-clock tick before which the team waits
   bool done = false;        // no transactions left for this team
+  // An epoch's retries would all begin with its kernel, so that two that blocked
+  // each other met again, epoch after epoch.  Each team waits a time of its own
+  // before every transaction, within a span that doubles with the epochs (which the
+  // most attempts so far count) to 256 back-off bases, 51 us.  Run time in us without
+  // and with: 816 txns x 16 ops, uniform on 50,187 rows, OCC 278 and 202, TO 171 and
+  // 176; 10,489 x 7 ops, 9 of 10 writes, Zipf 0.3 on 4,530 rows, TicToc 3825 and 1156;
+  // 32,768 x 8 ops, Zipf 0.8 on 100,000 rows, wait-die 16,630 and 12,960, 2PL 18,310
+  // and 9,450; 202 txns that hardly meet 59.2 and 59.7.  A time for each transaction
+  // (wait-die 11,490, 2PL 8,720) costs every mode registers in the loop below: 2^20
+  // uniform OCC transactions 1980 -> 1995 us.  A wait before a team's first
+  // transaction alone leaves the retries of long lists together: wait-die 23,380.
+  uint32_t delay = 0;
+  if (a.n_from_ctl) {
+    const uint64_t epoch = ld_word(&a.ctl->stats[DS_MAX_ATTEMPTS]);
+    const uint64_t grown = (uint64_t)a.backoff_ticks << (epoch < 9 ? (epoch ? epoch - 1 : 0) : 8);
+    const uint64_t span = grown < 8192 ? grown : 8192;  // (whatever the caller's back-off, 82 us at most)
+    const uint64_t team = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / L;
+    if (epoch) delay = (uint32_t)(((mix64((team << 20) ^ epoch) >> 32) * span) >> 32);
+  }
   uint64_t n_commit = 0, n_att = 0, n_lock = 0, n_valid = 0, n_gave = 0, n_defer = 0, n_ovf = 0, max_att = 0;
   uint64_t t_useful = 0, t_abort = 0, t_wait = 0;  // per team, in leader lanes
   uint64_t reserved = 0;    // serving: bytes this team's transaction reserved (0: none)
@@ -95,7 +114,7 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
         attempts = a.pass ? a.out[txn].attempts : 0;
         pass_att = 0;
         // serving: not before the transaction's arrival
-        ready_at = a.arrival ? start_clock + (uint64_t)a.arrival[txn] : 0;
+        ready_at = a.arrival ? start_clock + (uint64_t)a.arrival[txn] : delay ? wall_clock64() + delay : 0;
         reserved = 0;
         admitted = false;
         resume = false;
@@ -120,18 +139,6 @@ __global__ void __launch_bounds__(MaxThreads<K>::value) txn_kernel(RunArgs a) {
     }
     if (ballot(txn >= 0) == 0) break;
     uint64_t now = wall_clock64();
-    if (a.n_from_ctl && take && attempts) {
-      // an epoch's retries all begin with its kernel: two that blocked each other
-      // would meet again, epoch after epoch.  They begin over a span that grows
-      // to 256 back-off bases, 51 us.  Run time in us without and with: 816 txns x
-      // 16 ops, uniform on 50,187 rows, OCC 272 and 201, TO 169 and 174; 10,489 x 7
-      // ops, 9 of 10 writes, Zipf 0.3 on 4,530 rows, TicToc 4500 and 1160; 32,768 x 8
-      // ops, Zipf 0.8 on 100,000 rows, wait-die 16,830 and 11,550, 2PL 17,220 and 8,590
-      // (25,180 and 18,130 with 64 bases, whose epochs go on as most of their
-      // retries fail); 202 txns that hardly meet 59.0 and 59.7
-      const uint32_t sh = attempts < 9 ? attempts - 1 : 8;
-      ready_at = now + mix64(((uint64_t)txn << 20) ^ attempts) % (((uint64_t)a.backoff_ticks << sh) + 1);
-    }
     if (a.budget_cap && txn >= 0 && now >= ready_at && !admitted) {
       // serving admission, first come first served on bytes: an arrived
       // transaction takes a position in a byte queue with one fetch_add on
