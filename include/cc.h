@@ -166,7 +166,8 @@ typedef struct {
  *                  later pass with 8x fewer workgroups.
  *   CC_MODE_EPOCH  batching: in each epoch every pending transaction gets
  *                  defer_after (default 1) attempts on a persistent grid; the
- *                  aborted ones wait for the next epoch.  Four epochs are
+ *                  aborted ones wait for the next epoch, in which each waits
+ *                  up to 256 back-off bases before it begins.  Four epochs are
  *                  captured as one hipGraph and replayed until nothing is
  *                  pending (max_epochs bounds the total: CC_E_LIVELOCK).
  *   CC_MODE_SERVE  continuous batching over a stream: transactions are taken
@@ -192,16 +193,17 @@ enum cc_mode { CC_MODE_PLAIN = 0, CC_MODE_EPOCH = 1, CC_MODE_SERVE = 2 };
 #define CC_RUN_WAIT_UNLOCK 0x4u   /* reserved; always rejected with CC_E_INVAL (a retry-when-free policy
                                      whose teams of one wavefront could retry in lockstep and livelock
                                      in the final single-wavefront pass; the code path is removed) */
-#define CC_RUN_PRECHECK 0x8u      /* OCC, TicToc, TO and MVCC: an extra first round loads every row's word and aborts before
+#define CC_RUN_PRECHECK 0x8u      /* OCC and TicToc: an extra first round loads every row's word and aborts before
                                      taking any lock if one is held -- on every attempt.  By default it
                                      runs from a transaction's second attempt on (a failure is the
                                      sign of contention) when the batch's most written row takes writes
                                      from at least 2% of its transactions, and never below that, where
                                      the extra round costs more than it saves.  CC_E_INVAL for another
-                                     scheme, or together with CC_RUN_NO_PRECHECK.  TO and MVCC look at every word
-                                     before they take anything in any case: neither flag changes them */
-#define CC_RUN_NO_PRECHECK 0x10u  /* OCC, TicToc, TO and MVCC: never run the pre-check round (CC_E_INVAL for
-                                     another scheme) */
+                                     scheme, or together with CC_RUN_NO_PRECHECK.  Accepted for TO and MVCC, which look
+                                     at every word before they take anything in any case: neither flag changes them */
+#define CC_RUN_NO_PRECHECK 0x10u  /* OCC and TicToc: never run the pre-check round; accepted for TO and MVCC,
+                                     whose first round looks at the words in any case (CC_E_INVAL for another
+                                     scheme) */
 #define CC_RUN_LATCH 0x40u        /* latch variants of the non-deterministic schemes (paper Section 4.2,
                                      Exp-7): a 32-bit latch per row guards its control word, and every
                                      update of the word is a critical section [latch, load, store,
@@ -259,10 +261,11 @@ typedef struct {
   uint32_t waves_per_wg;  /* 64-lane wavefronts per workgroup, 1..16; 0 = chosen by contention */
   uint32_t grid;          /* workgroups of the first pass; 0 = one per compute unit, or, where lanes and
                              waves are 0 too, chosen by contention.
-                             CC_MODE_PLAIN, by the writes counted at submission: lanes, waves and
-                             workgroups that keep about as many transactions in flight as conflict
-                             once with one another, 64 to 16384, and 256 with 64 lanes each where 2%
-                             of the transactions write one row.
+                             CC_MODE_PLAIN, by the writes counted at submission and the reads they
+                             meet: lanes, waves and workgroups that keep about as many transactions in
+                             flight as conflict once with one another, 64 to 16384, and 256 with 64
+                             lanes each where 2% of the transactions write one row.  With waves set,
+                             as many lanes as those leave room for.
                              Otherwise, from the share of transactions that write the batch's most
                              written row: below 0.1% (no hot row) 4 lanes per transaction and 4
                              wavefronts per workgroup when the longest transaction has at most 64

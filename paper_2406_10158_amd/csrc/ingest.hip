@@ -35,9 +35,9 @@
 // transaction, each loading its 16-byte ops one after another, took 1.67 ms
 // for 2^18 transactions x 16 ops, and the rows' counts were made on the host,
 // over every row of the tables: 40 ms more there, and 36 ms for 2^14 uneven
-// transactions (540k ops) from the host.  Now 0.55 ms for the whole submission
-// of 2^18 x 16 device-resident ops (pack 0.32, counts 0.14, pick 0.07) and
-// 0.45 ms for the uneven host batch; 30 us of kernel for 256 transactions x 4.
+// transactions (540k ops) from the host.  Now 0.46 ms for the whole submission
+// of 2^18 x 16 device-resident ops (pack 0.30, counts 0.10, pick 0.07) and
+// 0.43 ms for the uneven host batch; 30 us of kernel for 256 transactions x 4.
 #include "select.h"
 
 namespace cce {
@@ -222,8 +222,7 @@ __device__ __forceinline__ void part_pack(const IngestArgs &a, PackLds<NT, LOCAL
     }
     const uint32_t chunks = (longest + IG_L - 1) / IG_L;
     // an op and its row's identity: its key on an indexed table (keyed batch), else its row
-    // (a select between the two: a key loaded under the lane's own condition was
-    // miscompiled, the row's register reused for the condition)
+    // (the key is loaded with the op, keyed or not, and selected afterwards)
     auto load = [&](uint32_t i, cc_op *o, int64_t *id) {
       *o = cc_op{0, 0, 0, 0, 0};
       int64_t key = 0;
